@@ -130,11 +130,11 @@ gpe_status lap_all(gpe_batch* b, const std::vector<Item>& g, const std::vector<c
       const gpe_handle* h = g[i].c->h;
       const LapAxis& ax = h->ax[a];
       recs[i] = LapArgs<T>{in[i], a == 0 ? nullptr : out[i], out[i], twid<T>(ax), nullptr, nullptr, nullptr,
-                           ax.lamc, ax.nlines, h->npts, 0, ax.inner, ax.n, nullptr};
-      nb[i] = lap_batch_blocks(ax.n, ax.nlines);
+                           ax.lamc, h->npts, 0, ax.inner, ax.n, nullptr};
+      nb[i] = lap_batch_blocks(ax.n, ax.inner, h->npts, h->K, sizeof(T) == 4);
     }
     GPE_TRY(launch_records(b, recs, nb, [&](const LapArgs<T>* d, const Span& sp) {
-      return lap_batched<T>(d, sp, b->F, 0, b->st);
+      return lap_batched<T>(d, sp, b->F, 0, a == 0, b->st);
     }));
   }
   return GPE_OK;
@@ -401,10 +401,10 @@ gpe_status hvp_batched(gpe_batch* b, std::vector<Item>& g, bool riem, bool cg, b
         const LapAxis& ax = h->ax[a];
         const Req& r = *g[i].r;
         lr[a][i] = LapArgs<T>{r.a, r.c, r.c, twid<T>(ax), proj ? (sizeof(T) == 8 ? h->Xp : h->Xp32) : nullptr,
-                              h->res + 32, h->part, ax.lamc, ax.nlines, h->npts, h->pstride, ax.inner, ax.n,
+                              h->res + 32, h->part, ax.lamc, h->npts, h->pstride, ax.inner, ax.n,
                               cg ? h->res + CG_DONE : nullptr};
         if (proj && ab_local) lr[a][i].ab = AbSrc{h->part, h->pstride, xb[i], h->gram_pt, h->res};
-        lb[i] = lap_batch_blocks(ax.n, ax.nlines);
+        lb[i] = lap_batch_blocks(ax.n, ax.inner, h->npts, h->K, sizeof(T) == 4);
         nb[i].nb[6 + a] = lb[i];
       }
       GPE_TRY(offsets(h0, lb, &l0[a]));
@@ -442,7 +442,7 @@ gpe_status hvp_batched(gpe_batch* b, std::vector<Item>& g, bool riem, bool cg, b
                                    b->st));
   for (int a = 1; a < b->dim; ++a)
     GPE_HIP(h0, lap_batched<T>(reinterpret_cast<const LapArgs<T>*>(dl[a]),
-                               Span{reinterpret_cast<const int*>(dl0[a]), n, l0[a].back()}, b->F, 6 + a, b->st));
+                               Span{reinterpret_cast<const int*>(dl0[a]), n, l0[a].back()}, b->F, 6 + a, false, b->st));
   if (!kappa) return GPE_OK;
   const int post = cg ? POST_CG_KAPPA : riem ? POST_HVP_KAPPA : POST_HVP_KAPPA_E;
   GPE_HIP(h0, finalize_batched(reinterpret_cast<const FinArgs*>(dk), n, nq, post, b->F, b->st));

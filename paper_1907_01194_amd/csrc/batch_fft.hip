@@ -2,11 +2,11 @@
 // launch covers every problem of a batch, whatever its grid.  A workgroup
 // finds its problem from the workgroup offsets, then runs the same device
 // body as the single-problem kernels (fft.h) for that problem's line length,
-// chosen at run time among the powers of two 16..512.  All those lengths give
-// the same axis-pass workgroup size, and a fused x pass is launched with the
-// largest workgroup any of them needs (the bodies leave the extra threads
-// idle), so one launch can hold all of them; the dynamic LDS is the largest
-// any of them needs.
+// chosen at run time among the powers of two 16..512.  An axis-pass workgroup
+// is 256 threads for every length (several tiles where a tile needs fewer), a
+// fused x pass is launched with the largest workgroup any length needs (the
+// bodies leave the extra threads idle), so one launch can hold all of them;
+// the dynamic LDS is the largest any of them needs.
 #include "fft.h"
 #include "batch_ops.h"
 
@@ -25,20 +25,28 @@ bool batch_size_supported(int n) {
 }
 
 // ---------------------------------------------------------------- axis pass
-template <int... Ns> struct LapBatchGeo {
-  static constexpr int THREADS = Geo<16>::THREADS;
-  static constexpr bool uniform = ((Geo<Ns>::THREADS == THREADS) && ...);
-  static constexpr size_t lds_elems() {
-    size_t m = 0;
-    ((m = (size_t)(Ns + Geo<Ns>::LPB * (Ns + 1)) > m ? (size_t)(Ns + Geo<Ns>::LPB * (Ns + 1)) : m), ...);
-    return m;
-  }
-};
-using LapB = LapBatchGeo<16, 32, 64, 128, 256, 512>;
-static_assert(LapB::uniform, "batched axis pass needs one workgroup size for every line length");
+constexpr int kLapBatchThreads = 256;
 
-template <typename T>
-__global__ void __launch_bounds__(LapB::THREADS)
+// tiles per workgroup
+template <typename T, int N, bool CONTIG> constexpr int lap_groups() {
+  static_assert(kLapBatchThreads % AxGeo<T, N, CONTIG>::THREADS == 0, "tiles fill a batched workgroup");
+  return kLapBatchThreads / AxGeo<T, N, CONTIG>::THREADS;
+}
+
+template <typename T, bool CONTIG> constexpr size_t lap_batch_lds() {
+  size_t m = 0;
+#define GPE_CASE(NN)                                                                              \
+  {                                                                                               \
+    const size_t e = (size_t)padded_len<T>(NN) + (size_t)lap_groups<T, NN, CONTIG>() * AxGeo<T, NN, CONTIG>::TILE; \
+    m = e > m ? e : m;                                                                            \
+  }
+  GPE_BSIZES(GPE_CASE)
+#undef GPE_CASE
+  return m * sizeof(c_t<T>);
+}
+
+template <typename T, bool CONTIG>
+__global__ void __launch_bounds__(kLapBatchThreads)
 lap_batched_kernel(const LapArgs<T>* __restrict__ args, const int* __restrict__ blk0, int nprob, int F, int slot) {
   using T2 = c_t<T>;
   const int gb = sizeof(T) == 4 ? xcd_local_block((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x;
@@ -48,10 +56,10 @@ lap_batched_kernel(const LapArgs<T>* __restrict__ args, const int* __restrict__ 
   switch (a.n) {
 #define GPE_CASE(NN)                                                                                          \
   case NN:                                                                                                    \
-    lap_body<T, NN>(reinterpret_cast<const T2*>(a.in), reinterpret_cast<const T2*>(a.acc),                    \
-                    reinterpret_cast<T2*>(a.out), reinterpret_cast<const T2*>(a.tw), a.nlines, a.inner,       \
-                    (T)a.lamc, F, a.npts, reinterpret_cast<const T2*>(a.X), a.coef, a.part, a.stride, slot,   \
-                    blk, a.skip, a.ab);                                                                       \
+    lap_body<T, NN, CONTIG, lap_groups<T, NN, CONTIG>()>(                                                     \
+        reinterpret_cast<const T2*>(a.in), reinterpret_cast<const T2*>(a.acc), reinterpret_cast<T2*>(a.out),  \
+        reinterpret_cast<const T2*>(a.tw), a.inner, (T)a.lamc, F, a.npts,                           \
+        reinterpret_cast<const T2*>(a.X), a.coef, a.part, a.stride, slot, blk, a.skip, a.ab);                 \
     break;
     GPE_BSIZES(GPE_CASE)
 #undef GPE_CASE
@@ -59,26 +67,37 @@ lap_batched_kernel(const LapArgs<T>* __restrict__ args, const int* __restrict__ 
   }
 }
 
-int lap_batch_blocks(int n, long nlines) {
-  int lpb = 0;
+int lap_batch_blocks(int n, int inner, size_t npts, int K, bool c64) {
+  auto wgs = [&](long tiles, int groups) { return (int)((tiles + groups - 1) / groups); };
   switch (n) {
-#define GPE_CASE(NN) case NN: lpb = Geo<NN>::LPB; break;
+#define GPE_CASE(NN)                                                                                             \
+  case NN:                                                                                                       \
+    if (inner == 1)                                                                                              \
+      return c64 ? wgs(ax_tiles<float, NN, true>(K, npts), lap_groups<float, NN, true>())                        \
+                 : wgs(ax_tiles<double, NN, true>(K, npts), lap_groups<double, NN, true>());                     \
+    return c64 ? wgs(ax_tiles<float, NN, false>(K, npts), lap_groups<float, NN, false>())                        \
+               : wgs(ax_tiles<double, NN, false>(K, npts), lap_groups<double, NN, false>());
     GPE_BSIZES(GPE_CASE)
 #undef GPE_CASE
     default: return -1;
   }
-  return (int)((nlines + lpb - 1) / lpb);
+}
+
+template <typename T, bool CONTIG>
+static void launch_lb(const LapArgs<T>* args, const Span& sp, int F, int slot, hipStream_t st) {
+  constexpr size_t lds = lap_batch_lds<T, CONTIG>();
+  if (lds > 65536)
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&lap_batched_kernel<T, CONTIG>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL((lap_batched_kernel<T, CONTIG>), dim3(sp.nblocks), dim3(kLapBatchThreads), lds, st, args,
+                     sp.blk0, sp.nprob, F, slot);
 }
 
 template <typename T>
-hipError_t lap_batched(const LapArgs<T>* args, const Span& sp, int F, int slot, hipStream_t st) {
+hipError_t lap_batched(const LapArgs<T>* args, const Span& sp, int F, int slot, bool contig, hipStream_t st) {
   if (sp.nprob < 1 || sp.nblocks < 1) return hipErrorInvalidValue;
-  const size_t lds = sizeof(c_t<T>) * LapB::lds_elems();
-  if (lds > 65536)
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&lap_batched_kernel<T>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL((lap_batched_kernel<T>), dim3(sp.nblocks), dim3(LapB::THREADS), lds, st, args, sp.blk0,
-                     sp.nprob, F, slot);
+  if (contig) launch_lb<T, true>(args, sp, F, slot, st);
+  else launch_lb<T, false>(args, sp, F, slot, st);
   return hipGetLastError();
 }
 
@@ -98,7 +117,7 @@ template <int K, int VAR, int... Ns> struct XBatchGeo {
 template <int K, int VAR> using XB = XBatchGeo<K, VAR, 16, 32, 64, 128, 256, 512>;
 
 template <typename T, int F, int VAR>
-__global__ void __launch_bounds__((XB<2 * F + 1, VAR>::THREADS))
+__global__ void __launch_bounds__((XB<2 * F + 1, VAR>::THREADS), (sizeof(T) == 8 ? 2 : 4))
 xpass_batched_kernel(const XpassArgs<T>* __restrict__ args, const int* __restrict__ blk0, int nprob) {
   using T2 = c_t<T>;
   const int gb = sizeof(T) == 4 ? xcd_local_block((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x;
@@ -111,7 +130,7 @@ xpass_batched_kernel(const XpassArgs<T>* __restrict__ args, const int* __restric
     xpass_body<T, NN, F, VAR>(reinterpret_cast<const T2*>(a.X), reinterpret_cast<const T2*>(a.Z),                \
                               reinterpret_cast<const T2*>(a.Y), reinterpret_cast<const T*>(a.V),                  \
                               reinterpret_cast<T2*>(a.W), reinterpret_cast<const T2*>(a.tw), (long)(a.npts / NN), \
-                              a.npts, (T)a.lamc, a.p, a.part, a.stride, blk, a.skip);                             \
+                              a.npts, (T)a.lamc, a.p, a.part, a.stride, blk, a.skip);                           \
     break;
     GPE_BSIZES(GPE_CASE)
 #undef GPE_CASE
@@ -169,8 +188,8 @@ hipError_t xpass_batched(int F, int var, const XpassArgs<T>* args, const Span& s
   }
 }
 
-template hipError_t lap_batched<double>(const LapArgs<double>*, const Span&, int, int, hipStream_t);
-template hipError_t lap_batched<float>(const LapArgs<float>*, const Span&, int, int, hipStream_t);
+template hipError_t lap_batched<double>(const LapArgs<double>*, const Span&, int, int, bool, hipStream_t);
+template hipError_t lap_batched<float>(const LapArgs<float>*, const Span&, int, int, bool, hipStream_t);
 template hipError_t xpass_batched<double>(int, int, const XpassArgs<double>*, const Span&, hipStream_t);
 template hipError_t xpass_batched<float>(int, int, const XpassArgs<float>*, const Span&, hipStream_t);
 

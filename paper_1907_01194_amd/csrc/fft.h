@@ -1,9 +1,21 @@
 // Device building blocks of the spectral Laplacian passes (Sec. 3, eq.
-// discrete:laplace): the mixed radix-8/4/3/2 Stockham line transforms in LDS,
-// one axis pass over a block of lines, and the fused x pass of the
-// Hessian-vector product (pointwise Hessian terms of Sec. 3 plus L_x).  The
-// bodies take their workgroup index explicitly so that one batched launch
-// can run them for many problems (batch_fft.hip) as well as one (lap.hip).
+// discrete:laplace): line transforms with each thread holding a whole
+// butterfly in registers, one axis pass over a tile of lines, and the fused x
+// pass of the Hessian-vector product (pointwise Hessian terms of Sec. 3 plus
+// L_x).  The bodies take their workgroup index explicitly so that one batched
+// launch can run them for many problems (batch_fft.hip) as well as one
+// (lap.hip).
+//
+// L_a of a line is DFT, multiply by lambda^2 / n, inverse DFT.  The forward
+// transform is decimation in frequency in place (natural order in, digit-
+// reversed out), the inverse its mirror image (digit-reversed in, natural
+// out), so no reordering pass exists and:
+//   * a stage reads and writes the same LDS elements from the same thread, so
+//     only the hand-over between two stages needs a barrier;
+//   * the last forward stage, the scaling and the first inverse stage act on
+//     the same elements and stay in registers.
+// A line of n = r0 r1 thus crosses LDS twice (once per direction), where a
+// self-sorting transform of three radix <= 8 stages crosses it five times.
 #pragma once
 
 #include "common.h"
@@ -12,22 +24,35 @@
 
 namespace gpe {
 
+// Stages of a line and the threads that share it.  Two stages where the larger
+// radix fits the registers (<= 16 complex values per thread), else three.  T
+// divides the wavefront for every length except 384 (T = 48), so that the
+// threads of one line sit in one wavefront wherever lines are contiguous.
 struct RadixPlan {
   int S;
-  int r[12];
-  int maxr;
+  int r[3];
+  int T;
 };
 
 constexpr RadixPlan make_plan(int N) {
-  RadixPlan p{0, {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}, 1};
-  int m = N;
-  while (m % 3 == 0) { p.r[p.S++] = 3; m /= 3; }
-  while (m % 8 == 0) { p.r[p.S++] = 8; m /= 8; }
-  if (m % 4 == 0) { p.r[p.S++] = 4; m /= 4; }
-  if (m % 2 == 0) { p.r[p.S++] = 2; m /= 2; }
-  for (int i = 0; i < p.S; ++i)
-    if (p.r[i] > p.maxr) p.maxr = p.r[i];
-  return p;
+  switch (N) {
+    case 4: return {1, {4, 1, 1}, 1};
+    case 6: return {1, {6, 1, 1}, 1};
+    case 8: return {1, {8, 1, 1}, 1};
+    case 12: return {2, {3, 4, 1}, 4};
+    case 16: return {2, {4, 4, 1}, 4};
+    case 24: return {2, {6, 4, 1}, 4};
+    case 32: return {2, {8, 4, 1}, 4};
+    case 48: return {2, {6, 8, 1}, 8};
+    case 64: return {2, {8, 8, 1}, 8};
+    case 96: return {2, {12, 8, 1}, 8};
+    case 128: return {2, {16, 8, 1}, 8};
+    case 192: return {2, {12, 16, 1}, 16};
+    case 256: return {2, {16, 16, 1}, 16};
+    case 384: return {3, {8, 8, 6}, 48};
+    case 512: return {3, {8, 8, 8}, 64};
+    default: return {0, {1, 1, 1}, 1};
+  }
 }
 
 constexpr int plan_prefix(RadixPlan p, int s) {
@@ -36,18 +61,53 @@ constexpr int plan_prefix(RadixPlan p, int s) {
   return v;
 }
 
-template <int N> struct Geo {
+// Stage s of a line: N / R butterflies of R elements at stride M; butterfly j
+// holds the elements base(j) + a M, a = 0..R-1; a thread takes the
+// butterflies tl, tl + T, ... (NB of them).
+template <int N, int s> struct Stage {
   static constexpr RadixPlan P = make_plan(N);
-  static constexpr int TPL = N / P.maxr;                       // threads per line
-  static constexpr int LPB0 = (256 / TPL) > 0 ? 256 / TPL : 1;
-  static constexpr int LPB = LPB0 >= 128 ? 128 : LPB0 >= 64 ? 64 : LPB0 >= 32 ? 32 : LPB0 >= 16 ? 16
-                           : LPB0 >= 8 ? 8 : LPB0 >= 4 ? 4 : LPB0 >= 2 ? 2 : 1;   // power of two
-  static constexpr int THREADS = LPB * TPL;
+  static constexpr int S = P.S, T = P.T;
+  static constexpr int R = P.r[s];
+  static constexpr int M = N / plan_prefix(P, s + 1);
+  static constexpr int NBF = N / R;
+  static constexpr int NB = (NBF + T - 1) / T;
+  static constexpr bool kFull = NBF % T == 0;
+  static __host__ __device__ constexpr int base(int j) { return s == 0 ? j : (j / M) * (M * R) + j % M; }
+  static __host__ __device__ constexpr bool has(int j) { return kFull || j < NBF; }
+  // frequency of output k of butterfly j of the last stage (digits of the location reversed)
+  static __host__ __device__ constexpr int freq(int j, int k) {
+    return S == 1 ? k : S == 2 ? j + P.r[0] * k : j / P.r[1] + P.r[0] * (j % P.r[1]) + P.r[0] * P.r[1] * k;
+  }
 };
 
 // multiply by -i (forward) or +i (inverse)
 template <bool FWD, typename T2> __device__ __forceinline__ T2 mul_mi(T2 a) {
   return FWD ? mk<T2>(a.y, -a.x) : mk<T2>(-a.y, a.x);
+}
+
+// cos(2 pi m / 48); every radix up to 16 divides 48
+__host__ __device__ constexpr double cos48(int m) {
+  constexpr double c[13] = {1.0, 0.9914448613738104, 0.9659258262890683, 0.9238795325112867, 0.8660254037844387,
+                            0.7933533402912352, 0.7071067811865476, 0.6087614290087207, 0.5, 0.38268343236508977,
+                            0.25881904510252074, 0.13052619222005157, 0.0};
+  m = ((m % 48) + 48) % 48;
+  if (m > 24) m = 48 - m;
+  return m <= 12 ? c[m] : -c[24 - m];
+}
+
+// a * exp(-+ 2 pi i M / R) with the factor known at compile time
+template <int R, int M, bool FWD, typename T2> __device__ __forceinline__ T2 mul_w(T2 a) {
+  using T = decltype(T2::x);
+  static_assert(48 % R == 0, "constants are multiples of 2 pi / 48");
+  constexpr int m = M % R;
+  if constexpr (m == 0) return a;
+  else if constexpr (4 * m == R) return mul_mi<FWD>(a);
+  else if constexpr (2 * m == R) return mk<T2>(-a.x, -a.y);
+  else {
+    constexpr T c = (T)cos48(m * (48 / R));
+    constexpr T s = (T)((FWD ? -1.0 : 1.0) * cos48(m * (48 / R) - 12));   // sin t = cos(t - pi/2)
+    return mk<T2>(a.x * c - a.y * s, a.x * s + a.y * c);
+  }
 }
 
 template <int R, bool FWD, typename T2> struct Dft;
@@ -57,6 +117,20 @@ template <bool FWD, typename T2> struct Dft<2, FWD, T2> {
     T2 t = a[0];
     a[0] = cadd(t, a[1]);
     a[1] = csub(t, a[1]);
+  }
+};
+
+template <bool FWD, typename T2> struct Dft<3, FWD, T2> {
+  __device__ static __forceinline__ void run(T2* a) {
+    using T = decltype(T2::x);
+    const T c = (T)0.86602540378443864676;  // sqrt(3)/2
+    T2 s = cadd(a[1], a[2]);
+    T2 d = csub(a[1], a[2]);
+    T2 m = mk<T2>(a[0].x - (T)0.5 * s.x, a[0].y - (T)0.5 * s.y);
+    T2 jd = mul_mi<FWD>(mk<T2>(c * d.x, c * d.y));   // -+ i sqrt(3)/2 d
+    a[0] = cadd(a[0], s);
+    a[1] = cadd(m, jd);
+    a[2] = csub(m, jd);
   }
 };
 
@@ -96,175 +170,213 @@ template <bool FWD, typename T2> struct Dft<8, FWD, T2> {
   }
 };
 
-template <bool FWD, typename T2> struct Dft<3, FWD, T2> {
+// R = P Q: P-point transforms over n1 of element Q n1 + n2, factors W_R^{n2 k1},
+// Q-point transforms over n2; output k1 + P k2
+template <int P, int Q, bool FWD, typename T2> struct DftPQ {
   __device__ static __forceinline__ void run(T2* a) {
-    using T = decltype(T2::x);
-    const T c = (T)0.86602540378443864676;  // sqrt(3)/2
-    T2 s = cadd(a[1], a[2]);
-    T2 d = csub(a[1], a[2]);
-    T2 m = mk<T2>(a[0].x - (T)0.5 * s.x, a[0].y - (T)0.5 * s.y);
-    T2 jd = mul_mi<FWD>(mk<T2>(c * d.x, c * d.y));   // -+ i sqrt(3)/2 d
-    a[0] = cadd(a[0], s);
-    a[1] = cadd(m, jd);
-    a[2] = csub(m, jd);
+    T2 y[Q][P];
+    sfor<0, Q>([&](auto N2) {
+      constexpr int n2 = N2;
+#pragma unroll
+      for (int n1 = 0; n1 < P; ++n1) y[n2][n1] = a[Q * n1 + n2];
+      Dft<P, FWD, T2>::run(y[n2]);
+    });
+    sfor<0, P>([&](auto K1) {
+      constexpr int k1 = K1;
+      T2 u[Q];
+      sfor<0, Q>([&](auto N2) {
+        constexpr int n2 = N2;
+        u[n2] = mul_w<P * Q, n2 * k1, FWD>(y[n2][k1]);
+      });
+      Dft<Q, FWD, T2>::run(u);
+#pragma unroll
+      for (int k2 = 0; k2 < Q; ++k2) a[k1 + P * k2] = u[k2];
+    });
   }
 };
-
-enum { SRC_GLOBAL = 0, SRC_LDS = 1 };
-enum { DST_LDS = 0, DST_GLOBAL = 1 };
-
-struct LineCtx {
-  size_t goff;      // global element offset of this thread's line
-  int gstride;      // element stride along the line in global memory
-  int lbase;        // LDS element offset of this thread's line
-  int lstride;      // element stride along the line in LDS (unpadded layouts)
-  int tl;           // thread index within the line
-  bool valid;       // line exists
-};
+template <bool FWD, typename T2> struct Dft<6, FWD, T2> : DftPQ<2, 3, FWD, T2> {};
+template <bool FWD, typename T2> struct Dft<12, FWD, T2> : DftPQ<4, 3, FWD, T2> {};
+template <bool FWD, typename T2> struct Dft<16, FWD, T2> : DftPQ<4, 4, FWD, T2> {};
 
 // Padded LDS layout of a line held contiguously: element j sits at
 // j + (j >> pad_shift<T>()), one pad per pad_run<T>() elements: 16 for c64
 // lines, 8 for c128 lines (the run with the fewest bank conflicts for each
-// element size).  The Stockham passes access a line at strides R (the first
-// pass's writes: 8 for radix 8) and 2rk (twiddles); the pads spread every such
-// group of lanes over distinct banks.
+// element size).  The stages access a line at strides R and M; the pads spread
+// every such group of lanes over distinct banks.
 template <typename T> __host__ __device__ constexpr int pad_shift() { return sizeof(T) == 4 ? 4 : 3; }
 template <typename T> __host__ __device__ constexpr int pad_run() { return 1 << pad_shift<T>(); }
 template <typename T> __host__ __device__ constexpr int lpad(int j) { return j + (j >> pad_shift<T>()); }
 // LDS elements a padded line (or twiddle table) of length N occupies
 template <typename T> __host__ __device__ constexpr int padded_len(int N) { return N + (N >> pad_shift<T>()) + 1; }
-// Index shortcuts of a padded pass with B = N / R butterflies and stride Ns:
-// reads at b + r B may be taken as lpad(b) + lpad(r B) when B is a multiple of
-// the pad run; writes at base + r Ns (base = (b / Ns) Ns R + b % Ns) as
-// lpad(base) + lpad(r Ns) when Ns is, or as lpad(base) + r when Ns = 1 and R
-// divides the pad run (base + r then never carries into the pad count).
+// Index shortcuts of a padded stage: elements b + r B may be taken as
+// lpad(b) + lpad(r B) when B is a multiple of the pad run; elements
+// base + r Ns (base = (b / Ns) Ns R + b % Ns) as lpad(base) + lpad(r Ns) when
+// Ns is, or as lpad(base) + r when Ns = 1 and R divides the pad run (base + r
+// then never carries into the pad count).
 template <typename T> __host__ __device__ constexpr bool read_split(int B) { return B % pad_run<T>() == 0; }
 template <typename T> __host__ __device__ constexpr bool write_split(int Ns, int R) {
-  return Ns % pad_run<T>() == 0 || (Ns == 1 && pad_run<T>() % R == 0);
+  return read_split<T>(Ns) || (Ns == 1 && pad_run<T>() % R == 0);
+}
+// The same base + r Ns where Ns divides the pad run and Ns R is a multiple of
+// it: b % Ns never carries, so the element is at lpad(base) + lpad(r Ns).
+template <typename T> __host__ __device__ constexpr bool digit_split(int Ns, int R) {
+  return pad_run<T>() % Ns == 0 && (Ns * R) % pad_run<T>() == 0;
 }
 
-// Epilogue of the last inverse pass: out = acc + val - pc * X (pc = 0: no projection).
-template <typename T> struct Epi {
-  const c_t<T>* acc;
-  const c_t<T>* X;
-  T pc;
+// LDS index of element a of a butterfly whose first element is `base`.
+// LS = 0: the line is contiguous from lbase in the padded layout; LS > 0: its
+// elements sit LS apart from lbase (lines side by side).
+template <typename T, int R, int M, int LS> __device__ __forceinline__ int lds_at(int lbase, int base, int a) {
+  if constexpr (LS > 0) return lbase + (base + a * M) * LS;
+  else if constexpr (write_split<T>(M, R)) return lbase + lpad<T>(base) + (M == 1 ? a : lpad<T>(a * M));
+  else if constexpr (digit_split<T>(M, R)) return lbase + lpad<T>(base) + lpad<T>(a * M);
+  else return lbase + lpad<T>(base + a * M);
+}
+
+// Hand-over of LDS data between the threads of a line.  WAVE: they sit in one
+// wavefront, whose LDS instructions execute in order, so only the compiler has
+// to keep the order; otherwise a workgroup barrier.
+template <bool WAVE> __device__ __forceinline__ void line_sync() {
+  if constexpr (WAVE) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  } else {
+    __syncthreads();
+  }
+}
+
+// A thread's place in its line.
+struct LineCtx {
+  int tl;        // thread index within the line
+  int lbase;     // LDS element offset of the line
+  bool valid;    // the line exists
 };
 
-// PAD: the line is contiguous in LDS in the padded layout (lpad), and so is
-// the twiddle table; otherwise element j of the line is at lbase + j lstride
-// and twiddle m at m.  raw (first pass only, may be null): the line as read
-// from global memory is also stored there, in the line's own LDS layout.
-template <typename T, bool PAD> __device__ __forceinline__ int lidx(const LineCtx& lc, int j) {
-  return PAD ? lc.lbase + lpad<T>(j) : lc.lbase + j * lc.lstride;
+// v *= W^{+-}: factors between stages s and s + 1 (W_{M R}^{b k} for element k of butterfly j)
+template <typename T, int N, int s, bool FWD>
+__device__ __forceinline__ void twiddle(c_t<T>* v, int j, const c_t<T>* tw) {
+  using St = Stage<N, s>;
+  const int b = j % St::M;
+#pragma unroll
+  for (int k = 1; k < St::R; ++k) {
+    c_t<T> w = tw[lpad<T>(b * k * (N / (St::M * St::R)))];
+    if (!FWD) w.y = -w.y;
+    v[k] = cmul(v[k], w);
+  }
 }
 
-template <typename T, int N, int s, bool FWD, int SRC, int DST, bool PAD>
-__device__ __forceinline__ void stage(const c_t<T>* __restrict__ gin, c_t<T>* lds,
-                                      const c_t<T>* tw, c_t<T>* __restrict__ gout,
-                                      const Epi<T>& epi, const LineCtx& lc, T lamc, T invn, double& pars,
-                                      c_t<T>* raw = nullptr) {
+// Multiply the last forward stage's outputs by lambda^2 / n and add
+// <Z, L_a Z> = sum lambda^2/n |Z^|^2 (Parseval) to pars.  INV: v is scaled for
+// the inverse transform.
+template <typename T, int N, bool INV>
+__device__ __forceinline__ void scale_freq(c_t<T>* v, int j, T lamc, T invn, double& pars) {
+  using St = Stage<N, make_plan(N).S - 1>;
+#pragma unroll
+  for (int k = 0; k < St::R; ++k) {
+    const int f = St::freq(j, k);
+    const int p = f < N / 2 ? f : f - N;
+    const T lam = lamc * (T)p;
+    const T sc = lam * lam * invn;
+    pars += (double)sc * (double)cabs2(v[k]);
+    if (INV) v[k] = cscale(v[k], sc);
+  }
+}
+
+// Stages s .. S-1 forward, the scaling, and (INV) the same stages inverse, on
+// lines whose stage s input is in LDS (handed over); the result is left there.
+template <typename T, int N, int s, int LS, bool WAVE, bool INV>
+__device__ __forceinline__ void inner_stages(c_t<T>* lds, const c_t<T>* tw, const LineCtx& lc, T lamc, T invn,
+                                             double& pars) {
   using T2 = c_t<T>;
-  constexpr RadixPlan P = Geo<N>::P;
-  constexpr int R = P.r[s];
-  constexpr int Ns = plan_prefix(P, s);
-  constexpr int B = N / R;
-  constexpr int TPL = Geo<N>::TPL;
-  constexpr int NB = (B + TPL - 1) / TPL;
-  constexpr bool LAST_FWD = FWD && (s == P.S - 1);
-  T2 v[NB][R];
-  constexpr bool kReadSplit = PAD && read_split<T>(B);
+  using St = Stage<N, s>;
+  constexpr bool kLast = s == St::S - 1;
 #pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    const int b = lc.tl + i * TPL;
-    if (lc.valid && (B % TPL == 0 || b < B)) {
-      const int pb = lc.lbase + lpad<T>(b);
+  for (int i = 0; i < St::NB; ++i) {
+    const int j = lc.tl + i * St::T;
+    if (lc.valid && St::has(j)) {
+      T2 v[St::R];
+      const int base = St::base(j);
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int j = b + r * B;
-        const int li = kReadSplit ? pb + lpad<T>(r * B) : lidx<T, PAD>(lc, j);
-        v[i][r] = (SRC == SRC_GLOBAL) ? gin[lc.goff + (size_t)j * lc.gstride] : lds[li];
-        if (SRC == SRC_GLOBAL && raw) raw[li] = v[i][r];
+      for (int a = 0; a < St::R; ++a) v[a] = lds[lds_at<T, St::R, St::M, LS>(lc.lbase, base, a)];
+      Dft<St::R, true, T2>::run(v);
+      if constexpr (kLast) {
+        scale_freq<T, N, INV>(v, j, lamc, invn, pars);
+        if constexpr (INV) Dft<St::R, false, T2>::run(v);
+      } else {
+        twiddle<T, N, s, true>(v, j, tw);
+      }
+      if constexpr (!kLast || INV) {
+#pragma unroll
+        for (int a = 0; a < St::R; ++a) lds[lds_at<T, St::R, St::M, LS>(lc.lbase, base, a)] = v[a];
       }
     }
   }
-  if (SRC == SRC_LDS) __syncthreads();
+  if constexpr (!kLast) {
+    line_sync<WAVE>();
+    inner_stages<T, N, s + 1, LS, WAVE, INV>(lds, tw, lc, lamc, invn, pars);
+    if constexpr (INV) {
+      line_sync<WAVE>();
 #pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    const int b = lc.tl + i * TPL;
-    if (lc.valid && (B % TPL == 0 || b < B)) {
-      const int k = b % Ns;
-      if (Ns > 1) {
+      for (int i = 0; i < St::NB; ++i) {
+        const int j = lc.tl + i * St::T;
+        if (lc.valid && St::has(j)) {
+          T2 v[St::R];
+          const int base = St::base(j);
 #pragma unroll
-        for (int r = 1; r < R; ++r) {
-          const int m = (r * k * (N / (Ns * R))) % N;
-          T2 w = tw[PAD ? lpad<T>(m) : m];
-          if (!FWD) w.y = -w.y;
-          v[i][r] = cmul(v[i][r], w);
-        }
-      }
-      Dft<R, FWD, T2>::run(v[i]);
-      const int base = (b / Ns) * Ns * R + k;
-      constexpr bool kWriteSplit = PAD && write_split<T>(Ns, R);
-      const int pbase = lc.lbase + lpad<T>(base);
+          for (int a = 0; a < St::R; ++a) v[a] = lds[lds_at<T, St::R, St::M, LS>(lc.lbase, base, a)];
+          twiddle<T, N, s, false>(v, j, tw);
+          Dft<St::R, false, T2>::run(v);
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int idx = base + r * Ns;
-        const int lw = kWriteSplit ? pbase + (Ns == 1 ? r : lpad<T>(r * Ns)) : lidx<T, PAD>(lc, idx);
-        T2 val = v[i][r];
-        if (LAST_FWD) {
-          const int p = idx < N / 2 ? idx : idx - N;
-          const T lam = lamc * (T)p;
-          const T sc = lam * lam * invn;
-          pars += (double)sc * (double)cabs2(val);   // Parseval: <Z, L_a Z> = sum lambda^2/n |Z^|^2
-          val = cscale(val, sc);
-        }
-        if (DST == DST_LDS) {
-          lds[lw] = val;
-        } else {
-          const size_t g = lc.goff + (size_t)idx * lc.gstride;
-          T2 o = epi.acc ? cadd(epi.acc[g], val) : val;
-          if (epi.X) {
-            const T2 xv = epi.X[g];
-            o.x -= epi.pc * xv.x;
-            o.y -= epi.pc * xv.y;
-          }
-          gout[g] = o;
+          for (int a = 0; a < St::R; ++a) lds[lds_at<T, St::R, St::M, LS>(lc.lbase, base, a)] = v[a];
         }
       }
     }
   }
-  if (DST == DST_LDS) __syncthreads();
 }
 
-template <typename T, int N, int s, bool PAD = false>
-__device__ __forceinline__ void fwd_stages(const c_t<T>* gin, c_t<T>* lds, const c_t<T>* tw,
-                                           const LineCtx& lc, T lamc, T invn, double& pars,
-                                           c_t<T>* raw = nullptr) {
-  constexpr int S = Geo<N>::P.S;
-  const Epi<T> none{nullptr, nullptr, T(0)};
-  if constexpr (s < S) {
-    if constexpr (s == 0)
-      stage<T, N, 0, true, SRC_GLOBAL, DST_LDS, PAD>(gin, lds, tw, nullptr, none, lc, lamc, invn, pars, raw);
-    else
-      stage<T, N, s, true, SRC_LDS, DST_LDS, PAD>(nullptr, lds, tw, nullptr, none, lc, lamc, invn, pars);
-    fwd_stages<T, N, s + 1, PAD>(gin, lds, tw, lc, lamc, invn, pars);
-  }
-}
-
-// LAST_TO_GLOBAL: the last inverse pass writes global memory through the
-// epilogue; otherwise it writes the result back to LDS.
-template <typename T, int N, int s, bool LAST_TO_GLOBAL, bool PAD = false>
-__device__ __forceinline__ void inv_stages(c_t<T>* lds, const c_t<T>* tw, c_t<T>* gout, const Epi<T>& epi,
-                                           const LineCtx& lc) {
-  constexpr int S = Geo<N>::P.S;
-  const Epi<T> none{nullptr, nullptr, T(0)};
-  double dummy = 0.0;
-  if constexpr (s < S) {
-    if constexpr (s == S - 1 && LAST_TO_GLOBAL)
-      stage<T, N, s, false, SRC_LDS, DST_GLOBAL, PAD>(nullptr, lds, tw, gout, epi, lc, T(0), T(0), dummy);
-    else
-      stage<T, N, s, false, SRC_LDS, DST_LDS, PAD>(nullptr, lds, tw, nullptr, none, lc, T(0), T(0), dummy);
-    inv_stages<T, N, s + 1, LAST_TO_GLOBAL, PAD>(lds, tw, gout, epi, lc);
+// L_a of a line whose stage 0 elements the thread holds: v[i][a] is element
+// tl + i T + a M (natural order) on entry and, with INV, the same element of
+// L_a of the line on return; without, only pars is formed.  LDS may be written
+// on entry (the caller has handed over whatever it held).
+template <typename T, int N> using LineRegs = c_t<T>[Stage<N, 0>::NB][Stage<N, 0>::R];
+template <typename T, int N, int LS, bool WAVE, bool INV>
+__device__ __forceinline__ void line_apply(LineRegs<T, N>& v, c_t<T>* lds, const c_t<T>* tw, const LineCtx& lc,
+                                           T lamc, T invn, double& pars) {
+  using T2 = c_t<T>;
+  using St = Stage<N, 0>;
+  if constexpr (St::S == 1) {
+    if (lc.valid && lc.tl == 0) {
+      Dft<St::R, true, T2>::run(v[0]);
+      scale_freq<T, N, INV>(v[0], 0, lamc, invn, pars);
+      if constexpr (INV) Dft<St::R, false, T2>::run(v[0]);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < St::NB; ++i) {
+      const int j = lc.tl + i * St::T;
+      if (lc.valid && St::has(j)) {
+        Dft<St::R, true, T2>::run(v[i]);
+        twiddle<T, N, 0, true>(v[i], j, tw);
+#pragma unroll
+        for (int a = 0; a < St::R; ++a) lds[lds_at<T, St::R, St::M, LS>(lc.lbase, j, a)] = v[i][a];
+      }
+    }
+    line_sync<WAVE>();
+    inner_stages<T, N, 1, LS, WAVE, INV>(lds, tw, lc, lamc, invn, pars);
+    if constexpr (INV) {
+      line_sync<WAVE>();
+#pragma unroll
+      for (int i = 0; i < St::NB; ++i) {
+        const int j = lc.tl + i * St::T;
+        if (lc.valid && St::has(j)) {
+#pragma unroll
+          for (int a = 0; a < St::R; ++a) v[i][a] = lds[lds_at<T, St::R, St::M, LS>(lc.lbase, j, a)];
+          twiddle<T, N, 0, false>(v[i], j, tw);
+          Dft<St::R, false, T2>::run(v[i]);
+        }
+      }
+    }
   }
 }
 
@@ -278,6 +390,7 @@ __device__ inline void ab_coeffs(const AbSrc& ab, int F, bool store, double* c) 
   __shared__ double cf[2];
   const int t = threadIdx.x;
   double s0 = 0.0, s1 = 0.0;
+#pragma unroll 8
   for (int b = t; b < ab.n; b += blockDim.x) {
     s0 += ab.part[b];
     s1 += ab.part[ab.stride + b];
@@ -315,49 +428,94 @@ __device__ inline void ab_coeffs(const AbSrc& ab, int F, bool store, double* c) 
   c[1] = cf[1];
 }
 
-// One axis pass for every line of every component: out = acc + L_a(in)
-// [- (coef[0] + coef[1] l) X], with the Parseval sum <in, L_a in> per workgroup
-// in part[slot * stride + wg] when part != null.
-// Threads at or beyond Geo<N>::THREADS (a batched launch sized for another
-// N) take no line.
-template <typename T, int N>
+// Element at a byte offset from a pointer that is uniform over the wavefront:
+// one 32-bit register per address (a component is at most 512^3 c128 values,
+// 2^31 bytes).
+template <typename T2> __device__ __forceinline__ const T2& at(const T2* base, unsigned off) {
+  return *reinterpret_cast<const T2*>(reinterpret_cast<const char*>(base) + off);
+}
+template <typename T2> __device__ __forceinline__ T2& at(T2* base, unsigned off) {
+  return *reinterpret_cast<T2*>(reinterpret_cast<char*>(base) + off);
+}
+
+// ---------------------------------------------------------------- axis pass
+// An axis pass is bound by HBM (read Z and W, write W; plus X with the
+// projection) once its values are in flight early enough, which the register
+// plan gives: up to 16 loads of a thread are issued before the first is used,
+// and acc and X are read in chunks ahead of the stores (reading acc between the
+// stores, which may alias it, serialises them: 150 us for the first row below).
+// Measured at spin-3 128^3 (a copy kernel reaches 5.7 TB/s on these sizes):
+//   c128 y pass (705 MB) 124 -> 120 us, z pass with projection (940 MB) 171 -> 170;
+//   c64 y pass 65 -> 62 us, z pass 89 -> 80;  2D 256^2 spin-2 c128 y pass 13.3 -> 9.5.
+//
+// Tile: strided lines (y, z) are taken LPB neighbours side by side, so that
+// LPB lanes read one contiguous segment, the threads of a line LPB lanes apart;
+// contiguous lines (x) have their threads side by side.  Segments of 16 values:
+// with 8 c128 values (128 B) the 128^3 passes take 131 and 187 us, as strides
+// that are powers of two then use fewer memory channels at a time; 32 c64
+// values measure as 16.  Lines of two or more wavefronts' worth per 16 (n >= 192,
+// c128) take 8: twice the workgroups on small grids (256^2: 9.5 against 10.6 us).
+template <typename T, int N, bool CONTIG> struct AxGeo {
+  static constexpr int TPL = make_plan(N).T;
+  static constexpr int SEG = sizeof(T) == 8 && TPL > 8 ? 8 : 16;
+  static constexpr int LPB = TPL > 16 ? (CONTIG && TPL == 64 ? 1 : 4)      // 384, 512: at most 256 threads
+                           : CONTIG || SEG * TPL < 64 ? 64 / TPL : SEG;
+  static constexpr int THREADS = ((LPB * TPL + 63) / 64) * 64;
+  static constexpr bool kWave = CONTIG ? 64 % TPL == 0 : LPB * TPL <= 64;
+  static constexpr int LSTR = padded_len<T>(N);
+  static constexpr int TILE = CONTIG ? LPB * LSTR : LPB * N;   // LDS elements of a tile
+};
+
+// One axis pass over tile `tile` (LPB lines of one component): out = acc +
+// L_a(in) [- (coef[0] + coef[1] l) X], with the Parseval sum <in, L_a in> of
+// the workgroup in part[slot * stride + blk] when part != null.  GROUPS tiles
+// share a workgroup (batched launches).
+template <typename T, int N, bool CONTIG, int GROUPS = 1>
 __device__ __forceinline__ void lap_body(const c_t<T>* __restrict__ in, const c_t<T>* acc, c_t<T>* out,
-                                         const c_t<T>* __restrict__ twg, long nlines, int inner, T lamc, int F,
-                                         size_t npts, const c_t<T>* __restrict__ X, const double* __restrict__ coef,
+                                         const c_t<T>* __restrict__ twg, int inner, T lamc, int F, size_t npts,
+                                         const c_t<T>* __restrict__ X, const double* __restrict__ coef,
                                          double* __restrict__ part, size_t stride, int slot, long blk,
                                          const double* skip, const AbSrc& ab) {
   if (skip && *skip != 0.0) return;   // uniform over the workgroup
   using T2 = c_t<T>;
-  constexpr int TPL = Geo<N>::TPL;
-  constexpr int LPB = Geo<N>::LPB;
+  using G = AxGeo<T, N, CONTIG>;
+  using St = Stage<N, 0>;
+  constexpr int TPL = G::TPL, LPB = G::LPB;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T2* tw = reinterpret_cast<T2*>(smem_raw);
-  T2* lds = tw + N;
+  // (a tile's threads are whole wavefronts)
+  const int grp = GROUPS > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / G::THREADS) : 0;
+  const int t = GROUPS > 1 ? (int)threadIdx.x % G::THREADS : (int)threadIdx.x;
+  T2* lds = tw + padded_len<T>(N) + grp * G::TILE;
+  if constexpr (St::S > 1)
+    for (int m = threadIdx.x; m < N; m += blockDim.x) tw[lpad<T>(m)] = twg[m];
 
-  const int t = threadIdx.x;
-  for (int m = t; m < N; m += blockDim.x) tw[m] = twg[m];
-
+  const unsigned lpc = (unsigned)(npts / N);    // lines per component: a tile never straddles two
+  const unsigned tpc = (lpc + LPB - 1) / LPB;
+  const unsigned tile = (unsigned)blk * GROUPS + grp;
+  const int comp = (int)(tile / tpc);
+  const int ln = CONTIG ? t / TPL : t % LPB;
+  const unsigned line = (tile - (unsigned)comp * tpc) * LPB + ln;   // within the component
   LineCtx lc;
-  int ln;
-  if (inner == 1) {
-    lc.tl = t % TPL;
-    ln = t / TPL;
-    lc.lstride = 1;
-    lc.lbase = ln * (N + 1);
-  } else {
-    ln = t % LPB;
-    lc.tl = t / LPB;
-    lc.lstride = LPB;
-    lc.lbase = ln;
-  }
-  const long L = blk * LPB + ln;
-  lc.valid = t < Geo<N>::THREADS && L < nlines;
-  const long o = L / inner;
-  const long i = L % inner;
-  lc.goff = (size_t)o * N * inner + i;
-  lc.gstride = inner;
+  lc.tl = CONTIG ? t % TPL : t / LPB;
+  lc.lbase = CONTIG ? ln * G::LSTR : ln;
+  lc.valid = ln < LPB && lc.tl < TPL && comp < 2 * F + 1 && line < lpc;
+  // byte offsets within the component: of the thread's first element, and along the line
+  const unsigned gs = CONTIG ? 1u : (unsigned)inner;
+  const unsigned goff = (unsigned)sizeof(T2) * ((CONTIG ? line * N : line / gs * (N * gs) + line % gs) + lc.tl * gs);
+  const unsigned gstep = (unsigned)sizeof(T2) * gs;
+  const size_t cbase = (size_t)comp * npts;
   const T invn = T(1) / T(N);
-  Epi<T> epi{acc, nullptr, T(0)};
+
+  LineRegs<T, N> v;
+#pragma unroll
+  for (int i = 0; i < St::NB; ++i) {
+    const int j = lc.tl + i * TPL;
+    if (lc.valid && St::has(j)) {
+#pragma unroll
+      for (int a = 0; a < St::R; ++a) v[i][a] = at(in + cbase, goff + (i * TPL + a * St::M) * gstep);
+    }
+  }
   double c0 = 0.0, c1 = 0.0;
   if (X && ab.part) {   // uniform: the coefficients from the x pass's partials
     double cf[2];
@@ -368,44 +526,74 @@ __device__ __forceinline__ void lap_body(const c_t<T>* __restrict__ in, const c_
     c0 = coef[0];
     c1 = coef[1];
   }
-  if (X && lc.valid) {
-    const int comp = (int)(lc.goff / npts);          // a line never crosses a component
-    epi.X = X;
-    epi.pc = (T)(c0 + c1 * (double)(F - comp));
-  }
+  const T pc = (T)(c0 + c1 * (double)(F - comp));   // (0 without a projection)
   double pars = 0.0;
-  // Stage 0 reads global memory and uses no twiddles; the barrier that ends it
-  // also publishes the twiddle table.
-  fwd_stages<T, N, 0>(in, lds, tw, lc, lamc, invn, pars);
-  inv_stages<T, N, 0, true>(lds, tw, out, epi, lc);
+  if constexpr (St::S > 1) __syncthreads();   // the twiddle table
+  line_apply<T, N, CONTIG ? 0 : LPB, G::kWave, true>(v, lds, tw, lc, lamc, invn, pars);
+  // (acc may be out: its values are read ahead of the stores, a chunk at a time)
+  constexpr int CH = St::R % 8 == 0 ? 8 : St::R % 6 == 0 ? 6 : St::R;
+#pragma unroll
+  for (int i = 0; i < St::NB; ++i) {
+    if (lc.valid && St::has(lc.tl + i * TPL)) {
+#pragma unroll
+      for (int a0 = 0; a0 < St::R; a0 += CH) {
+        T2 w[CH], xv[CH];
+#pragma unroll
+        for (int a = 0; a < CH; ++a) {
+          const unsigned g = goff + (i * TPL + (a0 + a) * St::M) * gstep;
+          w[a] = acc ? at(acc + cbase, g) : mk<T2>(0, 0);
+          xv[a] = X ? at(X + cbase, g) : mk<T2>(0, 0);
+        }
+#pragma unroll
+        for (int a = 0; a < CH; ++a) {
+          const unsigned g = goff + (i * TPL + (a0 + a) * St::M) * gstep;
+          T2 o = cadd(w[a], v[i][a0 + a]);
+          o.x -= pc * xv[a].x;
+          o.y -= pc * xv[a].y;
+          at(out + cbase, g) = o;
+        }
+      }
+    }
+  }
   if (part) {
     double a[1] = {pars};
     block_partials_any<1>(a, part + (size_t)slot * stride, 0, blk);
   }
 }
 
+// Tiles (workgroups) of an axis pass over K components of npts points.
+template <typename T, int N, bool CONTIG> constexpr long ax_tiles(int K, size_t npts) {
+  return (long)K * (((long)(npts / N) + AxGeo<T, N, CONTIG>::LPB - 1) / AxGeo<T, N, CONTIG>::LPB);
+}
+
+// ---------------------------------------------------------------- fused x pass
 // Fused x pass of the Hessian-vector product: RPB x-rows, all K components.
-// Schedule variant VAR: 0 = half the default rows per workgroup, 1 = default
-// (about 256 threads), 2 = twice the default (if it fits 1024 threads).
+// Schedule variant VAR: rows per workgroup for about one wavefront (0), two
+// (1, the default) or four (2).  At n = 128, K = 7 a variant-0 workgroup is one
+// wavefront that owns one row of every component: 56 lanes hold 16 values each
+// for the transform, 64 lanes two points each for the pointwise terms.
+//
+// Bound by its 29 streams of HBM traffic (4 fields and V; 5.0 TB/s of the copy
+// rate's 5.7 for this pattern) in c128 and by those and VALU issue in c64.  The
+// pointwise terms come first, while every operand is read once, and their
+// result q stays in registers; only the row of Z passes through LDS, so no
+// second copy of Z is kept there and twice the rows fit a CU.  The kernel has
+// no row loop: hoisted out of one, the spin constants fill the registers (256,
+// with spills).  At least 2 (c128) and 4 (c64) wavefronts per SIMD: 3 in c128
+// spill 70 registers.  Measured (c128, c64):
+//   spin-3 128^3 247 -> 194 us, 140 -> 102;  spin-1 256 x 256 x 64 212 -> 165, 92 -> 82;
+//   spin-2 96^3 79 -> 60 us, 41 -> 36;  spin-2 256^2 12.6 -> 12.2 us, 10.2 -> 9.8.
 template <int N, int K, int VAR = 1> struct XGeo {
-  static constexpr int TPL = Geo<N>::TPL;
-  static constexpr int R0 = 256 / (K * TPL);
-  static constexpr int RD = R0 >= 16 ? 16 : R0 >= 8 ? 8 : R0 >= 4 ? 4 : R0 >= 2 ? 2 : 1;
-  static constexpr int RPB = VAR == 0 ? (RD > 1 ? RD / 2 : 1)
-                           : VAR == 1 ? RD
-                           : (2 * RD * K * TPL <= 1024 ? 2 * RD : RD);
+  static constexpr int TPL = make_plan(N).T;
+  static constexpr int WANT = VAR == 0 ? 64 : VAR == 1 ? 128 : 256;
+  static constexpr int RPB = WANT / (K * TPL) >= 1 ? WANT / (K * TPL) : 1;
   static constexpr int LINES = RPB * K;
   static constexpr int THREADS = ((LINES * TPL + 63) / 64) * 64;
-  // LDS: the padded twiddle table, then LINES padded lines, then (FP64 only)
-  // LINES more holding the rows of Z as read (the pointwise terms take Z
-  // from there instead of reading global memory a second time)
+  static constexpr int PPT = (RPB * N + THREADS - 1) / THREADS;   // points per thread
+  static constexpr bool kWave = 64 % TPL == 0;
+  // LDS: the padded twiddle table, then LINES padded lines
   template <typename T> static constexpr int lstr() { return padded_len<T>(N); }
-  template <typename T> static constexpr bool stash() {
-    return sizeof(T) == 8 && 2 * sizeof(T) * ((size_t)lstr<T>() + 2 * (size_t)LINES * lstr<T>()) <= 150 * 1024;
-  }
-  template <typename T> static constexpr size_t lds_elems() {
-    return (size_t)lstr<T>() + (size_t)LINES * lstr<T>() * (stash<T>() ? 2 : 1);
-  }
+  template <typename T> static constexpr size_t lds_elems() { return (size_t)lstr<T>() * (1 + LINES); }
 };
 
 template <typename T, int N, int F, int VAR>
@@ -417,106 +605,107 @@ __device__ __forceinline__ void xpass_body(const c_t<T>* __restrict__ X, const c
   if (skip && *skip != 0.0) return;   // uniform over the workgroup
   using T2 = c_t<T>;
   constexpr int K = 2 * F + 1;
-  constexpr int TPL = Geo<N>::TPL;
   using G = XGeo<N, K, VAR>;
-  constexpr int RPB = G::RPB;
-  constexpr int LINES = G::LINES;
+  using St = Stage<N, 0>;
+  constexpr int TPL = G::TPL, RPB = G::RPB, LINES = G::LINES, PPT = G::PPT;
   constexpr int LSTR = G::template lstr<T>();
-  constexpr bool kStash = G::template stash<T>();
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T2* tw = reinterpret_cast<T2*>(smem_raw);
   T2* lds = tw + LSTR;
-  T2* zraw = kStash ? lds + LINES * LSTR : nullptr;
   const int t = threadIdx.x;
-  for (int m = t; m < N; m += blockDim.x) tw[lpad<T>(m)] = twg[m];
-  const long row0 = blk * RPB;
-
-  // ---- prefetch the global pointwise operands of this thread's first point
-  // (X, L X, V, and Z where it is not kept in LDS) so that their latency
-  // hides behind the transforms below.  FP64 keeps the rows of Z in LDS as
-  // the first transform pass reads them (an FP64 row block's traffic evicts Z
-  // from L2 before the pointwise loop would re-read it); they are taken from
-  // there once the transforms are done.
-  int pt = t;
-  bool have = pt < RPB * N && row0 + pt / N < nrows;
-  T2 x[K], z[K], y[K];
-  T vj = T(0);
-  size_t j = have ? (size_t)(row0 + pt / N) * N + pt % N : 0;
-  auto load_global = [&]() {
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      x[i] = X[i * npts + j];
-      if constexpr (!kStash) z[i] = Z[i * npts + j];
-      y[i] = Y[i * npts + j];
-    }
-    vj = V[j];
-  };
-  auto load_stashed = [&]() {
-    if constexpr (kStash) {
-#pragma unroll
-      for (int i = 0; i < K; ++i) z[i] = zraw[(i * RPB + pt / N) * LSTR + lpad<T>(pt % N)];
-    }
-  };
-  if (have) load_global();
-
-  // ---- L_x Z for the RPB rows of every component, left in LDS
-  LineCtx lc;
-  const int ls = t / TPL;                 // line slot = comp * RPB + row
-  lc.tl = t % TPL;
-  const int comp = ls / RPB, r = ls % RPB;
-  lc.valid = ls < LINES && row0 + r < nrows;
-  lc.goff = (size_t)comp * npts + (size_t)(row0 + r) * N;
-  lc.gstride = 1;
-  lc.lbase = ls * LSTR;
-  lc.lstride = 1;
+  if constexpr (St::S > 1)
+    for (int m = t; m < N; m += blockDim.x) tw[lpad<T>(m)] = twg[m];
   const T invn = T(1) / T(N);
-  double pars = 0.0;
-  const Epi<T> none{nullptr, nullptr, T(0)};
-  fwd_stages<T, N, 0, true>(Z, lds, tw, lc, lamc, invn, pars, zraw);
-  inv_stages<T, N, 0, false, true>(lds, tw, nullptr, none, lc);
-
-  // ---- pointwise Hessian terms, W = L_x Z + q
   T zcoef[K];
 #pragma unroll
   for (int i = 0; i < K; ++i) zcoef[i] = (T)p.zc[i];
-  double acc[7] = {0, 0, 0, 0, 0, 0, pars};
-  // Per point the partial sums run over the K components in the work
-  // precision; the sums over points accumulate in FP64.
-  auto point = [&](int rr, int xx) {
-    T s_xw = 0, s_lxw = 0, s_xz = 0, s_lxz = 0, s_zq = 0, s_zz = 0;
+  double acc[7] = {0, 0, 0, 0, 0, 0, 0};
+
+  const long row0 = blk * RPB;
+  // ---- pointwise Hessian terms q of this thread's points; the rows of Z go
+  // to LDS for the transform.  Per point the partial sums run over the K
+  // components in the work precision; the sums over points accumulate in FP64.
+  T2 q[PPT][K];
+  const size_t r0 = (size_t)row0 * N;   // (the points of the row block are contiguous)
+  const unsigned np = (unsigned)(nrows - row0 < RPB ? nrows - row0 : RPB) * N;
 #pragma unroll
-    for (int i = 0; i < K; ++i) {
-      const T c = cdotr(y[i], z[i]);     // <(LX)_i, Z_i> = <X_i, (LZ)_i>
-      const T xz = cdotr(x[i], z[i]);
-      s_xw += c;
-      s_lxw += T(F - i) * c;
-      s_xz += xz;
-      s_lxz += T(F - i) * xz;
-      s_zz += cabs2(z[i]);
+  for (int pp = 0; pp < PPT; ++pp) {
+    const unsigned pt = t + pp * G::THREADS;
+    if (t < G::THREADS && pt < np) {
+      T2 x[K], z[K], y[K];
+#pragma unroll
+      for (int i = 0; i < K; ++i) {
+        z[i] = at(Z + r0 + i * npts, pt * (unsigned)sizeof(T2));
+        x[i] = at(X + r0 + i * npts, pt * (unsigned)sizeof(T2));
+        y[i] = at(Y + r0 + i * npts, pt * (unsigned)sizeof(T2));
+      }
+      const T vj = at(V + r0, pt * (unsigned)sizeof(T));
+      T s_xw = 0, s_lxw = 0, s_xz = 0, s_lxz = 0, s_zq = 0, s_zz = 0;
+#pragma unroll
+      for (int i = 0; i < K; ++i) {
+        lds[(i * RPB + pt / N) * LSTR + lpad<T>(pt % N)] = z[i];
+        const T c = cdotr(y[i], z[i]);     // <(LX)_i, Z_i> = <X_i, (LZ)_i>
+        const T xz = cdotr(x[i], z[i]);
+        s_xw += c;
+        s_lxw += T(F - i) * c;
+        s_xz += xz;
+        s_lxz += T(F - i) * xz;
+        s_zz += cabs2(z[i]);
+      }
+      hvp_point<T, F>(x, z, vj, p, zcoef, [&](int i, T2 qi) {
+        q[pp][i] = qi;
+        const T xq = cdotr(x[i], qi);
+        s_xw += xq;
+        s_lxw += T(F - i) * xq;
+        s_zq += cdotr(z[i], qi);
+      });
+      acc[0] += (double)s_xw;
+      acc[1] += (double)s_lxw;
+      acc[2] += (double)s_xz;
+      acc[3] += (double)s_lxz;
+      acc[4] += (double)s_zq;
+      acc[5] += (double)s_zz;
     }
-    hvp_point<T, F>(x, z, vj, p, zcoef, [&](int i, T2 qi) {
-      const T2 lz = lds[(i * RPB + rr) * LSTR + lpad<T>(xx)];
-      W[i * npts + j] = cadd(lz, qi);
-      const T xq = cdotr(x[i], qi);
-      s_xw += xq;
-      s_lxw += T(F - i) * xq;
-      s_zq += cdotr(z[i], qi);
-    });
-    acc[0] += (double)s_xw;
-    acc[1] += (double)s_lxw;
-    acc[2] += (double)s_xz;
-    acc[3] += (double)s_lxz;
-    acc[4] += (double)s_zq;
-    acc[5] += (double)s_zz;
-  };
-  while (have) {
-    load_stashed();
-    point(pt / N, pt % N);
-    pt += blockDim.x;
-    have = pt < RPB * N && row0 + pt / N < nrows;
-    if (have) {
-      j = (size_t)(row0 + pt / N) * N + pt % N;
-      load_global();
+    // one point at a time: interleaving several would hold all their operands at once
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  __syncthreads();   // the rows of Z (and the twiddle table)
+
+  // ---- L_x Z for the RPB rows of every component, in place in LDS
+  LineCtx lc;
+  const int ls = t / TPL;                 // line slot = comp * RPB + row
+  lc.tl = t % TPL;
+  lc.valid = ls < LINES && row0 + ls % RPB < nrows;
+  lc.lbase = ls * LSTR;
+  LineRegs<T, N> v;
+#pragma unroll
+  for (int i = 0; i < St::NB; ++i) {
+    const int j = lc.tl + i * TPL;
+    if (lc.valid && St::has(j)) {
+#pragma unroll
+      for (int a = 0; a < St::R; ++a) v[i][a] = lds[lds_at<T, St::R, St::M, 0>(lc.lbase, j, a)];
+    }
+  }
+  line_apply<T, N, 0, G::kWave, true>(v, lds, tw, lc, lamc, invn, acc[6]);
+#pragma unroll
+  for (int i = 0; i < St::NB; ++i) {
+    const int j = lc.tl + i * TPL;
+    if (lc.valid && St::has(j)) {
+#pragma unroll
+      for (int a = 0; a < St::R; ++a) lds[lds_at<T, St::R, St::M, 0>(lc.lbase, j, a)] = v[i][a];
+    }
+  }
+  __syncthreads();
+
+  // ---- W = L_x Z + q
+#pragma unroll
+  for (int pp = 0; pp < PPT; ++pp) {
+    const unsigned pt = t + pp * G::THREADS;
+    if (t < G::THREADS && pt < np) {
+#pragma unroll
+      for (int i = 0; i < K; ++i)
+        at(W + r0 + i * npts, pt * (unsigned)sizeof(T2)) =
+            cadd(lds[(i * RPB + pt / N) * LSTR + lpad<T>(pt % N)], q[pp][i]);
     }
   }
   block_partials_any<7>(acc, part, stride, blk);

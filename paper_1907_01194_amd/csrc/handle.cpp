@@ -54,7 +54,7 @@ gpe_status alloc_field(gpe_handle* h, void** p, size_t bytes) {
 
 template <typename T>
 gpe_status laplacian(gpe_handle* h, const void* in, void* out) {
-  for (int a = 0; a < h->dim; ++a) GPE_KT(h, KK_LAP_X + a, lap_axis<T>(h->ax[a], in, a == 0 ? nullptr : out, out, h->st));
+  for (int a = 0; a < h->dim; ++a) GPE_KT(h, KK_LAP_X + a, lap_axis<T>(h->ax[a], in, a == 0 ? nullptr : out, out, h->F, h->npts, h->st));
   return GPE_OK;
 }
 template gpe_status laplacian<double>(gpe_handle*, const void*, void*);

@@ -20,7 +20,8 @@ struct LapAxis {
 };
 
 template <typename T>
-hipError_t lap_axis(const LapAxis& ax, const void* in, const void* acc, void* out, hipStream_t st);
+hipError_t lap_axis(const LapAxis& ax, const void* in, const void* acc, void* out, int F, size_t npts,
+                    hipStream_t st);
 bool lap_size_supported(int n);
 
 // Partial sums per reduction slot (finalize).
@@ -326,7 +327,6 @@ template <typename T> struct LapArgs {
   const double* coef;
   double* part;         // Parseval partials (null: none)
   double lamc;
-  long nlines;
   size_t npts;
   size_t stride;
   int inner;
@@ -335,8 +335,8 @@ template <typename T> struct LapArgs {
   AbSrc ab;             // projection coefficients formed in the pass (part null: from coef)
 };
 template <typename T>
-hipError_t lap_batched(const LapArgs<T>* args, const Span& sp, int F, int slot, hipStream_t st);
-int lap_batch_blocks(int n, long nlines);
+hipError_t lap_batched(const LapArgs<T>* args, const Span& sp, int F, int slot, bool contig, hipStream_t st);
+int lap_batch_blocks(int n, int inner, size_t npts, int K, bool c64);
 bool batch_size_supported(int n);
 
 // Batched fused x pass (hvp_xpass for every problem with schedule variant var).

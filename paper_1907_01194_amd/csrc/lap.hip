@@ -5,12 +5,13 @@
 // inverse DFT.  Each launch applies one L_alpha to every line of every
 // component and writes out = acc + L_alpha(in) (acc may be null or alias out).
 //
-// A workgroup owns LPB whole lines.  The forward and inverse transforms are
-// self-sorting (Stockham) mixed radix-8/4/3/2 passes on the lines held in LDS:
-// the first forward pass reads global memory directly, the last inverse pass
-// writes global memory directly, the lambda^2 scaling is folded into the last
-// forward pass.  Lines along x are contiguous; lines along y and z are taken
-// LPB at a time at consecutive x so that every global access is coalesced.
+// A workgroup owns a tile of whole lines (AxGeo): the first stage reads global
+// memory into registers, the last writes it from there, and LDS only hands
+// data from one stage to the next (fft.h).  Lines along x are contiguous;
+// lines along y and z are taken several at a time at consecutive x so that
+// every global access is coalesced.
+#include <algorithm>
+
 #include "fft.h"
 
 namespace gpe {
@@ -18,10 +19,10 @@ namespace gpe {
 // fin.part non-null: the launch has one more workgroup, dispatched first,
 // that forms the HVP's projection coefficients from the x pass's partials
 // into fin.res[32..33] for a later pass (instead of a finalize launch).
-template <typename T, int N>
-__global__ void __launch_bounds__(Geo<N>::THREADS)
+template <typename T, int N, bool CONTIG>
+__global__ void __launch_bounds__((AxGeo<T, N, CONTIG>::THREADS))
 lap_axis_kernel(const c_t<T>* __restrict__ in, const c_t<T>* acc, c_t<T>* out,
-                const c_t<T>* __restrict__ twg, long nlines, int inner, T lamc, int F, size_t npts,
+                const c_t<T>* __restrict__ twg, int inner, T lamc, int F, size_t npts,
                 const c_t<T>* __restrict__ X, const double* __restrict__ coef, double* __restrict__ part,
                 size_t stride, int slot, const double* skip, int rev, AbSrc ab, AbSrc fin) {
   // c64 lines: consecutive workgroups on one XCD (measured faster for c64
@@ -39,11 +40,11 @@ lap_axis_kernel(const c_t<T>* __restrict__ in, const c_t<T>* acc, c_t<T>* out,
     --nb;
   }
   const long blk = rev ? nb - 1 - b : b;
-  lap_body<T, N>(in, acc, out, twg, nlines, inner, lamc, F, npts, X, coef, part, stride, slot, blk, skip, ab);
+  lap_body<T, N, CONTIG>(in, acc, out, twg, inner, lamc, F, npts, X, coef, part, stride, slot, blk, skip, ab);
 }
 
 template <typename T, int N, int F, int VAR>
-__global__ void __launch_bounds__((XGeo<N, 2 * F + 1, VAR>::THREADS))
+__global__ void __launch_bounds__((XGeo<N, 2 * F + 1, VAR>::THREADS), (sizeof(T) == 8 ? 2 : 4))
 hvp_xpass_kernel(const c_t<T>* __restrict__ X, const c_t<T>* __restrict__ Z, const c_t<T>* __restrict__ Y,
                  const T* __restrict__ V, c_t<T>* __restrict__ W, const c_t<T>* __restrict__ twg, long nrows,
                  size_t npts, T lamc, PwParams p, double* __restrict__ part, size_t stride, const double* skip) {
@@ -51,19 +52,18 @@ hvp_xpass_kernel(const c_t<T>* __restrict__ X, const c_t<T>* __restrict__ Z, con
   xpass_body<T, N, F, VAR>(X, Z, Y, V, W, twg, nrows, npts, lamc, p, part, stride, blk, skip);
 }
 
-template <typename T, int N>
+template <typename T, int N, bool CONTIG>
 static void launch_lap(const LapAxis& ax, const void* in, const void* acc, void* out, int F, size_t npts,
                        const void* X, const double* coef, double* part, size_t stride, int slot, int* nb,
                        const double* skip, int rev, const AbSrc* ab, const AbSrc* fin, hipStream_t st) {
   using T2 = c_t<T>;
-  constexpr int LPB = Geo<N>::LPB;
-  const long nlines = ax.nlines;
-  const int grid = (int)((nlines + LPB - 1) / LPB);
-  const size_t lds = sizeof(T2) * (size_t)(N + LPB * (N + 1));
+  using G = AxGeo<T, N, CONTIG>;
+  const int grid = (int)ax_tiles<T, N, CONTIG>(2 * F + 1, npts);
+  const size_t lds = sizeof(T2) * (size_t)(padded_len<T>(N) + G::TILE);
   const T2* tw = reinterpret_cast<const T2*>(sizeof(T) == 8 ? ax.tw64 : ax.tw32);
-  hipLaunchKernelGGL((lap_axis_kernel<T, N>), dim3(grid + (fin ? 1 : 0)), dim3(Geo<N>::THREADS), lds, st,
+  hipLaunchKernelGGL((lap_axis_kernel<T, N, CONTIG>), dim3(grid + (fin ? 1 : 0)), dim3(G::THREADS), lds, st,
                      reinterpret_cast<const T2*>(in), reinterpret_cast<const T2*>(acc),
-                     reinterpret_cast<T2*>(out), tw, nlines, ax.inner, (T)ax.lamc, F, npts,
+                     reinterpret_cast<T2*>(out), tw, ax.inner, (T)ax.lamc, F, npts,
                      reinterpret_cast<const T2*>(X), coef, part, stride, slot, skip, rev, ab ? *ab : AbSrc{},
                      fin ? *fin : AbSrc{});
   if (nb) *nb = grid;   // partials of the pass itself (the extra workgroup writes none)
@@ -72,12 +72,16 @@ static void launch_lap(const LapAxis& ax, const void* in, const void* acc, void*
 #define GPE_SIZES(M) M(4) M(6) M(8) M(12) M(16) M(24) M(32) M(48) M(64) M(96) M(128) M(192) M(256) M(384) M(512)
 
 template <typename T>
-hipError_t lap_axis(const LapAxis& ax, const void* in, const void* acc, void* out, hipStream_t st) {
+hipError_t lap_axis_ex(const LapAxis& ax, const void* in, const void* acc, void* out, int F, size_t npts,
+                       const void* X, const double* coef, double* part, size_t stride, int slot, int* nb,
+                       const double* skip, int rev, const AbSrc* ab, const AbSrc* fin, hipStream_t st) {
   switch (ax.n) {
-#define GPE_CASE(NN) \
-  case NN:                                                                                                       \
-    launch_lap<T, NN>(ax, in, acc, out, 0, 1, nullptr, nullptr, nullptr, 0, 0, nullptr, nullptr, 0, nullptr,     \
-                      nullptr, st);                                                                               \
+#define GPE_CASE(NN)                                                                                              \
+  case NN:                                                                                                        \
+    if (ax.inner == 1)                                                                                            \
+      launch_lap<T, NN, true>(ax, in, acc, out, F, npts, X, coef, part, stride, slot, nb, skip, rev, ab, fin, st); \
+    else                                                                                                          \
+      launch_lap<T, NN, false>(ax, in, acc, out, F, npts, X, coef, part, stride, slot, nb, skip, rev, ab, fin, st); \
     break;
     GPE_SIZES(GPE_CASE)
 #undef GPE_CASE
@@ -87,18 +91,10 @@ hipError_t lap_axis(const LapAxis& ax, const void* in, const void* acc, void* ou
 }
 
 template <typename T>
-hipError_t lap_axis_ex(const LapAxis& ax, const void* in, const void* acc, void* out, int F, size_t npts,
-                       const void* X, const double* coef, double* part, size_t stride, int slot, int* nb,
-                       const double* skip, int rev, const AbSrc* ab, const AbSrc* fin, hipStream_t st) {
-  switch (ax.n) {
-#define GPE_CASE(NN)                                                                                          \
-  case NN: launch_lap<T, NN>(ax, in, acc, out, F, npts, X, coef, part, stride, slot, nb, skip, rev, ab, fin, st); \
-    break;
-    GPE_SIZES(GPE_CASE)
-#undef GPE_CASE
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+hipError_t lap_axis(const LapAxis& ax, const void* in, const void* acc, void* out, int F, size_t npts,
+                    hipStream_t st) {
+  return lap_axis_ex<T>(ax, in, acc, out, F, npts, nullptr, nullptr, nullptr, 0, 0, nullptr, nullptr, 0, nullptr,
+                        nullptr, st);
 }
 
 template <typename T, int N, int F, int VAR>
@@ -158,19 +154,18 @@ hipError_t hvp_xpass(int F, const LapAxis& ax, size_t npts, const void* X, const
 }
 
 size_t lap_max_blocks(const LapAxis& ax, int K) {
-  size_t lpb = 1, rpb = 1;
+  const size_t npts = (size_t)ax.nlines / K * ax.n;
+  size_t m = (size_t)ax.nlines / K;   // x pass: at least one row per workgroup
   switch (ax.n) {
-#define GPE_CASE(NN)                                                                       \
-  case NN:                                                                                 \
-    lpb = Geo<NN>::LPB;                                                                    \
-    rpb = 1; /* the smallest rows-per-workgroup of any schedule variant */               \
+#define GPE_CASE(NN)                                                                             \
+  case NN:                                                                                       \
+    m = std::max({m, (size_t)ax_tiles<double, NN, true>(K, npts), (size_t)ax_tiles<float, NN, true>(K, npts),    \
+                  (size_t)ax_tiles<double, NN, false>(K, npts), (size_t)ax_tiles<float, NN, false>(K, npts)});   \
     break;
     GPE_SIZES(GPE_CASE)
 #undef GPE_CASE
   }
-  const size_t a = (ax.nlines + lpb - 1) / lpb;
-  const size_t b = ((size_t)ax.nlines / K + rpb - 1) / rpb;
-  return a > b ? a : b;
+  return m;
 }
 
 bool lap_size_supported(int n) {
@@ -181,8 +176,8 @@ bool lap_size_supported(int n) {
   }
 }
 
-template hipError_t lap_axis<double>(const LapAxis&, const void*, const void*, void*, hipStream_t);
-template hipError_t lap_axis<float>(const LapAxis&, const void*, const void*, void*, hipStream_t);
+template hipError_t lap_axis<double>(const LapAxis&, const void*, const void*, void*, int, size_t, hipStream_t);
+template hipError_t lap_axis<float>(const LapAxis&, const void*, const void*, void*, int, size_t, hipStream_t);
 template hipError_t lap_axis_ex<double>(const LapAxis&, const void*, const void*, void*, int, size_t, const void*,
                                         const double*, double*, size_t, int, int*, const double*, int,
                                         const AbSrc*, const AbSrc*, hipStream_t);

@@ -1,0 +1,41 @@
+"""Line transforms of every supported length, as contiguous (x) and strided (y)
+lines with tiles that are only partly filled: the Hessian-vector product of a
+2D problem against the oracle, FP64 and mixed.  The tolerances are those of the
+other field comparisons (1e-11, 1e-5): an error of a transform is a few ulps
+times log2 n, about 5e-15 and 1e-6 at n = 512."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1907_01194_amd import workloads as W
+from helpers import oracle_problem, small_spec
+
+pytestmark = pytest.mark.gpu
+
+SIZES = (4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256, 384, 512)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("n", SIZES)
+def test_every_line_length(n, precision):
+    import torch
+    from paper_1907_01194_amd.binding import Problem
+    from gpu_util import dev, host, assert_field
+    tol = 1e-11 if precision == "fp64" else 1e-5
+    # 6 and 12 lines per component: no tile of 8, 16 or 64 lines is full; 48: some are
+    for F, grid in ((1, (n, 6)), (2, (12, n)), (1, (48, n))):
+        print("line length", n, "grid", grid, precision, flush=True)
+        spec = small_spec(F, grid)
+        prob = oracle_problem(spec)
+        u = oracle.retraction.psi(prob, W.noisy_envelope_state(spec, n, (0.2, 0.2)), 1)
+        xi = oracle.project(prob, u, W.random_direction(spec, n + 1))
+        gp = Problem(spec, precision)
+        gp.set_point(dev(u))
+        Z = dev(xi, gp.work_dtype)
+        assert_field(host(gp.hvp(Z, riemannian=False)), oracle.hvp(prob, u, xi), tol, "hvp")
+        HR, kappa = gp.hvp_dot(Z, 0.2)
+        ref = oracle.rhess(prob, u, xi, sigma=0.2)
+        assert_field(host(HR), ref, tol, "rhess")
+        k_or = oracle.inner(xi, ref)
+        assert abs(kappa - k_or) <= tol * abs(k_or)
+        gp.close()
