@@ -156,7 +156,6 @@ gpe_status ex_eval(gpe_batch* b, std::vector<Item>& g) {
     t[i] = g[i].c->h->T64;
   }
   GPE_TRY(lap_all<double>(b, g, in, t));
-  const bool grad = g[0].r->c != nullptr;
   std::vector<int> nb(g.size());
   for (size_t i = 0; i < g.size(); ++i) nb[i] = g[i].c->h->nblk;
   auto pw = [&](auto tag) -> gpe_status {
@@ -169,18 +168,15 @@ gpe_status ex_eval(gpe_batch* b, std::vector<Item>& g) {
     return ops(b, recs, nb);
   };
   gpe_status s = GPE_EINVAL;
-  switch (b->F * 2 + (grad ? 1 : 0)) {
-    case 2: s = pw(PwGradArgs<double, 1, false>{}); break;
-    case 3: s = pw(PwGradArgs<double, 1, true>{}); break;
-    case 4: s = pw(PwGradArgs<double, 2, false>{}); break;
-    case 5: s = pw(PwGradArgs<double, 2, true>{}); break;
-    case 6: s = pw(PwGradArgs<double, 3, false>{}); break;
-    case 7: s = pw(PwGradArgs<double, 3, true>{}); break;
+  switch (b->F) {
+    case 1: s = pw(PwGradArgs<double, 1>{}); break;
+    case 2: s = pw(PwGradArgs<double, 2>{}); break;
+    case 3: s = pw(PwGradArgs<double, 3>{}); break;
   }
   GPE_TRY(s);
   std::vector<double*> gram(g.size());
-  for (size_t i = 0; i < g.size(); ++i) gram[i] = grad ? g[i].r->gram : nullptr;
-  return fin_nblk(b, g, 1 + 2 * (2 * b->F + 1), grad ? POST_GRAD : POST_NONE, gram);
+  for (size_t i = 0; i < g.size(); ++i) gram[i] = g[i].r->gram;
+  return fin_nblk(b, g, 1 + 2 * (2 * b->F + 1), POST_GRAD, gram);
 }
 
 gpe_status ex_pgrad(gpe_batch* b, std::vector<Item>& g) {
@@ -604,6 +600,7 @@ gpe_status Lockstep::round(std::vector<Ctx*>& cs, bool sync) {
   // Run the queues head by head, each step taking the operation that heads
   // the most queues: a problem's own order is kept and launches are shared.
   std::vector<size_t> head(cs.size(), 0);
+  bool cg = false;   // some operation left its results in res alone
   for (;;) {
     unsigned best = 0;
     int best_n = 0;
@@ -622,6 +619,7 @@ gpe_status Lockstep::round(std::vector<Ctx*>& cs, bool sync) {
     std::vector<Item> g;
     for (size_t i = 0; i < cs.size(); ++i)
       if (head[i] < cs[i]->q.size() && key_of(cs[i]->q[head[i]]) == best) g.push_back({cs[i], &cs[i]->q[head[i]++]});
+    cg = cg || g[0].r->cg;
     const gpe_status s = execute(b_, g[0].r->kind, g);
     if (s != GPE_OK) {
       if (b_) b_->err = g[0].c->h->err;
@@ -634,7 +632,7 @@ gpe_status Lockstep::round(std::vector<Ctx*>& cs, bool sync) {
   if (b_) {
     GPE_HIP(h0, hipMemcpyAsync(b_->hres, b_->res, sizeof(double) * kResDoubles * b_->hs.size(),
                                hipMemcpyDeviceToHost, b_->st));
-  } else {
+  } else if (cg) {   // (a lone handle's other reductions arrive in hres by themselves)
     for (Ctx* c : cs)
       GPE_HIP(c->h, hipMemcpyAsync(c->h->hres, c->h->res, sizeof(double) * kResDoubles, hipMemcpyDeviceToHost,
                                    c->h->st));

@@ -22,17 +22,111 @@ constexpr int kFinThreads = 1024;   // up to 16k partials per slot: 16 loads per
 constexpr int kFinWaves = kFinThreads / kWave;
 constexpr int kFinOneBlockMax = 1024;   // partials per slot up to which one workgroup does all
 
-__device__ void finalize_body(const double* __restrict__ part, size_t stride, const SlotCounts& nb, int nq,
-                              double* __restrict__ res, int post, int F, double* gram, unsigned int* ticket,
-                              const double* skip) {
+// Apply a post-operation.  sum: the nq sums; st: the caller's copy of res[0..64),
+// which put() keeps current beside res itself (thread 0 only; every value it
+// needs was fetched in parallel before).
+__device__ void finalize_post(const double* sum, int nq, double* st, double* res, int post, int F, double* gram,
+                              const double* gin) {
+  const int K = 2 * F + 1;
+  auto put = [&](int k, double v) {
+    st[k] = v;
+    res[k] = v;
+  };
+  if (post == POST_GRAD) {
+    // Gram system of Lemma 4.1 (proof) with the measured u^T u, u^T G u, u^T G^2 u
+    double a11 = 0, a12 = 0, a22 = 0, r1 = 0, r2 = 0, e = sum[0];
+    for (int i = 0; i < K; ++i) {
+      double xg = sum[1 + i];
+      for (int k = 1 + 2 * K + i; k < nq; k += K) {   // kinetic sums of the axes kept apart
+        xg += sum[k];
+        e += 0.5 * sum[k];
+      }
+      const double l = F - i, nrm = sum[1 + K + i];
+      a11 += nrm;
+      a12 += l * nrm;
+      a22 += l * l * nrm;
+      r1 += xg;
+      r2 += l * xg;
+      put(1 + i, xg);
+      put(1 + K + i, nrm);
+      if (gram) gram[i] = nrm;
+    }
+    const double det = a11 * a22 - a12 * a12;
+    put(0, e);
+    put(1 + 2 * K, (a22 * r1 - a12 * r2) / det);
+    put(2 + 2 * K, (a11 * r2 - a12 * r1) / det);
+  } else if (post == POST_ENERGY) {
+    double e = sum[0];
+    for (int k = 1; k < nq; ++k) e += 0.5 * sum[k];
+    put(0, e);
+  } else if (post == POST_HVP_AB) {
+    double a11 = 0, a12 = 0, a22 = 0;
+    for (int i = 0; i < K; ++i) {
+      const double l = F - i;
+      a11 += gin[i];
+      a12 += l * gin[i];
+      a22 += l * l * gin[i];
+    }
+    const double det = a11 * a22 - a12 * a12;
+    put(32, (a22 * sum[0] - a12 * sum[1]) / det);
+    put(33, (a11 * sum[1] - a12 * sum[0]) / det);
+  } else if (post == POST_HVP_KAPPA || post == POST_HVP_KAPPA_E || post == POST_CG_KAPPA) {
+    double zlz = 0.0;
+    for (int k = 6; k < nq; ++k) zlz += sum[k];
+    const double kappa = post == POST_HVP_KAPPA_E ? sum[4] + zlz : sum[4] + zlz - st[32] * sum[2] - st[33] * sum[3];
+    const double pp = sum[5];
+    put(34, kappa);
+    put(35, pp);
+    if (post == POST_CG_KAPPA) {
+      const int it = (int)st[CG_IT];   // iterations done before this one
+      put(CG_IT, (double)(it + 1));
+      if (!(kappa > st[CG_EPS] * pp)) {   // curvature stop (a NaN stops too)
+        put(CG_KAPPA, kappa);
+        put(CG_PP, pp);
+        put(CG_REASON, CG_STOP_CURVATURE);
+        put(CG_CURV, 1.0);
+        put(CG_DONE, 1.0);
+      } else {
+        put(CG_ALPHA, st[cg_rr_slot(it)] / kappa);
+      }
+    }
+  } else if (post == POST_CG_STEP) {
+    const double rr = sum[0];
+    const int it = (int)st[CG_IT];   // iterations done, this one included
+    if (sqrt(rr) <= st[CG_TOL]) {
+      put(CG_REASON, CG_STOP_RESIDUAL);
+      put(CG_DONE, 1.0);
+    } else {
+      put(CG_BETA, rr / st[cg_rr_slot(it - 1)]);
+      put(cg_rr_slot(it), rr);
+      if (st[CG_IT] >= st[CG_MAXIT]) {
+        put(CG_REASON, CG_STOP_CAP);
+        put(CG_DONE, 1.0);
+      }
+    }
+  }
+}
+
+// raw: where the sums are stored (res itself unless post forms res from them).
+// slot(q): first partial of slot q; count(q): its partials.
+template <typename Slot, typename Count>
+__device__ void finalize_body(Slot&& slot, Count&& count, int nq, double* raw, double* res, int post, int F,
+                              double* gram, unsigned int* ticket, const double* skip, double* mirror) {
   __shared__ double red[kMaxQ > kFinWaves ? kMaxQ : kFinWaves];
+  __shared__ double sum[kMaxQ];
+  __shared__ double st[64];
+  __shared__ double gin[8];
   __shared__ bool last;
   if (skip && *skip != 0.0) return;   // uniform over the launch: no ticket is taken
   const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
+  // state of the post-operation, fetched while the partials are summed (slots
+  // 32 and up: no workgroup of this launch writes them before the post)
+  if (threadIdx.x < 64) st[threadIdx.x] = res[threadIdx.x];
+  if (threadIdx.x < 8) gin[threadIdx.x] = gram ? gram[threadIdx.x] : 0.0;
   if (ticket) {
     const int q = blockIdx.x;
-    const double* pq = part + (size_t)q * stride;
-    const int n = nb.nb[q];
+    const double* pq = slot(q);
+    const int n = count(q);
     double s0 = 0, s1 = 0, s2 = 0, s3 = 0;
     int b = threadIdx.x;
     for (; b + 3 * kFinThreads < n; b += 4 * kFinThreads) {
@@ -48,20 +142,22 @@ __device__ void finalize_body(const double* __restrict__ part, size_t stride, co
     if (threadIdx.x == 0) {
       double t = 0.0;
       for (int u = 0; u < kFinWaves; ++u) t += red[u];
-      res[q] = t;
+      raw[q] = t;
       __threadfence();
       last = atomicAdd(ticket, 1u) == (unsigned)(nq - 1);
+      if (last) __threadfence();
     }
     __syncthreads();
-    if (!last || threadIdx.x != 0) return;
-    *ticket = 0u;   // every workgroup of this launch has taken its ticket
-    __threadfence();
+    if (!last) return;
+    if (threadIdx.x == 0) *ticket = 0u;   // every workgroup of this launch has taken its ticket
+    if ((int)threadIdx.x < nq)            // (written by other workgroups: not from this CU's cache)
+      sum[threadIdx.x] = __hip_atomic_load(&raw[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   } else {
     const int wps = nq < kFinWaves ? kFinWaves / nq : 1;   // waves per slot; nq * wps <= max(nq, kFinWaves)
     for (int q = w / wps; q < nq; q += kFinWaves / wps) {
       const int sub = w % wps;
-      const double* pq = part + (size_t)q * stride;
-      const int n = nb.nb[q];
+      const double* pq = slot(q);
+      const int n = count(q);
       const int step = wps * kWave;
       double s0 = 0, s1 = 0, s2 = 0, s3 = 0;
       int b = sub * kWave + lane;
@@ -76,89 +172,41 @@ __device__ void finalize_body(const double* __restrict__ part, size_t stride, co
       if (lane == 0) red[q * wps + sub] = s;
     }
     __syncthreads();
-    if (threadIdx.x != 0) return;
-    for (int q = 0; q < nq; ++q) {
+    if ((int)threadIdx.x < nq) {
       double t = 0.0;
-      for (int u = 0; u < wps; ++u) t += red[q * wps + u];
-      res[q] = t;
+      for (int u = 0; u < wps; ++u) t += red[threadIdx.x * wps + u];
+      raw[threadIdx.x] = t;
+      sum[threadIdx.x] = t;
     }
   }
-  const volatile double* out = res;   // (slots written by other workgroups in the ticket form)
-  const int K = 2 * F + 1;
-  if (post == POST_GRAD) {
-    // Gram system of Lemma 4.1 (proof) with the measured u^T u, u^T G u, u^T G^2 u
-    double a11 = 0, a12 = 0, a22 = 0, r1 = 0, r2 = 0;
-    for (int i = 0; i < K; ++i) {
-      const double l = F - i, nrm = out[1 + K + i];
-      a11 += nrm;
-      a12 += l * nrm;
-      a22 += l * l * nrm;
-      r1 += out[1 + i];
-      r2 += l * out[1 + i];
-    }
-    const double det = a11 * a22 - a12 * a12;
-    res[nq] = (a22 * r1 - a12 * r2) / det;
-    res[nq + 1] = (a11 * r2 - a12 * r1) / det;
-    if (gram)
-      for (int i = 0; i < K; ++i) gram[i] = out[1 + K + i];
-  } else if (post == POST_HVP_AB) {
-    double a11 = 0, a12 = 0, a22 = 0;
-    for (int i = 0; i < K; ++i) {
-      const double l = F - i;
-      a11 += gram[i];
-      a12 += l * gram[i];
-      a22 += l * l * gram[i];
-    }
-    const double det = a11 * a22 - a12 * a12;
-    res[32] = (a22 * out[0] - a12 * out[1]) / det;
-    res[33] = (a11 * out[1] - a12 * out[0]) / det;
-  } else if (post == POST_HVP_KAPPA || post == POST_HVP_KAPPA_E || post == POST_CG_KAPPA) {
-    double zlz = 0.0;
-    for (int k = 6; k < nq; ++k) zlz += out[k];
-    const double kappa = post == POST_HVP_KAPPA_E ? out[4] + zlz
-                                                  : out[4] + zlz - out[32] * out[2] - out[33] * out[3];
-    const double pp = out[5];
-    res[34] = kappa;
-    res[35] = pp;
-    if (post == POST_CG_KAPPA) {
-      res[CG_IT] = out[CG_IT] + 1.0;
-      if (!(kappa > out[CG_EPS] * pp)) {   // curvature stop (a NaN stops too)
-        res[CG_KAPPA] = kappa;
-        res[CG_PP] = pp;
-        res[CG_REASON] = CG_STOP_CURVATURE;
-        res[CG_CURV] = 1.0;
-        res[CG_DONE] = 1.0;
-      } else {
-        res[CG_ALPHA] = out[cg_rr_slot((int)out[CG_IT] - 1)] / kappa;   // (CG_IT counts this iteration already)
-      }
-    }
-  } else if (post == POST_CG_STEP) {
-    const double rr = out[0];
-    const int it = (int)out[CG_IT];   // iterations done, this one included
-    if (sqrt(rr) <= out[CG_TOL]) {
-      res[CG_REASON] = CG_STOP_RESIDUAL;
-      res[CG_DONE] = 1.0;
-    } else {
-      res[CG_BETA] = rr / out[cg_rr_slot(it - 1)];
-      res[cg_rr_slot(it)] = rr;
-      if (out[CG_IT] >= out[CG_MAXIT]) {
-        res[CG_REASON] = CG_STOP_CAP;
-        res[CG_DONE] = 1.0;
-      }
-    }
-  }
+  __syncthreads();
+  if (raw >= res && raw + nq <= res + 64 && (int)threadIdx.x < nq) st[raw - res + threadIdx.x] = sum[threadIdx.x];
+  __syncthreads();
+  if (threadIdx.x == 0) finalize_post(sum, nq, st, res, post, F, gram, gin);
+  if (!mirror) return;
+  __syncthreads();
+  if (threadIdx.x < 64) mirror[threadIdx.x] = st[threadIdx.x];
 }
 
 __global__ void __launch_bounds__(kFinThreads)
 finalize_kernel(const double* __restrict__ part, size_t stride, SlotCounts nb, int nq, double* __restrict__ res,
-                int post, int F, double* gram, unsigned int* ticket, const double* skip) {
-  finalize_body(part, stride, nb, nq, res, post, F, gram, ticket, skip);
+                int post, int F, double* gram, unsigned int* ticket, const double* skip, double* mirror) {
+  finalize_body([&](int q) { return part + (size_t)q * stride; }, [&](int q) { return nb.nb[q]; }, nq, res, res, post,
+                F, gram, ticket, skip, mirror);
+}
+
+__global__ void __launch_bounds__(kFinThreads)
+finalize_segs_kernel(const double* __restrict__ part, SlotSegs s, double* raw, double* __restrict__ res, int post,
+                     int F, double* gram, unsigned int* ticket, double* mirror) {
+  finalize_body([&](int q) { return part + s.off[q]; }, [&](int q) { return s.nb[q]; }, s.nq, raw, res, post, F, gram,
+                ticket, nullptr, mirror);
 }
 
 __global__ void __launch_bounds__(kFinThreads)
 finalize_batched_kernel(const FinArgs* __restrict__ args, int nq, int post, int F) {
   const FinArgs& a = args[blockIdx.x];
-  finalize_body(a.part, a.stride, a.nb, nq, a.res, post, F, a.gram, nullptr, a.skip);
+  finalize_body([&](int q) { return a.part + (size_t)q * a.stride; }, [&](int q) { return a.nb.nb[q]; }, nq, a.res,
+                a.res, post, F, a.gram, nullptr, a.skip, nullptr);
 }
 
 static bool counts_ok(const SlotCounts& nb, int nq, size_t stride) {
@@ -169,13 +217,27 @@ static bool counts_ok(const SlotCounts& nb, int nq, size_t stride) {
 }
 
 hipError_t finalize(const double* part, size_t stride, const SlotCounts& nb, int nq, double* res, int post, int F,
-                    double* gram, unsigned int* ticket, const double* skip, hipStream_t st) {
+                    double* gram, unsigned int* ticket, const double* skip, double* mirror, hipStream_t st) {
   if (!counts_ok(nb, nq, stride)) return hipErrorInvalidValue;
   int most = 0;
   for (int q = 0; q < nq; ++q) most = nb.nb[q] > most ? nb.nb[q] : most;
   const bool split = ticket && most > kFinOneBlockMax;
   hipLaunchKernelGGL(finalize_kernel, dim3(split ? nq : 1), dim3(kFinThreads), 0, st, part, stride, nb, nq, res, post,
-                     F, gram, split ? ticket : nullptr, skip);
+                     F, gram, split ? ticket : nullptr, skip, mirror);
+  return hipGetLastError();
+}
+
+hipError_t finalize_segs(const double* part, const SlotSegs& s, double* raw, double* res, int post, int F, double* gram,
+                         unsigned int* ticket, double* mirror, hipStream_t st) {
+  if (s.nq < 1 || s.nq > kMaxQ) return hipErrorInvalidValue;
+  int most = 0;
+  for (int q = 0; q < s.nq; ++q) {
+    if (s.nb[q] < 0 || s.off[q] < 0) return hipErrorInvalidValue;
+    most = s.nb[q] > most ? s.nb[q] : most;
+  }
+  const bool split = ticket && most > kFinOneBlockMax;
+  hipLaunchKernelGGL(finalize_segs_kernel, dim3(split ? s.nq : 1), dim3(kFinThreads), 0, st, part, s, raw, res, post, F,
+                     gram, split ? ticket : nullptr, mirror);
   return hipGetLastError();
 }
 

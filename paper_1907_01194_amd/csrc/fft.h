@@ -466,16 +466,22 @@ template <typename T, int N, bool CONTIG> struct AxGeo {
   static constexpr int TILE = CONTIG ? LPB * LSTR : LPB * N;   // LDS elements of a tile
 };
 
+// What an axis pass leaves.  LAP_SUM: the Parseval sum only (no inverse
+// transform, no output); LAP_ACC: out and the sum; LAP_FULL: also ||out||^2 of
+// the workgroup in the slot after the sum's, and out in c64 at out32 instead of
+// at out where out32 is given.
+enum LapMode { LAP_ACC = 0, LAP_SUM = 1, LAP_FULL = 2 };
+
 // One axis pass over tile `tile` (LPB lines of one component): out = acc +
 // L_a(in) [- (coef[0] + coef[1] l) X], with the Parseval sum <in, L_a in> of
 // the workgroup in part[slot * stride + blk] when part != null.  GROUPS tiles
 // share a workgroup (batched launches).
-template <typename T, int N, bool CONTIG, int GROUPS = 1>
+template <typename T, int N, bool CONTIG, int GROUPS = 1, int MODE = LAP_ACC>
 __device__ __forceinline__ void lap_body(const c_t<T>* __restrict__ in, const c_t<T>* acc, c_t<T>* out,
                                          const c_t<T>* __restrict__ twg, int inner, T lamc, int F, size_t npts,
                                          const c_t<T>* __restrict__ X, const double* __restrict__ coef,
                                          double* __restrict__ part, size_t stride, int slot, long blk,
-                                         const double* skip, const AbSrc& ab) {
+                                         const double* skip, const AbSrc& ab, float2* out32 = nullptr) {
   if (skip && *skip != 0.0) return;   // uniform over the workgroup
   using T2 = c_t<T>;
   using G = AxGeo<T, N, CONTIG>;
@@ -529,12 +535,15 @@ __device__ __forceinline__ void lap_body(const c_t<T>* __restrict__ in, const c_
   const T pc = (T)(c0 + c1 * (double)(F - comp));   // (0 without a projection)
   double pars = 0.0;
   if constexpr (St::S > 1) __syncthreads();   // the twiddle table
-  line_apply<T, N, CONTIG ? 0 : LPB, G::kWave, true>(v, lds, tw, lc, lamc, invn, pars);
+  line_apply<T, N, CONTIG ? 0 : LPB, G::kWave, MODE != LAP_SUM>(v, lds, tw, lc, lamc, invn, pars);
+  double sums[MODE == LAP_FULL ? 2 : 1];
+  sums[0] = pars;
+  if constexpr (MODE == LAP_FULL) sums[1] = 0.0;
   // (acc may be out: its values are read ahead of the stores, a chunk at a time)
   constexpr int CH = St::R % 8 == 0 ? 8 : St::R % 6 == 0 ? 6 : St::R;
 #pragma unroll
   for (int i = 0; i < St::NB; ++i) {
-    if (lc.valid && St::has(lc.tl + i * TPL)) {
+    if (MODE != LAP_SUM && lc.valid && St::has(lc.tl + i * TPL)) {
 #pragma unroll
       for (int a0 = 0; a0 < St::R; a0 += CH) {
         T2 w[CH], xv[CH];
@@ -550,16 +559,21 @@ __device__ __forceinline__ void lap_body(const c_t<T>* __restrict__ in, const c_
           T2 o = cadd(w[a], v[i][a0 + a]);
           o.x -= pc * xv[a].x;
           o.y -= pc * xv[a].y;
-          at(out + cbase, g) = o;
+          if constexpr (MODE == LAP_FULL) {
+            sums[1] += (double)cabs2(o);
+            if (out32) at(out32 + cbase, g / (sizeof(T2) / sizeof(float2))) = mk<float2>((float)o.x, (float)o.y);
+            else at(out + cbase, g) = o;
+          } else {
+            at(out + cbase, g) = o;
+          }
         }
       }
     }
   }
-  if (part) {
-    double a[1] = {pars};
-    block_partials_any<1>(a, part + (size_t)slot * stride, 0, blk);
-  }
+  if (part) block_partials_any(sums, part + (size_t)slot * stride, stride, blk);
 }
+
+#define GPE_SIZES(M) M(4) M(6) M(8) M(12) M(16) M(24) M(32) M(48) M(64) M(96) M(128) M(192) M(256) M(384) M(512)
 
 // Tiles (workgroups) of an axis pass over K components of npts points.
 template <typename T, int N, bool CONTIG> constexpr long ax_tiles(int K, size_t npts) {

@@ -1,0 +1,166 @@
+// Fused x pass of the energy and the gradient (Sec. 3), FP64: one read of X and
+// V gives the pointwise energy density and gradient terms and L_x X of the same
+// rows.  Included once per spin F (GPE_GRAD_F) so that the three compile side by
+// side.
+//
+// With LX formed in full first, a gradient reads and writes 11 fields in 3D (x
+// 2, y 3, z 3, pointwise 3) and an energy 10.  Here the x pass writes G = L_x X +
+// q at once and the other axes accumulate into it (8 fields), and every kinetic
+// sum <X_i, L_a X_i> comes from Parseval inside its pass, so an energy needs the
+// forward transforms only and writes nothing (3 fields).  Bound by HBM on large
+// grids (spin-2 96^3: 52 us for 2 fields and V with the gradient's sums, 24 us for
+// the energy's one) and by latency on small ones (256^2: 12 us).  Measured, with
+// the results stored in pinned memory by the finalize instead of a copy:
+//   energy, spin-1 512^2 (4 launches -> 3) 56.5 -> 31.2 us;
+//   Riemannian gradient, spin-2 256^2 (7 launches, 2 synchronisations -> 5, 1) 75.9 -> 48.0 us;
+//   energy, gradient, set point and product, spin-2 96^3 (autograd) 984 -> 636 us.
+#include "fft.h"
+
+namespace gpe {
+
+// GRAD: G = L_x X + q (point: G = L_x X alone), the partial sums
+//   [0] pointwise energy + 1/2 <X, L_x X>, [1 + i] <X_i, q_i + (L_x X)_i>, [1 + K + i] ||X_i||^2,
+// and copies of X to xc (c128) and xc32 (c64) where given.  !GRAD: [0] only.
+template <int N, int F, bool GRAD>
+__global__ void __launch_bounds__((XGeo<N, 2 * F + 1>::THREADS), 2)
+grad_xpass_kernel(const double2* __restrict__ X, const double* __restrict__ V, double2* __restrict__ G,
+                  double2* __restrict__ xc, float2* __restrict__ xc32, const double2* __restrict__ twg, long nrows,
+                  size_t npts, double lamc, PwParams p, bool point, double* __restrict__ part, size_t stride) {
+  using T = double;
+  using T2 = double2;
+  constexpr int K = 2 * F + 1;
+  using GG = XGeo<N, K>;
+  using St = Stage<N, 0>;
+  constexpr int TPL = GG::TPL, RPB = GG::RPB, LINES = GG::LINES, PPT = GG::PPT;
+  constexpr int LSTR = GG::template lstr<T>();
+  constexpr int NQ = GRAD ? 1 + 2 * K : 1;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  T2* tw = reinterpret_cast<T2*>(smem_raw);
+  T2* lds = tw + LSTR;
+  const int t = threadIdx.x;
+  if constexpr (St::S > 1)
+    for (int m = t; m < N; m += blockDim.x) tw[lpad<T>(m)] = twg[m];
+  double acc[NQ];
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) acc[i] = 0.0;
+  const long row0 = (long)blockIdx.x * RPB;
+  const size_t r0 = (size_t)row0 * N;
+  const unsigned np = (unsigned)(nrows - row0 < RPB ? nrows - row0 : RPB) * N;
+
+  // ---- pointwise terms of this thread's points; the rows of X go to LDS
+  T2 q[GRAD ? PPT : 1][K];
+#pragma unroll
+  for (int pp = 0; pp < PPT; ++pp) {
+    const unsigned pt = t + pp * GG::THREADS;
+    if (pt < np) {
+      const unsigned ob = pt * (unsigned)sizeof(T2);
+      T2 x[K];
+#pragma unroll
+      for (int i = 0; i < K; ++i) x[i] = at(X + r0 + i * npts, ob);
+      const T vj = at(V + r0, pt * (unsigned)sizeof(T));
+#pragma unroll
+      for (int i = 0; i < K; ++i) {
+        lds[(i * RPB + pt / N) * LSTR + lpad<T>(pt % N)] = x[i];
+        if constexpr (GRAD) acc[1 + K + i] += cabs2(x[i]);
+      }
+      acc[0] += grad_point<T, F>(x, vj, p, [&](int i, T2 qi) {
+        if constexpr (GRAD) {
+          acc[1 + i] += cdotr(x[i], qi);
+          q[pp][i] = qi;
+        }
+      });
+      if constexpr (GRAD) {
+        if (xc)
+#pragma unroll
+          for (int i = 0; i < K; ++i) at(xc + r0 + i * npts, ob) = x[i];
+        if (xc32)
+#pragma unroll
+          for (int i = 0; i < K; ++i)
+            at(xc32 + r0 + i * npts, pt * (unsigned)sizeof(float2)) = mk<float2>((float)x[i].x, (float)x[i].y);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);   // one point at a time
+  }
+  __syncthreads();
+
+  // ---- L_x X of every component's rows, in place in LDS
+  LineCtx lc;
+  const int ls = t / TPL;
+  lc.tl = t % TPL;
+  lc.valid = ls < LINES && row0 + ls % RPB < nrows;
+  lc.lbase = ls * LSTR;
+  LineRegs<T, N> v;
+#pragma unroll
+  for (int i = 0; i < St::NB; ++i) {
+    const int j = lc.tl + i * TPL;
+    if (lc.valid && St::has(j)) {
+#pragma unroll
+      for (int a = 0; a < St::R; ++a) v[i][a] = lds[lds_at<T, St::R, St::M, 0>(lc.lbase, j, a)];
+    }
+  }
+  double pars = 0.0;
+  line_apply<T, N, 0, GG::kWave, GRAD>(v, lds, tw, lc, lamc, T(1) / T(N), pars);
+  acc[0] += 0.5 * pars;
+  if constexpr (GRAD) {
+#pragma unroll
+    for (int i = 0; i < K; ++i) acc[1 + i] += ls / RPB == i ? pars : 0.0;
+#pragma unroll
+    for (int i = 0; i < St::NB; ++i) {
+      const int j = lc.tl + i * TPL;
+      if (lc.valid && St::has(j)) {
+#pragma unroll
+        for (int a = 0; a < St::R; ++a) lds[lds_at<T, St::R, St::M, 0>(lc.lbase, j, a)] = v[i][a];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int pp = 0; pp < PPT; ++pp) {
+      const unsigned pt = t + pp * GG::THREADS;
+      if (pt < np) {
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+          const T2 l = lds[(i * RPB + pt / N) * LSTR + lpad<T>(pt % N)];
+          at(G + r0 + i * npts, pt * (unsigned)sizeof(T2)) = point ? l : cadd(l, q[pp][i]);
+        }
+      }
+    }
+  }
+  block_partials_any<NQ>(acc, part, stride, blockIdx.x);
+}
+
+template <int N, int F>
+static void launch_gx(const LapAxis& ax, size_t npts, const void* X, const double* V, void* G, void* xc, void* xc32,
+                      const PwParams& p, bool point, double* part, size_t stride, int* nb, hipStream_t st) {
+  using GG = XGeo<N, 2 * F + 1>;
+  const long nrows = (long)(npts / N);
+  const int grid = (int)((nrows + GG::RPB - 1) / GG::RPB);
+  const size_t lds = sizeof(double2) * GG::template lds_elems<double>();
+  auto run = [&](auto* kernel) {
+    if (lds > 65536)
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)lds);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(GG::THREADS), lds, st, reinterpret_cast<const double2*>(X), V,
+                       reinterpret_cast<double2*>(G), reinterpret_cast<double2*>(xc), reinterpret_cast<float2*>(xc32),
+                       reinterpret_cast<const double2*>(ax.tw64), nrows, npts, ax.lamc, p, point, part, stride);
+  };
+  if (G) run(&grad_xpass_kernel<N, F, true>);
+  else run(&grad_xpass_kernel<N, F, false>);
+  *nb = grid;
+}
+
+template <int F>
+hipError_t grad_xpass(const LapAxis& ax, size_t npts, const void* X, const double* V, void* G, void* xc, void* xc32,
+                      const PwParams& p, bool point, double* part, size_t stride, int* nb, hipStream_t st) {
+  switch (ax.n) {
+#define GPE_CASE(NN) \
+  case NN: launch_gx<NN, F>(ax, npts, X, V, G, xc, xc32, p, point, part, stride, nb, st); break;
+    GPE_SIZES(GPE_CASE)
+#undef GPE_CASE
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+template hipError_t grad_xpass<GPE_GRAD_F>(const LapAxis&, size_t, const void*, const double*, void*, void*, void*,
+                                           const PwParams&, bool, double*, size_t, int*, hipStream_t);
+
+}  // namespace gpe

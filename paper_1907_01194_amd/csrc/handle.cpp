@@ -7,6 +7,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <type_traits>
 
 #include "common.h"
 #include "retract_scalar.h"
@@ -63,13 +64,13 @@ template gpe_status laplacian<float>(gpe_handle*, const void*, void*);
 gpe_status finalize_enq(gpe_handle* h, int nq, int post, double* gram) {
   SlotCounts nb;
   for (int q = 0; q < kMaxQ; ++q) nb.nb[q] = h->nblk;
-  GPE_KT(h, KK_FINALIZE, finalize(h->part, h->nblk, nb, nq, h->res, post, h->F, gram, h->ticket, nullptr, h->st));
+  GPE_KT(h, KK_FINALIZE,
+         finalize(h->part, h->nblk, nb, nq, h->res, post, h->F, gram, h->ticket, nullptr, h->hres, h->st));
   return GPE_OK;
 }
 
 gpe_status fetch(gpe_handle* h) {
-  GPE_HIP(h, hipMemcpyAsync(h->hres, h->res, sizeof(double) * kResDoubles, hipMemcpyDeviceToHost, h->st));
-  GPE_HIP(h, hipStreamSynchronize(h->st));
+  GPE_HIP(h, hipStreamSynchronize(h->st));   // (the finalize stored its results in hres)
   return GPE_OK;
 }
 
@@ -79,16 +80,77 @@ static gpe_status finite(gpe_handle* h, const double* v, int n, const char* what
   return GPE_OK;
 }
 
-gpe_status reduce_to_host(gpe_handle* h, int nq, int post, double* gram, int nout) {
-  GPE_TRY(finalize_enq(h, nq, post, gram));
-  GPE_TRY(fetch(h));
-  return finite(h, h->hres, nout, "a reduction");
+// The energy at X and, with G, the gradient (Sec. 3).  GRAD_EUCLID: G and the
+// multipliers of its projection; GRAD_RIEM: G projected (Lemma 4.1), the
+// multipliers staying on the device in between; GRAD_POINT: G = L X, with the
+// gradient's sums all the same, X copied to the set point (and its c64 copy),
+// the last axis storing G in c64 for a mixed handle.  norm: ||G||^2 into
+// res[kResNorm] (always with GRAD_RIEM).
+//
+// The last axis pass of GRAD_RIEM needs every kinetic sum before it starts, its
+// own axis' included: a pass that only reads X and sums comes first (1 field),
+// in place of a projection that reads X and G and writes G after it (3 fields).
+enum GradKind { GRAD_EUCLID = 0, GRAD_RIEM, GRAD_POINT };
+static gpe_status grad_enq(gpe_handle* h, const void* X, void* G, double* gram, GradKind kind, bool norm) {
+  const int K = h->K, last = h->dim - 1;
+  const bool riem = kind == GRAD_RIEM, point = kind == GRAD_POINT;
+  const bool mixed_point = point && h->prec == GPE_MIXED;
+  norm = norm || riem;
+  int nbx = 0, tpc[3] = {0, 0, 0};
+  auto gx = [&](auto f) {
+    return grad_xpass<f()>(h->ax[0], h->npts, X, h->V64, G, point ? h->Xp : nullptr, mixed_point ? h->Xp32 : nullptr,
+                           h->pw, point, h->part, h->pstride, &nbx, h->st);
+  };
+  GPE_KT(h, KK_PW_GRAD,
+         h->F == 1 ? gx(std::integral_constant<int, 1>{}) : h->F == 2 ? gx(std::integral_constant<int, 2>{})
+                                                                      : gx(std::integral_constant<int, 3>{}));
+  const int first = G ? 1 + 2 * K : 1;   // slot of the first kinetic sum kept apart
+  for (int a = 1; a <= last; ++a)
+    GPE_KT(h, KK_LAP_X + a,
+           grad_axis(h->ax[a], !G || (riem && a == last), X, G, G, mixed_point && a == last ? h->LX32 : nullptr, h->F,
+                     h->npts, nullptr, nullptr, h->part, h->pstride, first + a - 1, &tpc[a], h->st));
+  const size_t ps = h->pstride;
+  SlotSegs s;
+  auto add = [&](size_t off, int n) {
+    s.off[s.nq] = (int)off;
+    s.nb[s.nq++] = n;
+  };
+  for (int q = 0; q < first; ++q) add(q * ps, nbx);
+  for (int a = 1; a <= last; ++a) {
+    if (!G) add((first + a - 1) * ps, K * tpc[a]);
+    for (int i = 0; G && i < K; ++i) add((first + a - 1) * ps + (size_t)i * tpc[a], tpc[a]);
+  }
+  GPE_KT(h, KK_FINALIZE,
+         finalize_segs(h->part, s, h->part + (kMaxQ - 1) * ps, h->res, G ? POST_GRAD : POST_ENERGY, h->F,
+                       G ? gram : nullptr, h->ticket, norm ? nullptr : h->hres, h->st));
+  if (!norm) return GPE_OK;
+  const double* coef = h->res + 1 + 2 * K;
+  SlotSegs sn;
+  sn.nq = 1;
+  if (h->dim > 1) {
+    if (riem)
+      GPE_KT(h, KK_LAP_X + last,
+             grad_axis(h->ax[last], false, X, G, G, nullptr, h->F, h->npts, X, coef, h->part, ps, first + last - 1,
+                       &tpc[last], h->st));
+    sn.off[0] = (int)((first + last) * ps);   // the slot after the last axis' sums
+    sn.nb[0] = K * tpc[last];
+  } else {
+    if (riem)
+      GPE_KT(h, KK_PROJECT,
+             launch_single(ProjArgs<double, double, true>{X, G, G, coef, 0.0, 0.0, h->part, h->npts, h->F}, h->nblk,
+                           h->st));
+    else
+      GPE_KT(h, KK_VECTOR, (dot<double, double>(G, G, h->part, h->nblk, h->nel, h->st)));
+    sn.off[0] = 0;
+    sn.nb[0] = h->nblk;
+  }
+  GPE_KT(h, KK_FINALIZE,
+         finalize_segs(h->part, sn, h->res + kResNorm, h->res, POST_NONE, h->F, nullptr, h->ticket, h->hres, h->st));
+  return GPE_OK;
 }
 
 gpe_status eval_enq(gpe_handle* h, const void* X, void* G, double* gram) {
-  GPE_TRY(laplacian<double>(h, X, h->T64));
-  GPE_KT(h, KK_PW_GRAD, pw_grad<double>(h->F, X, h->T64, h->V64, G, h->part, h->nblk, h->npts, h->pw, h->st));
-  return finalize_enq(h, 1 + 2 * h->K, G ? POST_GRAD : POST_NONE, G ? gram : nullptr);
+  return grad_enq(h, X, G, gram, GRAD_EUCLID, false);
 }
 
 gpe_status eval_read(gpe_handle* h, bool grad, double* E, double* ag, double* bg) {
@@ -115,12 +177,6 @@ gpe_status eval_read(gpe_handle* h, bool grad, double* E, double* ag, double* bg
   return GPE_OK;
 }
 
-gpe_status eval_point(gpe_handle* h, const void* X, void* G, double* gram, double* E, double* ag, double* bg) {
-  GPE_TRY(eval_enq(h, X, G, gram));
-  GPE_TRY(fetch(h));
-  return eval_read(h, G != nullptr, E, ag, bg);
-}
-
 gpe_status pgrad_enq(gpe_handle* h, const void* X, const void* G, void* gR, double ag, double bg) {
   GPE_KT(h, KK_PROJECT,
          launch_single(ProjArgs<double, double, true>{X, G, gR, nullptr, ag, bg, h->part, h->npts, h->F}, h->nblk,
@@ -139,18 +195,6 @@ gpe_status project_grad(gpe_handle* h, const void* X, const void* G, void* gR, d
   GPE_TRY(pgrad_enq(h, X, G, gR, ag, bg));
   GPE_TRY(fetch(h));
   return pgrad_read(h, gnorm);
-}
-
-gpe_status adopt_point(gpe_handle* h) {
-  // the HVP needs L X_p for <X_i, (LZ)_i> = <(LX)_i, Z_i>
-  if (work32(h)) {
-    GPE_HIP(h, to_c64(h->Xp, h->Xp32, h->nel, h->st));
-    GPE_TRY(laplacian<float>(h, h->Xp32, h->LX32));
-  } else {
-    GPE_TRY(laplacian<double>(h, h->Xp, h->LX64));
-  }
-  h->has_point = true;
-  return GPE_OK;
 }
 
 // cg: one iteration of the device-resident truncated CG (the launches are
@@ -178,7 +222,8 @@ static gpe_status hvp_t(gpe_handle* h, const void* Z, void* HZ, bool riem, const
   const bool ab_ypass = riem && !ab_local && h->dim == 3;
   if (riem && !ab_local && !ab_ypass)
     GPE_KT(h, KK_FINALIZE,
-           finalize(h->part, h->pstride, nb, 7, h->res, POST_HVP_AB, h->F, h->gram_pt, h->ticket, skip, h->st));
+           finalize(h->part, h->pstride, nb, 7, h->res, POST_HVP_AB, h->F, h->gram_pt, h->ticket, skip, nullptr,
+                    h->st));
   int nq = 7;
   if (h->dim == 1) {
     // (after a CG stop this projection still runs, on an HZ that nothing reads any more)
@@ -200,7 +245,8 @@ static gpe_status hvp_t(gpe_handle* h, const void* Z, void* HZ, bool riem, const
   }
   if (!cg && !kappa) return GPE_OK;
   const int post = cg ? POST_CG_KAPPA : riem ? POST_HVP_KAPPA : POST_HVP_KAPPA_E;
-  GPE_KT(h, KK_FINALIZE, finalize(h->part, h->pstride, nb, nq, h->res, post, h->F, h->gram_pt, h->ticket, skip, h->st));
+  GPE_KT(h, KK_FINALIZE, finalize(h->part, h->pstride, nb, nq, h->res, post, h->F, h->gram_pt, h->ticket, skip,
+                                  cg ? nullptr : h->hres, h->st));
   return GPE_OK;
 }
 
@@ -376,12 +422,6 @@ gpe_status dot_read(gpe_handle* h, double* out) {
   return GPE_OK;
 }
 
-gpe_status dot_host(gpe_handle* h, const void* a, bool a32, const void* b, bool b32, size_t n, double* out) {
-  GPE_TRY(dot_enq(h, a, a32, b, b32, n));
-  GPE_TRY(fetch(h));
-  return dot_read(h, out);
-}
-
 gpe_status cg_init_enq(gpe_handle* h, double tol, double eps, int maxit) {
   GPE_KT(h, KK_VECTOR, launch_single(CgInitArgs{h->res, tol, eps, maxit}, 1, h->st));
   return GPE_OK;
@@ -404,7 +444,7 @@ static gpe_status cg_step_t(gpe_handle* h, const void* p, const void* q, void* z
   SlotCounts nb;
   for (int k = 0; k < kMaxQ; ++k) nb.nb[k] = h->nblk;
   GPE_KT(h, KK_FINALIZE, finalize(h->part, h->nblk, nb, 1, h->res, POST_CG_STEP, h->F, nullptr, h->ticket,
-                                  h->res + CG_DONE, h->st));
+                                  h->res + CG_DONE, nullptr, h->st));
   return GPE_OK;
 }
 
@@ -787,32 +827,35 @@ gpe_status gpe_create(const gpe_problem* pr, const double* V, int precision, voi
 
 gpe_status gpe_energy(gpe_handle* h, const void* X, double* E) {
   if (!h || !X || !E) return fail(h, GPE_EINVAL, "NULL argument");
-  return eval_point(h, X, nullptr, nullptr, E, nullptr, nullptr);
+  GPE_TRY(eval_enq(h, X, nullptr, nullptr));
+  GPE_TRY(fetch(h));
+  return eval_read(h, false, E, nullptr, nullptr);
 }
 
 gpe_status gpe_grad(gpe_handle* h, const void* X, void* G, int riemannian, double* E, double* gnorm) {
   if (!h || !X || !G) return fail(h, GPE_EINVAL, "NULL argument");
   if (X == G) return fail(h, GPE_EINVAL, "X and G must be distinct");
   double e, ag, bg;
-  GPE_TRY(eval_point(h, X, G, h->gram_tmp, &e, &ag, &bg));
+  GPE_TRY(grad_enq(h, X, G, h->gram_tmp, riemannian ? GRAD_RIEM : GRAD_EUCLID, gnorm != nullptr));
+  GPE_TRY(fetch(h));
+  GPE_TRY(eval_read(h, true, &e, &ag, &bg));
   if (E) *E = e;
-  if (riemannian) {
-    double gn;
-    GPE_TRY(project_grad(h, X, G, G, ag, bg, &gn));
-    if (gnorm) *gnorm = gn;
-  } else if (gnorm) {
-    double g2;
-    GPE_TRY(dot_host(h, G, false, G, false, h->nel, &g2));
-    *gnorm = std::sqrt(g2);
+  if (gnorm) {
+    GPE_TRY(finite(h, h->hres + kResNorm, 1, "the gradient norm"));
+    *gnorm = std::sqrt(h->hres[kResNorm]);
   }
   return GPE_OK;
 }
 
 gpe_status gpe_set_point(gpe_handle* h, const void* X) {
   if (!h || !X) return fail(h, GPE_EINVAL, "NULL argument");
-  GPE_HIP(h, hipMemcpyAsync(h->Xp, X, h->nel * 16, hipMemcpyDeviceToDevice, h->st));
-  GPE_TRY(eval_point(h, h->Xp, h->Gp, h->gram_pt, &h->E_pt, &h->alpha_g, &h->beta_g));
-  return adopt_point(h);
+  // the multipliers and L X_p, which the HVP needs for <X_i, (LZ)_i> = <(LX)_i, Z_i>
+  GPE_TRY(grad_enq(h, X, h->prec == GPE_MIXED ? h->T64 : h->LX64, h->gram_pt, GRAD_POINT, false));
+  GPE_TRY(fetch(h));
+  GPE_TRY(eval_read(h, true, &h->E_pt, &h->alpha_g, &h->beta_g));
+  if (h->prec == GPE_MIXED && h->dim == 1) GPE_HIP(h, to_c64(h->T64, h->LX32, h->nel, h->st));
+  h->has_point = true;
+  return GPE_OK;
 }
 
 gpe_status gpe_hvp(gpe_handle* h, const void* Z, void* HZ, int riemannian, double sigma) {
@@ -958,7 +1001,7 @@ gpe_status gpe_retract_noalloc(const gpe_problem* pr, const void* X, const void*
   NA_HIP((comp_norms<double, double>(K, X, Xi, part, nblk, npts, st)));
   SlotCounts nb;
   for (int q = 0; q < kMaxQ; ++q) nb.nb[q] = nblk;
-  NA_HIP(finalize(part, nblk, nb, nq, res, POST_NONE, F, nullptr, ticket, nullptr, st));
+  NA_HIP(finalize(part, nblk, nb, nq, res, POST_NONE, F, nullptr, ticket, nullptr, nullptr, st));
   double r[3 * 7];
   NA_HIP(hipMemcpyAsync(r, res, sizeof(double) * nq, hipMemcpyDeviceToHost, st));
   NA_HIP(hipStreamSynchronize(st));

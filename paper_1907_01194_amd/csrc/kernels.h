@@ -28,6 +28,12 @@ bool lap_size_supported(int n);
 struct SlotCounts {
   int nb[32];   // kMaxQ
 };
+// Reduction slots anywhere in the partials: slot q is part[off[q]] .. + nb[q].
+struct SlotSegs {
+  int nq = 0;
+  int off[32];
+  int nb[32];
+};
 
 // Projection coefficients formed inside an axis pass instead of by a finalize
 // launch: every workgroup sums slots 0 and 1 of the x pass's n partials
@@ -55,12 +61,18 @@ struct PwParams {
   double zc[7];  // HVP only: extra multiple of Z_i added to W_i
 };
 
-// Energy density (+ gradient).  Partials layout (nq = 1 + 2K):
-//   [0] sum of the energy density, [1+i] <X_i, G_i>, [1+K+i] ||X_i||^2.
-// G may be null (energy only; then [1+i] is 0).
-template <typename T>
-hipError_t pw_grad(int F, const void* X, const void* LX, const T* V, void* G, double* part,
-                   int nblk, size_t npts, const PwParams& p, hipStream_t st);
+// Fused x pass of the energy / gradient (FP64, grad_x.h).  G null: the energy
+// only.  Partial sums in slots 0 .. 2K (0 only for the energy), *nb per slot.
+template <int F>
+hipError_t grad_xpass(const LapAxis& ax, size_t npts, const void* X, const double* V, void* G, void* xc, void* xc32,
+                      const PwParams& p, bool point, double* part, size_t stride, int* nb, hipStream_t st);
+// Strided axis pass of the energy / gradient (FP64): sum_only forms the Parseval
+// sums <X_i, L_a X_i> alone (slot), else out = acc + L_a in [- projection] with
+// the sums in slot and ||out||^2 in slot + 1, written as c64 to out32 if given.
+// A component's sums are *tpc consecutive partials of the slot.
+hipError_t grad_axis(const LapAxis& ax, bool sum_only, const void* in, const void* acc, void* out, void* out32, int F,
+                     size_t npts, const void* X, const double* coef, double* part, size_t stride, int slot, int* tpc,
+                     hipStream_t st);
 
 // Fused x-axis pass of the HVP (all components of RPB x-rows per workgroup):
 //   W = L_x Z + (pointwise Hessian terms of Sec. 3) + p.zc[i] Z_i,
@@ -93,7 +105,9 @@ size_t lap_max_blocks(const LapAxis& ax, int K);
 // partial sums into res[0..nq).
 enum PostOp {
   POST_NONE = 0,
-  // res = [e, <X_i,G_i>, ||X_i||^2]: writes alpha_g, beta_g to res[nq], res[nq+1]
+  // sums [e, <X_i,G_i>, ||X_i||^2] and, beyond those, pairs of kinetic sums per
+  // component and axis still to be added (<X_i, L_a X_i> to <X_i,G_i>, half of it to
+  // e): writes the totals to res[0 .. 2K], alpha_g, beta_g to res[2K+1], res[2K+2]
   // and copies ||X_i||^2 into gram[0..K).
   POST_GRAD = 1,
   // res = HVP slots 0..6 (see hvp_xpass), gram = ||X_i||^2 of the point:
@@ -111,7 +125,9 @@ enum PostOp {
   POST_CG_KAPPA = 5,
   // after the CG update (res[0] = ||r||^2): the residual test stops the CG,
   // else beta = ||r||^2 / rr, rr = ||r||^2, and the iteration cap stops it
-  POST_CG_STEP = 6
+  POST_CG_STEP = 6,
+  // res[0] = sum 0 + half of the other sums (the energy's kinetic parts)
+  POST_ENERGY = 7
 };
 
 // Device-resident state of the truncated CG of the Newton model, in a
@@ -140,9 +156,14 @@ enum CgStop { CG_STOP_NONE = 0, CG_STOP_CURVATURE = 1, CG_STOP_RESIDUAL = 2, CG_
 // Sum partials part[q * stride + b], b < nb[q], for q < nq into res[q]
 // (deterministic), then apply `post`.  One workgroup, or with many partials
 // one per slot; ticket (may be null: always one workgroup) is a device counter
-// that is 0 between launches (the launch leaves it at 0).
+// that is 0 between launches (the launch leaves it at 0).  mirror (may be
+// null): res[0..64) as the launch leaves it is also stored there (pinned host
+// memory: the results arrive with the launch, without a copy of their own).
 hipError_t finalize(const double* part, size_t stride, const SlotCounts& nb, int nq, double* res, int post,
-                    int F, double* gram, unsigned int* ticket, const double* skip, hipStream_t st);
+                    int F, double* gram, unsigned int* ticket, const double* skip, double* mirror, hipStream_t st);
+// The same over segments: sums go to raw[0 .. s.nq) and post forms res from them.
+hipError_t finalize_segs(const double* part, const SlotSegs& s, double* raw, double* res, int post, int F, double* gram,
+                         unsigned int* ticket, double* mirror, hipStream_t st);
 
 // out_i = W_i - (coef[0] + coef[1] l_i) X_i (coef on the device).  X is c128
 // or c64 as TX; W/out in T.  If part != null, partial sums of ||out||^2 (nq = 1).
@@ -288,7 +309,9 @@ template <typename T, typename TX, bool NORM> struct ProjArgs {
   size_t npts;
   int F;
 };
-template <typename T, int F, bool GRAD> struct PwGradArgs {   // see pw_grad
+// Energy density and gradient G of a field with its Laplacian LX.  Partials:
+// [0] sum of the energy density, [1+i] <X_i, G_i>, [1+K+i] ||X_i||^2.
+template <typename T, int F> struct PwGradArgs {
   const void* X;
   const void* LX;
   const void* V;

@@ -69,8 +69,6 @@ static void launch_lap(const LapAxis& ax, const void* in, const void* acc, void*
   if (nb) *nb = grid;   // partials of the pass itself (the extra workgroup writes none)
 }
 
-#define GPE_SIZES(M) M(4) M(6) M(8) M(12) M(16) M(24) M(32) M(48) M(64) M(96) M(128) M(192) M(256) M(384) M(512)
-
 template <typename T>
 hipError_t lap_axis_ex(const LapAxis& ax, const void* in, const void* acc, void* out, int F, size_t npts,
                        const void* X, const double* coef, double* part, size_t stride, int slot, int* nb,

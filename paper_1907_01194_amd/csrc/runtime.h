@@ -72,6 +72,7 @@ struct gpe_handle {
 namespace gpe {
 
 constexpr int kResDoubles = 64;   // reduction results per handle (res, hres)
+constexpr int kResNorm = 28;      // slot of ||G||^2 of a gradient call
 
 // Status helpers: record a message on the handle and return the status.
 gpe_status fail(gpe_handle* h, gpe_status s, const std::string& msg);
@@ -129,23 +130,17 @@ gpe_status laplacian(gpe_handle* h, const void* in, void* out);
 // after h->res has reached h->hres (fetch, or a lock-step round of a batch)
 // *_read checks and returns the values.  The plain forms do both.
 gpe_status finalize_enq(gpe_handle* h, int nq, int post, double* gram);
-gpe_status fetch(gpe_handle* h);   // h->res -> h->hres, synchronises
-gpe_status reduce_to_host(gpe_handle* h, int nq, int post, double* gram, int nout);
+gpe_status fetch(gpe_handle* h);   // synchronises: what the last finalize mirrored is in h->hres
 
 // Energy, gradient G (may be null), alpha_g/beta_g of G and ||X_i||^2 into gram.
 gpe_status eval_enq(gpe_handle* h, const void* X, void* G, double* gram);
 gpe_status eval_read(gpe_handle* h, bool grad, double* E, double* ag, double* bg);
-gpe_status eval_point(gpe_handle* h, const void* X, void* G, double* gram, double* E, double* ag,
-                      double* bg);
 
 // gR = P_X G with the multipliers (ag, bg) already known; returns ||gR||.
 gpe_status pgrad_enq(gpe_handle* h, const void* X, const void* G, void* gR, double ag, double bg);
 gpe_status pgrad_read(gpe_handle* h, double* gnorm);
 gpe_status project_grad(gpe_handle* h, const void* X, const void* G, void* gR, double ag, double bg,
                         double* gnorm);
-
-// Make (X, G, E, ag, bg, gram) the set point without recomputing anything.
-gpe_status adopt_point(gpe_handle* h);
 
 // HVP at the set point in the work precision; if kappa != null also
 // returns <Z, HZ> and ||Z||^2 (synchronises).
@@ -177,7 +172,6 @@ gpe_status retraction_sigma(gpe_handle* h, const double* a, int kind, double* si
 // <a, b> with a c128 and b in (b32 ? c64 : c128), or both in the work precision.
 gpe_status dot_enq(gpe_handle* h, const void* a, bool a32, const void* b, bool b32, size_t n);
 gpe_status dot_read(gpe_handle* h, double* out);
-gpe_status dot_host(gpe_handle* h, const void* a, bool a32, const void* b, bool b32, size_t n, double* out);
 
 // Device-resident truncated CG (state in h->res[CG_*], see kernels.h), work
 // precision: cg_init_enq after a reduction of ||r||^2 into res[0]; per

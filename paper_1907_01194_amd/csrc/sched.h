@@ -21,7 +21,7 @@ namespace gpe {
 // Queued device operations.  Operand precisions: a32/b32/c32 select c64
 // (true) or c128 (false); "work" is the handle's work precision.
 enum ReqKind {
-  RQ_EVAL = 0,   // energy and gradient: a = X, c = G (or null), gram; read with eval_read
+  RQ_EVAL = 0,   // energy and gradient: a = X, c = G, gram; read with eval_read
   RQ_PGRAD,      // c = P_a b with multipliers (s0, s1), all c128; read with pgrad_read
   RQ_NORMS,      // retraction norms of a (c128) and b (b32, or null); read with norms_read
   RQ_SCALE,      // c (c128) = sig_i (a_i + s0 b_i), a c128, b in b32 or null

@@ -67,64 +67,6 @@ template <int F> __device__ constexpr double singlet_s(int i) {
   return ((i & 1) ? -1.0 : 1.0) / (F == 2 ? 2.2360679774997896964 : 2.6457513110645905905);
 }
 
-// Spin densities of one point.
-template <typename T, int F> struct Dens {
-  using T2 = c_t<T>;
-  T rho, fz;
-  T2 fp;        // F_+
-  T2 a00;       // singlet pair amplitude
-  T2 a2[5];     // quintet amplitudes (F = 3)
-};
-
-template <typename T, int F>
-__device__ __forceinline__ void densities(const c_t<T> (&x)[2 * F + 1], Dens<T, F>& d) {
-  using T2 = c_t<T>;
-  constexpr int K = 2 * F + 1;
-  d.rho = 0;
-  d.fz = 0;
-#pragma unroll
-  for (int i = 0; i < K; ++i) {
-    const T a = cabs2(x[i]);
-    d.rho += a;
-    d.fz += T(F - i) * a;
-  }
-  d.fp = mk<T2>(0, 0);
-#pragma unroll
-  for (int i = 1; i < K; ++i) {
-    const T c = (T)raise_c<F>(i);
-    d.fp = cadd(d.fp, cscale(cmulc(x[i - 1], x[i]), c));
-  }
-  if constexpr (F >= 2) {
-    d.a00 = mk<T2>(0, 0);
-#pragma unroll
-    for (int i = 0; i < K; ++i) d.a00 = cadd(d.a00, cscale(cmul(x[i], x[K - 1 - i]), (T)singlet_s<F>(i)));
-  }
-  if constexpr (F == 3) {
-#pragma unroll
-    for (int mi = 0; mi < 5; ++mi) {
-      T2 s = mk<T2>(0, 0);
-#pragma unroll
-      for (int i = 0; i < 7; ++i) {
-        const int k = 8 - mi - i;
-        if (k >= 0 && k < 7) s = cadd(s, cscale(cmul(x[i], x[k]), (T)a2coef(mi, i)));
-      }
-      d.a2[mi] = s;
-    }
-  }
-}
-
-// (F.f Y)_i with spin vector given by (fz, fp)
-template <typename T, int F>
-__device__ __forceinline__ c_t<T> ffy(T fz, c_t<T> fp, const c_t<T> (&y)[2 * F + 1], int i) {
-  using T2 = c_t<T>;
-  constexpr int K = 2 * F + 1;
-  T2 r = cscale(y[i], fz * T(F - i));
-  if (i + 1 < K) r = cadd(r, cscale(cmulc(fp, y[i + 1]), (T)(0.5 * raise_c<F>(i + 1))));
-  if (i >= 1) r = cadd(r, cscale(cmul(fp, y[i - 1]), (T)(0.5 * raise_c<F>(i))));
-  return r;
-}
-
-
 // Compile-time loop: fn(std::integral_constant<int, I>) for I = B .. E-1.
 template <int B, int E, typename Fn> __device__ __forceinline__ void sfor(Fn&& fn) {
   if constexpr (B < E) {
@@ -250,6 +192,75 @@ __device__ __forceinline__ void hvp_point(const c_t<T> (&x)[2 * F + 1], const c_
     }
     sink(i, q);   // q_i is consumed at once, never held for all i
   });
+}
+
+// Pointwise part of the energy density and of the gradient at one point (Sec. 3;
+// the kinetic terms are the caller's): returns (V + b_i) |X_i|^2 summed plus the
+// interaction energy density, and hands sink(i, q_i) the gradient terms
+// q_i = 2 (V + b_i) X_i + (2/h)[beta0 ... + beta3 ...].  Same amplitudes, symmetry
+// and order as hvp_point.
+template <typename T, int F, typename Sink>
+__device__ __forceinline__ T grad_point(const c_t<T> (&x)[2 * F + 1], T v, const PwParams& p, Sink&& sink) {
+  using T2 = c_t<T>;
+  constexpr int K = 2 * F + 1;
+  T rho = 0, fz = 0, ev = 0;
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    const T a = cabs2(x[i]);
+    rho += a;
+    fz += T(F - i) * a;
+    ev += (v + (T)p.zee[i]) * a;
+  }
+  T2 fp = mk<T2>(0, 0);
+  sfor<1, K>([&](auto I) {
+    constexpr int i = I;
+    acc_cjmul(fp, x[i - 1], x[i], (T)raise_c<F>(i));
+  });
+  T inter = (T)p.e[0] * rho * rho + (T)p.e[1] * (fz * fz + cabs2(fp));
+  T2 sa = mk<T2>(0, 0);
+  if constexpr (F >= 2) {
+    sfor<0, F>([&](auto I) {
+      constexpr int i = I;
+      acc_mul(sa, x[i], x[K - 1 - i], (T)(2.0 * singlet_s<F>(i)));
+    });
+    acc_mul(sa, x[F], x[F], (T)singlet_s<F>(F));
+    inter += (T)p.e[2] * cabs2(sa);
+    sa = cscale(sa, (T)p.g[2]);
+  }
+  T2 b2[5];
+  if constexpr (F == 3) {
+    sfor<0, 5>([&](auto MI) {
+      constexpr int mi = MI;
+      T2 b = mk<T2>(0, 0);
+      sfor<0, 7>([&](auto I) {
+        constexpr int i = I;
+        constexpr int k = 8 - mi - i;
+        if constexpr (k >= 0 && k < 7 && i <= k && a2coef(mi, i) != 0.0)
+          acc_mul(b, x[i], x[k], (T)((i < k ? 2.0 : 1.0) * a2coef(mi, i)));
+      });
+      inter += (T)p.e[3] * cabs2(b);
+      b2[mi] = cscale(b, (T)p.g[3]);
+    });
+  }
+  const T c0 = (T)p.g[0] * rho, cfz = (T)p.g[1] * fz;
+  const T2 hfp = cscale(fp, T(0.5) * (T)p.g[1]);
+  sfor<0, K>([&](auto I) {
+    constexpr int i = I;
+    const T c = T(2) * (v + (T)p.zee[i]) + c0 + T(F - i) * cfz;
+    T2 q = cscale(x[i], c);
+    if constexpr (i + 1 < K) acc_cjmul(q, hfp, x[i + 1], (T)raise_c<F>(i + 1));
+    if constexpr (i >= 1) acc_mul(q, hfp, x[i - 1], (T)raise_c<F>(i));
+    if constexpr (F >= 2) acc_cjmul(q, x[K - 1 - i], sa, (T)singlet_s<F>(i));
+    if constexpr (F == 3) {
+      sfor<0, 5>([&](auto MI) {
+        constexpr int mi = MI;
+        constexpr int k = 8 - mi - i;
+        if constexpr (k >= 0 && k < 7 && a2coef(mi, i) != 0.0) acc_cjmul(q, x[k], b2[mi], (T)a2coef(mi, i));
+      });
+    }
+    sink(i, q);
+  });
+  return ev + inter;
 }
 
 }  // namespace gpe

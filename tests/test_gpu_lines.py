@@ -39,3 +39,29 @@ def test_every_line_length(n, precision):
         k_or = oracle.inner(xi, ref)
         assert abs(kappa - k_or) <= tol * abs(k_or)
         gp.close()
+
+
+@pytest.mark.parametrize("n", SIZES)
+def test_energy_and_gradients_every_line_length(n):
+    """The energy (forward transforms and Parseval sums only), the Euclidean and
+    the Riemannian gradient with their norms (the latter through the last axis'
+    own sums) against the oracle: 1e-10 relative on E, 1e-11 on fields."""
+    import torch
+    from paper_1907_01194_amd.binding import Problem
+    from gpu_util import dev, host, assert_field
+    for F, grid in ((1, (n,)), (3, (n, 6)), (2, (12, n)), (1, (6, 8, n)), (1, (8, n, 4))):
+        print("energy / gradient, line length", n, "grid", grid, flush=True)
+        spec = small_spec(F, grid, p=0.1, q=0.05)
+        prob = oracle_problem(spec)
+        u = oracle.retraction.psi(prob, W.noisy_envelope_state(spec, n, (0.2,) * len(grid)), 1)
+        E_or, G_or = oracle.energy(prob, u), oracle.grad(prob, u)
+        gR_or = oracle.rgrad(prob, u)[0]
+        gp = Problem(spec, "fp64")
+        X = dev(u)
+        assert abs(gp.energy(X) - E_or) <= 1e-10 * abs(E_or)
+        for riem, ref in ((False, G_or), (True, gR_or)):
+            G, E, gn = gp.grad(X, riemannian=riem)
+            assert abs(E - E_or) <= 1e-10 * abs(E_or)
+            assert_field(host(G), ref, 1e-11, "gradient")
+            assert abs(gn - np.linalg.norm(ref)) <= 1e-11 * gn
+        gp.close()
