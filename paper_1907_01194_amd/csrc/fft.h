@@ -266,28 +266,32 @@ __device__ __forceinline__ void twiddle(c_t<T>* v, int j, const c_t<T>* tw) {
   }
 }
 
-// Multiply the last forward stage's outputs by lambda^2 / n and add
-// <Z, L_a Z> = sum lambda^2/n |Z^|^2 (Parseval) to pars.  INV: v is scaled for
-// the inverse transform.
-template <typename T, int N, bool INV>
-__device__ __forceinline__ void scale_freq(c_t<T>* v, int j, T lamc, T invn, double& pars) {
-  using St = Stage<N, make_plan(N).S - 1>;
+// What happens to the frequencies between the two directions: apply<N, INV>(v, j)
+// gets the outputs v of butterfly j of the last forward stage (frequencies
+// freq(j, k)) and, with INV, leaves there what the inverse transform starts from.
+
+// L_a: times lambda^2 / n; adds <Z, L_a Z> = sum lambda^2/n |Z^|^2 (Parseval) to pars.
+template <typename T> struct LambdaScale {
+  T lamc, invn;
+  double& pars;
+  template <int N, bool INV> __device__ __forceinline__ void apply(c_t<T>* v, int j) const {
+    using St = Stage<N, make_plan(N).S - 1>;
 #pragma unroll
-  for (int k = 0; k < St::R; ++k) {
-    const int f = St::freq(j, k);
-    const int p = f < N / 2 ? f : f - N;
-    const T lam = lamc * (T)p;
-    const T sc = lam * lam * invn;
-    pars += (double)sc * (double)cabs2(v[k]);
-    if (INV) v[k] = cscale(v[k], sc);
+    for (int k = 0; k < St::R; ++k) {
+      const int f = St::freq(j, k);
+      const int p = f < N / 2 ? f : f - N;
+      const T lam = lamc * (T)p;
+      const T sc = lam * lam * invn;
+      pars += (double)sc * (double)cabs2(v[k]);
+      if (INV) v[k] = cscale(v[k], sc);
+    }
   }
-}
+};
 
 // Stages s .. S-1 forward, the scaling, and (INV) the same stages inverse, on
 // lines whose stage s input is in LDS (handed over); the result is left there.
-template <typename T, int N, int s, int LS, bool WAVE, bool INV>
-__device__ __forceinline__ void inner_stages(c_t<T>* lds, const c_t<T>* tw, const LineCtx& lc, T lamc, T invn,
-                                             double& pars) {
+template <typename T, int N, int s, int LS, bool WAVE, bool INV, typename Scale>
+__device__ __forceinline__ void inner_stages(c_t<T>* lds, const c_t<T>* tw, const LineCtx& lc, const Scale& scale) {
   using T2 = c_t<T>;
   using St = Stage<N, s>;
   constexpr bool kLast = s == St::S - 1;
@@ -301,7 +305,7 @@ __device__ __forceinline__ void inner_stages(c_t<T>* lds, const c_t<T>* tw, cons
       for (int a = 0; a < St::R; ++a) v[a] = lds[lds_at<T, St::R, St::M, LS>(lc.lbase, base, a)];
       Dft<St::R, true, T2>::run(v);
       if constexpr (kLast) {
-        scale_freq<T, N, INV>(v, j, lamc, invn, pars);
+        scale.template apply<N, INV>(v, j);
         if constexpr (INV) Dft<St::R, false, T2>::run(v);
       } else {
         twiddle<T, N, s, true>(v, j, tw);
@@ -314,7 +318,7 @@ __device__ __forceinline__ void inner_stages(c_t<T>* lds, const c_t<T>* tw, cons
   }
   if constexpr (!kLast) {
     line_sync<WAVE>();
-    inner_stages<T, N, s + 1, LS, WAVE, INV>(lds, tw, lc, lamc, invn, pars);
+    inner_stages<T, N, s + 1, LS, WAVE, INV>(lds, tw, lc, scale);
     if constexpr (INV) {
       line_sync<WAVE>();
 #pragma unroll
@@ -335,20 +339,21 @@ __device__ __forceinline__ void inner_stages(c_t<T>* lds, const c_t<T>* tw, cons
   }
 }
 
-// L_a of a line whose stage 0 elements the thread holds: v[i][a] is element
-// tl + i T + a M (natural order) on entry and, with INV, the same element of
-// L_a of the line on return; without, only pars is formed.  LDS may be written
+// Forward transform, `scale`, inverse transform of a line whose stage 0 elements
+// the thread holds: v[i][a] is element tl + i T + a M (natural order) on entry
+// and, with INV, the same element of the result on return; without, the line
+// goes no further than scale.  LDS may be written
 // on entry (the caller has handed over whatever it held).
 template <typename T, int N> using LineRegs = c_t<T>[Stage<N, 0>::NB][Stage<N, 0>::R];
-template <typename T, int N, int LS, bool WAVE, bool INV>
+template <typename T, int N, int LS, bool WAVE, bool INV, typename Scale>
 __device__ __forceinline__ void line_apply(LineRegs<T, N>& v, c_t<T>* lds, const c_t<T>* tw, const LineCtx& lc,
-                                           T lamc, T invn, double& pars) {
+                                           const Scale& scale) {
   using T2 = c_t<T>;
   using St = Stage<N, 0>;
   if constexpr (St::S == 1) {
     if (lc.valid && lc.tl == 0) {
       Dft<St::R, true, T2>::run(v[0]);
-      scale_freq<T, N, INV>(v[0], 0, lamc, invn, pars);
+      scale.template apply<N, INV>(v[0], 0);
       if constexpr (INV) Dft<St::R, false, T2>::run(v[0]);
     }
   } else {
@@ -363,7 +368,7 @@ __device__ __forceinline__ void line_apply(LineRegs<T, N>& v, c_t<T>* lds, const
       }
     }
     line_sync<WAVE>();
-    inner_stages<T, N, 1, LS, WAVE, INV>(lds, tw, lc, lamc, invn, pars);
+    inner_stages<T, N, 1, LS, WAVE, INV>(lds, tw, lc, scale);
     if constexpr (INV) {
       line_sync<WAVE>();
 #pragma unroll
@@ -535,7 +540,7 @@ __device__ __forceinline__ void lap_body(const c_t<T>* __restrict__ in, const c_
   const T pc = (T)(c0 + c1 * (double)(F - comp));   // (0 without a projection)
   double pars = 0.0;
   if constexpr (St::S > 1) __syncthreads();   // the twiddle table
-  line_apply<T, N, CONTIG ? 0 : LPB, G::kWave, MODE != LAP_SUM>(v, lds, tw, lc, lamc, invn, pars);
+  line_apply<T, N, CONTIG ? 0 : LPB, G::kWave, MODE != LAP_SUM>(v, lds, tw, lc, LambdaScale<T>{lamc, invn, pars});
   double sums[MODE == LAP_FULL ? 2 : 1];
   sums[0] = pars;
   if constexpr (MODE == LAP_FULL) sums[1] = 0.0;
@@ -700,7 +705,7 @@ __device__ __forceinline__ void xpass_body(const c_t<T>* __restrict__ X, const c
       for (int a = 0; a < St::R; ++a) v[i][a] = lds[lds_at<T, St::R, St::M, 0>(lc.lbase, j, a)];
     }
   }
-  line_apply<T, N, 0, G::kWave, true>(v, lds, tw, lc, lamc, invn, acc[6]);
+  line_apply<T, N, 0, G::kWave, true>(v, lds, tw, lc, LambdaScale<T>{lamc, invn, acc[6]});
 #pragma unroll
   for (int i = 0; i < St::NB; ++i) {
     const int j = lc.tl + i * TPL;

@@ -99,7 +99,7 @@ grad_xpass_kernel(const double2* __restrict__ X, const double* __restrict__ V, d
     }
   }
   double pars = 0.0;
-  line_apply<T, N, 0, GG::kWave, GRAD>(v, lds, tw, lc, lamc, T(1) / T(N), pars);
+  line_apply<T, N, 0, GG::kWave, GRAD>(v, lds, tw, lc, LambdaScale<T>{lamc, T(1) / T(N), pars});
   acc[0] += 0.5 * pars;
   if constexpr (GRAD) {
 #pragma unroll

@@ -481,21 +481,6 @@ gpe_status cg_state_read(gpe_handle* h, CgState* cs) {
   return GPE_OK;
 }
 
-// Interpolation matrix of the Fourier interpolant from n nodes to the 2n nodes
-// of the refined axis: P[j'][k] = (1/n) sum_{p=-n/2}^{n/2} c_p e^{i 2 pi p (j'/(2n) - k/n)},
-// c_{+-n/2} = 1/2 (real: the sum pairs p and -p).
-static std::vector<double> interp_matrix(int n) {
-  std::vector<double> P((size_t)2 * n * n);
-  for (int jp = 0; jp < 2 * n; ++jp)
-    for (int k = 0; k < n; ++k) {
-      const double th = M_PI * (double)(jp - 2 * k) / (double)n;
-      double s = 1.0 + std::cos(0.5 * n * th);
-      for (int p = 1; p < n / 2; ++p) s += 2.0 * std::cos(p * th);
-      P[(size_t)jp * n + k] = s / n;
-    }
-  return P;
-}
-
 gpe_status prolong(const gpe_handle* c, const void* Xc, gpe_handle* f, void* Xf) {
   if (c->F != f->F || c->dim != f->dim) return fail(f, GPE_EINVAL, "prolong: problems differ");
   for (int a = 0; a < c->dim; ++a)
@@ -504,33 +489,18 @@ gpe_status prolong(const gpe_handle* c, const void* Xc, gpe_handle* f, void* Xf)
   f->has_point = false;
   const void* src = Xc;
   size_t sizes[3] = {(size_t)c->n[0], (size_t)c->n[1], (size_t)c->n[2]};
-  std::vector<double*> mats;
-  gpe_status rs = GPE_OK;
-  for (int a = 0; a < c->dim && rs == GPE_OK; ++a) {
-    const int n = c->n[a];
-    std::vector<double> P = interp_matrix(n);
-    double* dP = nullptr;
-    rs = alloc_field(f, (void**)&dP, P.size() * sizeof(double));
-    if (rs != GPE_OK) break;
-    mats.push_back(dP);
-    hipError_t e = hipMemcpyAsync(dP, P.data(), P.size() * sizeof(double), hipMemcpyHostToDevice, f->st);
-    if (e == hipSuccess) e = hipStreamSynchronize(f->st);   // P is a stack vector
-    if (e != hipSuccess) { rs = hip_fail(f, e, "copy interpolation matrix"); break; }
+  for (int a = 0; a < c->dim; ++a) {
     size_t inner = 1, outer = (size_t)c->K;
     for (int b = 0; b < a; ++b) inner *= sizes[b];
     for (int b = a + 1; b < c->dim; ++b) outer *= sizes[b];
     const bool last = a == c->dim - 1;
     void* dst = last ? Xf : (a == 0 ? f->T64 : f->Gp);
     const double scale = last ? std::pow(2.0, -0.5 * c->dim) : 1.0;
-    e = prolong_axis(src, dst, dP, n, inner, outer, scale, f->st);
-    if (e != hipSuccess) { rs = hip_fail(f, e, "prolong_axis"); break; }
-    sizes[a] = 2 * (size_t)n;
+    GPE_HIP(f, prolong_axis(src, dst, c->ax[a].tw64, f->ax[a].tw64, c->n[a], inner, outer, scale, f->st));
+    sizes[a] *= 2;
     src = dst;
   }
-  hipError_t e = hipStreamSynchronize(f->st);
-  for (double* m : mats) (void)hipFree(m);
-  if (rs != GPE_OK) return rs;
-  if (e != hipSuccess) return hip_fail(f, e, "prolong sync");
+  GPE_HIP(f, hipStreamSynchronize(f->st));
   return GPE_OK;
 }
 

@@ -382,12 +382,13 @@ template <typename T>
 hipError_t xpass_batched(int F, int var, const XpassArgs<T>* args, const Span& sp, hipStream_t st);
 int xpass_batch_blocks(int n, int F, int var, size_t npts);
 
-// Multigrid transfer (c128 fields).  prolong_axis: out[o][j'][i] = scale *
-// sum_k P[j' n + k] in[o][k][i] with j' < 2n (P real, on the device).
+// Multigrid transfer (c128 fields).  prolong_axis: lines of n values (stride
+// inner, outer blocks of n inner) to the Fourier interpolant on 2n nodes, times
+// scale; tw, tw2: FP64 twiddles of the coarse and the fine axis.
 // restrict_inject: coarse[c][z][y][x] = scale * fine[c][2z][2y][2x] (nc = coarse
 // sizes, x first).
-hipError_t prolong_axis(const void* in, void* out, const double* P, int n, size_t inner, size_t outer, double scale,
-                        hipStream_t st);
+hipError_t prolong_axis(const void* in, void* out, const void* tw, const void* tw2, int n, size_t inner, size_t outer,
+                        double scale, hipStream_t st);
 hipError_t restrict_inject(const void* fine, void* coarse, int K, int dim, const int* nc, double scale,
                            hipStream_t st);
 

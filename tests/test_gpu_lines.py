@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 
 import oracle
+from oracle.multigrid import prolong as oracle_prolong
 from paper_1907_01194_amd import workloads as W
 from helpers import oracle_problem, small_spec
 
@@ -65,3 +66,21 @@ def test_energy_and_gradients_every_line_length(n):
             assert_field(host(G), ref, 1e-11, "gradient")
             assert abs(gn - np.linalg.norm(ref)) <= 1e-11 * gn
         gp.close()
+
+
+@pytest.mark.parametrize("n", [s for s in SIZES if 2 * s in SIZES])
+def test_prolong_every_line_length(n):
+    """Fourier prolongation of every coarse length, as a contiguous and as a
+    strided axis with partly filled tiles, against the oracle: 1e-12 on fields
+    (one forward and one inverse transform per axis, a few ulps times log2 n)."""
+    import torch
+    from paper_1907_01194_amd.binding import Problem
+    from gpu_util import dev, host, assert_field
+    for F, grid in ((2, (n,)), (1, (n, 6)), (3, (4, n)), (1, (6, 4, n))):
+        print("prolong, coarse length", n, "grid", grid, flush=True)
+        sc, sf = small_spec(F, grid), small_spec(F, tuple(2 * m for m in grid))
+        Xc = W.random_direction(sc, n)
+        pc, pf = Problem(sc, "fp64"), Problem(sf, "fp64")
+        assert_field(host(pc.prolong(dev(Xc), pf)), oracle_prolong(oracle_problem(sc), Xc), 1e-12, "prolong")
+        pc.close()
+        pf.close()
