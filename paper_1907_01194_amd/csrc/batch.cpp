@@ -61,13 +61,15 @@ gpe_status ops(gpe_batch* b, const std::vector<A>& recs, const std::vector<int>&
 }
 
 // Finalize records of every problem of g (slot counts checked against the stride).
+enum SlotStride { STRIDE_NBLK = 0, STRIDE_PART, STRIDE_COMP };   // partials from slot to slot
 gpe_status fin_records(gpe_batch* b, const std::vector<Item>& g, int nq, const std::vector<double*>& gram,
-                       const std::vector<SlotCounts>& nb, bool pstride, bool cg, std::vector<FinArgs>* recs) {
+                       const std::vector<SlotCounts>& nb, SlotStride kind, bool cg, std::vector<FinArgs>* recs) {
   gpe_handle* h0 = b->hs[0];
   recs->resize(g.size());
   for (size_t i = 0; i < g.size(); ++i) {
     gpe_handle* h = g[i].c->h;
-    const size_t stride = pstride ? h->pstride : (size_t)h->nblk;
+    const size_t stride = kind == STRIDE_PART ? h->pstride
+                          : (size_t)(kind == STRIDE_COMP ? comp_blocks(h->npts) : h->nblk);
     for (int q = 0; q < nq; ++q)
       if (nb[i].nb[q] < 0 || (size_t)nb[i].nb[q] > stride) return fail(h0, GPE_EINVAL, "finalize: slot count");
     (*recs)[i] = FinArgs{h->part, h->res, gram[i], stride, nb[i], cg ? h->res + CG_DONE : nullptr};
@@ -76,10 +78,10 @@ gpe_status fin_records(gpe_batch* b, const std::vector<Item>& g, int nq, const s
 }
 
 gpe_status fin(gpe_batch* b, const std::vector<Item>& g, int nq, int post, const std::vector<double*>& gram,
-               const std::vector<SlotCounts>& nb, bool pstride, bool cg = false) {
+               const std::vector<SlotCounts>& nb, SlotStride kind, bool cg = false) {
   gpe_handle* h0 = b->hs[0];
   std::vector<FinArgs> recs;
-  GPE_TRY(fin_records(b, g, nq, gram, nb, pstride, cg, &recs));
+  GPE_TRY(fin_records(b, g, nq, gram, nb, kind, cg, &recs));
   const void* d = nullptr;
   GPE_TRY(b->sg.put(h0, b->st, recs.data(), sizeof(FinArgs) * recs.size(), &d));
   GPE_HIP(h0, finalize_batched(reinterpret_cast<const FinArgs*>(d), (int)recs.size(), nq, post, b->F, b->st));
@@ -111,7 +113,7 @@ gpe_status fin_nblk(gpe_batch* b, const std::vector<Item>& g, int nq, int post, 
                     bool cg = false) {
   std::vector<SlotCounts> nb(g.size());
   for (size_t i = 0; i < g.size(); ++i) nb[i] = all_slots(g[i].c->h->nblk);
-  return fin(b, g, nq, post, gram, nb, false, cg);
+  return fin(b, g, nq, post, gram, nb, STRIDE_NBLK, cg);
 }
 
 std::vector<double*> no_gram(size_t n) { return std::vector<double*>(n, nullptr); }
@@ -202,29 +204,53 @@ gpe_status ex_norms(gpe_batch* b, std::vector<Item>& g) {
     return GPE_OK;
   }
   std::vector<int> nb(g.size());
-  for (size_t i = 0; i < g.size(); ++i) nb[i] = g[i].c->h->nblk;
+  std::vector<SlotCounts> sc(g.size());
+  for (size_t i = 0; i < g.size(); ++i) {
+    const int nbc = comp_blocks(g[i].c->h->npts);
+    nb[i] = g[i].c->h->K * nbc;
+    sc[i] = all_slots(nbc);
+  }
   auto run = [&](auto tag) -> gpe_status {
     using A = decltype(tag);
     std::vector<A> recs(g.size());
-    for (size_t i = 0; i < g.size(); ++i) recs[i] = A{g[i].r->a, g[i].r->b, g[i].c->h->part, g[i].c->h->npts};
+    for (size_t i = 0; i < g.size(); ++i) {
+      const gpe_handle* h = g[i].c->h;
+      recs[i] = A{g[i].r->a, g[i].r->b, h->part, h->npts, h->K};
+    }
     return ops(b, recs, nb);
   };
-  gpe_status s = GPE_EINVAL;
-  const bool x32 = g[0].r->b32;
-  switch (b->F * 2 + (x32 ? 1 : 0)) {
-    case 2: s = run(NormsArgs<double, double, 3>{}); break;
-    case 3: s = run(NormsArgs<double, float, 3>{}); break;
-    case 4: s = run(NormsArgs<double, double, 5>{}); break;
-    case 5: s = run(NormsArgs<double, float, 5>{}); break;
-    case 6: s = run(NormsArgs<double, double, 7>{}); break;
-    case 7: s = run(NormsArgs<double, float, 7>{}); break;
-  }
-  GPE_TRY(s);
+  GPE_TRY(g[0].r->b32 ? run(NormsArgs<double, float>{}) : run(NormsArgs<double, double>{}));
   // the slots of <u_i, xi_i> and ||xi_i||^2 only where some problem has a xi
   // (a problem without one reads only its ||u_i||^2)
   bool any_xi = false;
   for (auto& it : g) any_xi = any_xi || it.r->b != nullptr;
-  return fin_nblk(b, g, (any_xi ? 3 : 1) * (2 * b->F + 1), POST_NONE, no_gram(g.size()));
+  return fin(b, g, (any_xi ? 3 : 1) * (2 * b->F + 1), POST_NONE, no_gram(g.size()), sc, STRIDE_COMP);
+}
+
+gpe_status ex_rgbb(gpe_batch* b, std::vector<Item>& g) {
+  if (!b || g.size() == 1) {
+    for (auto& it : g) {
+      const Req& r = *it.r;
+      GPE_TRY(rgbb_enq(it.c->h, r.a, r.b, r.e, r.f, r.c, r.s0, r.s1));
+    }
+    return GPE_OK;
+  }
+  gpe_handle* h0 = b->hs[0];
+  std::vector<RgbbArgs> recs(g.size());
+  std::vector<FinSegArgs> fr(g.size());
+  std::vector<int> nb(g.size());
+  for (size_t i = 0; i < g.size(); ++i) {
+    const gpe_handle* h = g[i].c->h;
+    const Req& r = *g[i].r;
+    recs[i] = rgbb_args(h, r.a, r.b, r.e, r.f, r.c, r.s0, r.s1);
+    fr[i] = FinSegArgs{h->part, h->res, rgbb_segs(h)};
+    nb[i] = h->K * comp_blocks(h->npts);
+  }
+  GPE_TRY(ops(b, recs, nb));
+  const void* d = nullptr;
+  GPE_TRY(b->sg.put(h0, b->st, fr.data(), sizeof(FinSegArgs) * fr.size(), &d));
+  GPE_HIP(h0, finalize_segs_batched(reinterpret_cast<const FinSegArgs*>(d), (int)fr.size(), b->st));
+  return GPE_OK;
 }
 
 gpe_status ex_scale(gpe_batch* b, std::vector<Item>& g) {
@@ -368,7 +394,7 @@ gpe_status hvp_batched(gpe_batch* b, std::vector<Item>& g, bool riem, bool cg, b
   bool ab_local = riem && b->dim >= 2;
   for (size_t i = 0; i < m; ++i) ab_local = ab_local && xb[i] <= kAbLocalMax;
   std::vector<FinArgs> fab;
-  if (riem && !ab_local) GPE_TRY(fin_records(b, g, 7, gram, nb, true, cg, &fab));
+  if (riem && !ab_local) GPE_TRY(fin_records(b, g, 7, gram, nb, STRIDE_PART, cg, &fab));
   // remaining stages: the 1-D projection, or the other axis passes
   std::vector<ProjArgs<T, T, false>> pr;
   std::vector<int> pb, p0;
@@ -408,7 +434,7 @@ gpe_status hvp_batched(gpe_batch* b, std::vector<Item>& g, bool riem, bool cg, b
     }
   }
   std::vector<FinArgs> fk;   // the kappa finalize, where anyone reads kappa
-  if (kappa) GPE_TRY(fin_records(b, g, nq, gram, nb, true, cg, &fk));
+  if (kappa) GPE_TRY(fin_records(b, g, nq, gram, nb, STRIDE_PART, cg, &fk));
 
   // one staging copy for every launch below
   const void *dx = nullptr, *dx0 = nullptr, *dab = nullptr, *dp = nullptr, *dp0 = nullptr, *dk = nullptr;
@@ -474,7 +500,7 @@ gpe_status ex_cg(gpe_batch* b, std::vector<Item>& g) {
   std::vector<SlotCounts> sc(g.size());
   for (size_t i = 0; i < g.size(); ++i) sc[i] = all_slots(g[i].c->h->nblk);
   std::vector<FinArgs> fr;
-  if (!local) GPE_TRY(fin_records(b, g, 1, no_gram(g.size()), sc, false, true, &fr));
+  if (!local) GPE_TRY(fin_records(b, g, 1, no_gram(g.size()), sc, STRIDE_NBLK, true, &fr));
   auto run = [&](auto tag, auto dtag) -> gpe_status {
     using A = decltype(tag);
     using D = decltype(dtag);
@@ -526,6 +552,7 @@ gpe_status execute(gpe_batch* b, int kind, std::vector<Item>& g) {
     case RQ_EVAL: return ex_eval(b, g);
     case RQ_PGRAD: return ex_pgrad(b, g);
     case RQ_NORMS: return ex_norms(b, g);
+    case RQ_RGBB: return ex_rgbb(b, g);
     case RQ_SCALE: return ex_scale(b, g);
     case RQ_DOT: return ex_dot(b, g);
     case RQ_DIFF: return ex_diff(b, g);

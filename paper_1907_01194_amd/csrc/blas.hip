@@ -209,6 +209,12 @@ finalize_batched_kernel(const FinArgs* __restrict__ args, int nq, int post, int 
                 a.res, post, F, a.gram, nullptr, a.skip, nullptr);
 }
 
+__global__ void __launch_bounds__(kFinThreads) finalize_segs_batched_kernel(const FinSegArgs* __restrict__ args) {
+  const FinSegArgs& a = args[blockIdx.x];
+  finalize_body([&](int q) { return a.part + a.s.off[q]; }, [&](int q) { return a.s.nb[q]; }, a.s.nq, a.res, a.res,
+                POST_NONE, 1, nullptr, nullptr, nullptr, nullptr);
+}
+
 static bool counts_ok(const SlotCounts& nb, int nq, size_t stride) {
   if (nq < 1 || nq > kMaxQ || nq > (int)(sizeof(nb.nb) / sizeof(nb.nb[0]))) return false;
   for (int q = 0; q < nq; ++q)
@@ -248,6 +254,12 @@ hipError_t finalize_batched(const FinArgs* args, int nprob, int nq, int post, in
   return hipGetLastError();
 }
 
+hipError_t finalize_segs_batched(const FinSegArgs* args, int nprob, hipStream_t st) {
+  if (nprob < 1 || nprob > 65535) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(finalize_segs_batched_kernel, dim3(nprob), dim3(kFinThreads), 0, st, args);
+  return hipGetLastError();
+}
+
 // ----------------------------------------------------------------- projection
 template <typename T, typename TX, bool NORM>
 __device__ void run_op(const ProjArgs<T, TX, NORM>& a, int blk, int nblk) {
@@ -279,39 +291,70 @@ hipError_t project(int F, const void* X, const void* W, void* out, const double*
 }
 
 // ----------------------------------------------------------------- retraction support
-template <typename TU, typename TXI, int K>
-__device__ void run_op(const NormsArgs<TU, TXI, K>& a, int blk, int nblk) {
-  auto u = reinterpret_cast<const c_t<TU>*>(a.u);
+// Workgroups [i nbc, (i + 1) nbc) take component i (nbc = nblk / K): slot q K + i
+// holds nbc partials.  Bound by HBM on large fields (spin-3 128^3, c128: 470 MB in
+// 112 us with all components per point, 94 now), by latency on small ones (256^2
+// spin-2: 10.4 -> 5.3 us).
+template <typename TU, typename TXI>
+__device__ void run_op(const NormsArgs<TU, TXI>& a, int blk, int nblk) {
+  const int nbc = nblk / a.K, comp = blk / nbc, b0 = blk % nbc;
+  auto u = reinterpret_cast<const c_t<TU>*>(a.u) + (size_t)comp * a.npts;
   auto xi = reinterpret_cast<const c_t<TXI>*>(a.xi);
-  const size_t n = a.npts;
-  double acc[3 * K];
-#pragma unroll
-  for (int q = 0; q < 3 * K; ++q) acc[q] = 0.0;
-  for (size_t j = (size_t)blk * blockDim.x + threadIdx.x; j < n; j += (size_t)nblk * blockDim.x) {
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      const c_t<TU> av = u[i * n + j];
-      const double ax = av.x, ay = av.y;
-      acc[i] += ax * ax + ay * ay;
-      if (xi) {
-        const c_t<TXI> b = xi[i * n + j];
-        const double bx = b.x, by = b.y;
-        acc[K + i] += ax * bx + ay * by;
-        acc[2 * K + i] += bx * bx + by * by;
-      }
+  if (xi) xi += (size_t)comp * a.npts;
+  double acc[3] = {0.0, 0.0, 0.0};
+  const size_t step = (size_t)nbc * blockDim.x;
+#pragma unroll 4
+  for (size_t j = (size_t)b0 * blockDim.x + threadIdx.x; j < a.npts; j += step) {
+    const c_t<TU> av = u[j];
+    const double ax = av.x, ay = av.y;
+    acc[0] += ax * ax + ay * ay;
+    if (xi) {
+      const c_t<TXI> b = xi[j];
+      const double bx = b.x, by = b.y;
+      acc[1] += ax * bx + ay * by;
+      acc[2] += bx * bx + by * by;
     }
   }
-  block_partials_any<3 * K>(acc, a.part, nblk, blk);
+  block_partials_any(acc, a.part + (size_t)comp * nbc, (size_t)a.K * nbc, b0);
 }
 
 template <typename TU, typename TXI>
-hipError_t comp_norms(int K, const void* u, const void* xi, double* part, int nblk, size_t npts, hipStream_t st) {
-  switch (K) {
-    case 3: return launch_single(NormsArgs<TU, TXI, 3>{u, xi, part, npts}, nblk, st);
-    case 5: return launch_single(NormsArgs<TU, TXI, 5>{u, xi, part, npts}, nblk, st);
-    case 7: return launch_single(NormsArgs<TU, TXI, 7>{u, xi, part, npts}, nblk, st);
-    default: return hipErrorInvalidValue;
+hipError_t comp_norms(int K, const void* u, const void* xi, double* part, int nbc, size_t npts, hipStream_t st) {
+  return launch_single(NormsArgs<TU, TXI>{u, xi, part, npts, K}, K * nbc, st);
+}
+
+// Closing pass of a first-order step from u to z (see RgbbArgs): one read of z,
+// G(z), u and the gradient at u gives the Riemannian gradient at z, the
+// Barzilai-Borwein products and the norms the next retraction needs.  As
+// separate operations (projection, two differences, two inner products, the
+// norms) these traverse 16 fields and wait for the host four times (256^2 spin-2:
+// 45 us of kernels in 12 launches); here 5 and once (7 us and a finalize).
+__device__ void run_op(const RgbbArgs& a, int blk, int nblk) {
+  const int nbc = nblk / a.K, comp = blk / nbc, b0 = blk % nbc;
+  const size_t o = (size_t)comp * a.npts;
+  auto z = reinterpret_cast<const double2*>(a.z) + o;
+  auto gz = reinterpret_cast<const double2*>(a.gz) + o;
+  auto u = reinterpret_cast<const double2*>(a.u) + o;
+  auto gu = reinterpret_cast<const double2*>(a.gu) + o;
+  auto out = reinterpret_cast<double2*>(a.out) + o;
+  const double c = a.c0 + a.c1 * (double)(a.K / 2 - comp);
+  double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+  const size_t step = (size_t)nbc * blockDim.x;
+#pragma unroll 2
+  for (size_t j = (size_t)b0 * blockDim.x + threadIdx.x; j < a.npts; j += step) {
+    const double2 zv = z[j], uv = u[j], pv = gu[j];
+    double2 g = gz[j];
+    g.x -= c * zv.x;
+    g.y -= c * zv.y;
+    out[j] = g;
+    const double sx = zv.x - uv.x, sy = zv.y - uv.y, vx = g.x - pv.x, vy = g.y - pv.y;
+    acc[0] += zv.x * zv.x + zv.y * zv.y;
+    acc[1] += zv.x * g.x + zv.y * g.y;
+    acc[2] += g.x * g.x + g.y * g.y;
+    acc[3] += sx * vx + sy * vy;
+    acc[4] += vx * vx + vy * vy;
   }
+  block_partials_any(acc, a.part + (size_t)comp * nbc, (size_t)a.K * nbc, b0);
 }
 
 template <typename TU, typename TXI, typename TO>
@@ -321,7 +364,9 @@ __device__ void run_op(const ScaleArgs<TU, TXI, TO>& a, int blk, int nblk) {
   auto out = reinterpret_cast<c_t<TO>*>(a.out);
   const size_t n = a.npts;
   const size_t total = (size_t)a.K * n;
-  for (size_t e = (size_t)blk * blockDim.x + threadIdx.x; e < total; e += (size_t)nblk * blockDim.x) {
+  const bool rev = read_backwards(total * sizeof(c_t<TU>));   // (the norms before it ended on the last component)
+  for (size_t f = (size_t)blk * blockDim.x + threadIdx.x; f < total; f += (size_t)nblk * blockDim.x) {
+    const size_t e = rev ? total - 1 - f : f;
     const int i = (int)(e / n);
     const double si = a.s[i];
     const c_t<TU> av = u[e];
@@ -388,9 +433,9 @@ __device__ void run_op(const CgArgs<T>& a, int blk, int nblk) {
   auto r = reinterpret_cast<c_t<T>*>(a.r);
   const T ca = (T)(a.adev ? *a.adev : a.a);
   double acc[1] = {0.0};
-  // last element first: the HVP before this update ends on the last component
+  const bool rev = read_backwards(a.n * sizeof(c_t<T>));   // (the HVP before this update ends on the last component)
   for (size_t f = (size_t)blk * blockDim.x + threadIdx.x; f < a.n; f += (size_t)nblk * blockDim.x) {
-    const size_t e = a.n - 1 - f;
+    const size_t e = rev ? a.n - 1 - f : f;
     const c_t<T> qv = q[e];
     c_t<T> rv = r[e];
     if (z) {
@@ -588,15 +633,9 @@ GPE_OP(ProjArgs<double, double, true>)
 GPE_OP(ProjArgs<double, double, false>)
 GPE_OP(ProjArgs<float, float, true>)
 GPE_OP(ProjArgs<float, float, false>)
-GPE_OP(NormsArgs<double, double, 3>)
-GPE_OP(NormsArgs<double, double, 5>)
-GPE_OP(NormsArgs<double, double, 7>)
-GPE_OP(NormsArgs<double, float, 3>)
-GPE_OP(NormsArgs<double, float, 5>)
-GPE_OP(NormsArgs<double, float, 7>)
-GPE_OP(NormsArgs<float, float, 3>)
-GPE_OP(NormsArgs<float, float, 5>)
-GPE_OP(NormsArgs<float, float, 7>)
+GPE_OP(NormsArgs<double, double>)
+GPE_OP(NormsArgs<double, float>)
+GPE_OP(RgbbArgs)
 GPE_OP(ScaleArgs<double, double, double>)
 GPE_OP(ScaleArgs<double, float, double>)
 GPE_OP(ScaleArgs<float, float, float>)
@@ -623,7 +662,6 @@ template hipError_t project<double, double>(int, const void*, const void*, void*
 template hipError_t project<float, float>(int, const void*, const void*, void*, const double*, double*, int, size_t, hipStream_t);
 template hipError_t comp_norms<double, double>(int, const void*, const void*, double*, int, size_t, hipStream_t);
 template hipError_t comp_norms<double, float>(int, const void*, const void*, double*, int, size_t, hipStream_t);
-template hipError_t comp_norms<float, float>(int, const void*, const void*, double*, int, size_t, hipStream_t);
 template hipError_t scale_comps<double, double, double>(int, const void*, const void*, double, const double*, void*, size_t, hipStream_t);
 template hipError_t scale_comps<double, float, double>(int, const void*, const void*, double, const double*, void*, size_t, hipStream_t);
 template hipError_t scale_comps<float, float, float>(int, const void*, const void*, double, const double*, void*, size_t, hipStream_t);

@@ -51,6 +51,14 @@ __device__ __forceinline__ int xcd_local_block(int b, int nb) {
   return x * q + (x < rem ? x : rem) + i;
 }
 
+// Whether an elementwise pass over a field of `bytes` that an earlier pass has
+// just gone through takes the last element first: a large field's end is what
+// the 256 MB cache still holds (retraction scaling at spin-3 128^3, 235 MB: 120 ->
+// 115 us), while a field that fits the XCDs' L2 (32 MB together) is best met in
+// the same order, since the same workgroup numbers, hence XCDs, then read back
+// what they wrote (256^2 spin-2, 5 MB: 6.2 -> 4.0 us).
+__host__ __device__ __forceinline__ bool read_backwards(size_t bytes) { return bytes > ((size_t)32 << 20); }
+
 // Sum of a double over the wavefront (shuffle tree).
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
@@ -101,10 +109,27 @@ __device__ inline void block_partials_any(const double (&acc)[NQ], double* __res
   }
 }
 
+// Workgroups of a reduction over npts grid points: four points per thread, but
+// no fewer than one per thread up to 256 workgroups (a small field's reduction is
+// bound by each thread's chain of loads: the CG update of a 256^2 spin-2 field
+// takes 10.2 us with 64 workgroups and 5.7 with 256).
 inline int red_blocks(size_t npts) {
+  const size_t wide = (npts + kRedThreads - 1) / kRedThreads;
   size_t b = (npts + kRedThreads * 4 - 1) / (kRedThreads * 4);
+  if (b < 256) b = wide < 256 ? wide : 256;
   if (b < 1) b = 1;
   if (b > (size_t)kMaxRedBlocks) b = kMaxRedBlocks;
+  return (int)b;
+}
+
+// Workgroups per component of a reduction that keeps the components' sums
+// apart: each takes one component's points, so it streams two or four arrays,
+// not that many per component (K of them a power of two apart), and carries a
+// few sums instead of several per component.
+inline int comp_blocks(size_t npts) {
+  size_t b = (npts + kRedThreads * 2 - 1) / (kRedThreads * 2);
+  if (b < 1) b = 1;
+  if (b > 512) b = 512;
   return (int)b;
 }
 

@@ -61,11 +61,11 @@ gpe_status laplacian(gpe_handle* h, const void* in, void* out) {
 template gpe_status laplacian<double>(gpe_handle*, const void*, void*);
 template gpe_status laplacian<float>(gpe_handle*, const void*, void*);
 
-gpe_status finalize_enq(gpe_handle* h, int nq, int post, double* gram) {
+gpe_status finalize_enq(gpe_handle* h, int nblk, int nq, int post, double* gram) {
   SlotCounts nb;
-  for (int q = 0; q < kMaxQ; ++q) nb.nb[q] = h->nblk;
+  for (int q = 0; q < kMaxQ; ++q) nb.nb[q] = nblk;
   GPE_KT(h, KK_FINALIZE,
-         finalize(h->part, h->nblk, nb, nq, h->res, post, h->F, gram, h->ticket, nullptr, h->hres, h->st));
+         finalize(h->part, nblk, nb, nq, h->res, post, h->F, gram, h->ticket, nullptr, h->hres, h->st));
   return GPE_OK;
 }
 
@@ -181,7 +181,7 @@ gpe_status pgrad_enq(gpe_handle* h, const void* X, const void* G, void* gR, doub
   GPE_KT(h, KK_PROJECT,
          launch_single(ProjArgs<double, double, true>{X, G, gR, nullptr, ag, bg, h->part, h->npts, h->F}, h->nblk,
                        h->st));
-  return finalize_enq(h, 1, POST_NONE, nullptr);
+  return finalize_enq(h, h->nblk, 1, POST_NONE, nullptr);
 }
 
 gpe_status pgrad_read(gpe_handle* h, double* gnorm) {
@@ -258,6 +258,13 @@ template <typename T>
 static gpe_status tune_xpass_t(gpe_handle* h) {
   const int nv = xpass_variants(h->n[0]);
   if (nv <= 1 || h->npts < (1u << 15)) return GPE_OK;
+  // Below 2^18 points a pass takes 10 us or so, which events around a launch (+- 5
+  // us) cannot rank; the smallest workgroups, the most of them, are the fastest
+  // there (spin-2 256^2, rocprof: 12.3, 12.2 and 15.0 us for variants 0, 1, 2).
+  if (h->npts < (1u << 18)) {
+    h->xvar = 0;
+    return GPE_OK;
+  }
   // three distinct fields for X, Z, LX (aliasing them would hide memory traffic)
   void* A = sizeof(T) == 8 ? h->T64 : h->T32;
   void* Bz = sizeof(T) == 8 ? h->Xp : h->Xp32;
@@ -333,11 +340,48 @@ gpe_status hvp(gpe_handle* h, const void* Z, void* HZ, bool riem, double sigma, 
 
 gpe_status norms_enq(gpe_handle* h, const void* u, const void* xi, bool xi32) {
   if (xi32)
-    GPE_KT(h, KK_NORMS, (comp_norms<double, float>(h->K, u, xi, h->part, h->nblk, h->npts, h->st)));
+    GPE_KT(h, KK_NORMS, (comp_norms<double, float>(h->K, u, xi, h->part, comp_blocks(h->npts), h->npts, h->st)));
   else
-    GPE_KT(h, KK_NORMS, (comp_norms<double, double>(h->K, u, xi, h->part, h->nblk, h->npts, h->st)));
-  // without xi only the K slots of ||u_i||^2 are written, so only they are summed
-  return finalize_enq(h, xi ? 3 * h->K : h->K, POST_NONE, nullptr);
+    GPE_KT(h, KK_NORMS, (comp_norms<double, double>(h->K, u, xi, h->part, comp_blocks(h->npts), h->npts, h->st)));
+  return finalize_enq(h, comp_blocks(h->npts), xi ? 3 * h->K : h->K, POST_NONE, nullptr);
+}
+
+RgbbArgs rgbb_args(const gpe_handle* h, const void* z, const void* gz, const void* u, const void* gu, void* out,
+                   double ag, double bg) {
+  return RgbbArgs{z, gz, u, gu, out, ag, bg, h->part, h->npts, h->K};
+}
+
+// Sums 0 .. 3K-1 per component; the last two over every component (consecutive slots).
+SlotSegs rgbb_segs(const gpe_handle* h) {
+  const int K = h->K, nbc = comp_blocks(h->npts);
+  SlotSegs s;
+  s.nq = 3 * K + 2;
+  for (int q = 0; q < s.nq; ++q) {
+    const int first = q < 3 * K ? q : (q == 3 * K ? 3 * K : 4 * K);
+    s.off[q] = first * nbc;
+    s.nb[q] = q < 3 * K ? nbc : K * nbc;
+  }
+  return s;
+}
+
+gpe_status rgbb_enq(gpe_handle* h, const void* z, const void* gz, const void* u, const void* gu, void* out, double ag,
+                    double bg) {
+  GPE_KT(h, KK_PROJECT,
+         launch_single(rgbb_args(h, z, gz, u, gu, out, ag, bg), h->K * comp_blocks(h->npts), h->st));
+  GPE_KT(h, KK_FINALIZE, finalize_segs(h->part, rgbb_segs(h), h->res, h->res, POST_NONE, h->F, nullptr, h->ticket,
+                                       h->hres, h->st));
+  return GPE_OK;
+}
+
+gpe_status rgbb_read(gpe_handle* h, RetractNorms* rn, double* gnorm, double* sv, double* vv) {
+  GPE_TRY(norms_read(h, true, rn));
+  GPE_TRY(finite(h, h->hres + 3 * h->K, 2, "the Barzilai-Borwein products"));
+  double g2 = 0.0;
+  for (int i = 0; i < h->K; ++i) g2 += rn->xx[i];
+  *gnorm = std::sqrt(g2);
+  *sv = h->hres[3 * h->K];
+  *vv = h->hres[3 * h->K + 1];
+  return GPE_OK;
 }
 
 gpe_status norms_read(gpe_handle* h, bool has_xi, RetractNorms* rn) {
@@ -413,7 +457,7 @@ gpe_status dot_enq(gpe_handle* h, const void* a, bool a32, const void* b, bool b
   else if (a32 && b32) GPE_KT(h, KK_VECTOR, (dot<float, float>(a, b, h->part, h->nblk, n, h->st)));
   else if (!a32 && b32) GPE_KT(h, KK_VECTOR, (dot<double, float>(a, b, h->part, h->nblk, n, h->st)));
   else GPE_KT(h, KK_VECTOR, (dot<double, float>(b, a, h->part, h->nblk, n, h->st)));
-  return finalize_enq(h, 1, POST_NONE, nullptr);
+  return finalize_enq(h, h->nblk, 1, POST_NONE, nullptr);
 }
 
 gpe_status dot_read(gpe_handle* h, double* out) {
@@ -952,8 +996,8 @@ gpe_status gpe_retract_noalloc(const gpe_problem* pr, const void* X, const void*
   const int F = pr->F, K = 2 * F + 1;
   size_t npts = 1;
   for (int a = 0; a < pr->dim; ++a) npts *= (size_t)pr->n[a];
-  const int nblk = red_blocks(npts);
-  const int nq = Xi ? 3 * K : K;   // without Xi the norms kernel writes the K slots of ||X_i||^2 only
+  const int nblk = comp_blocks(npts);   // per component
+  const int nq = Xi ? 3 * K : K;
   if ((size_t)3 * K * (size_t)nblk > kNaPart) return fail(nullptr, GPE_EINVAL, "problem exceeds the static scratch");
   double* base = nullptr;
   GPE_TRY(scratch_on_device(&base));

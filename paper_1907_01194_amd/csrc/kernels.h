@@ -172,9 +172,10 @@ hipError_t project(int F, const void* X, const void* W, void* out, const double*
                    double* part, int nblk, size_t npts, hipStream_t st);
 
 // Per-component sums for the retraction: [i] ||u_i||^2, [K+i] <u_i, xi_i>,
-// [2K+i] ||xi_i||^2 (nq = 3K).  xi may be null (then only the first K are set).
+// [2K+i] ||xi_i||^2 (nq = 3K), nbc partials each (comp_blocks).  xi may be null
+// (the sums with xi are then 0).
 template <typename TU, typename TXI>
-hipError_t comp_norms(int K, const void* u, const void* xi, double* part, int nblk,
+hipError_t comp_norms(int K, const void* u, const void* xi, double* part, int nbc,
                       size_t npts, hipStream_t st);
 
 // out_i = s_i (u_i + t xi_i), i = 0..K-1.  out may alias u.
@@ -291,11 +292,27 @@ template <typename TU, typename TXI, typename TO> struct ScaleArgs {   // out_i 
   size_t npts;
   int K;
 };
-template <typename TU, typename TXI, int K> struct NormsArgs {   // retraction norms (see comp_norms)
+template <typename TU, typename TXI> struct NormsArgs {   // retraction norms (see comp_norms); K nbc workgroups
   const void* u;
   const void* xi;
   double* part;
   size_t npts;
+  int K;
+};
+// First-order step from u (Riemannian gradient gu) to z (Euclidean gradient gz,
+// multipliers c0, c1): out_i = gz_i - (c0 + c1 l_i) z_i, with K nbc workgroups and
+// nbc partials per slot: [i] ||z_i||^2, [K+i] <z_i, out_i>, [2K+i] ||out_i||^2,
+// [3K+i] <z_i - u_i, out_i - gu_i>, [4K+i] ||out_i - gu_i||^2.
+struct RgbbArgs {
+  const void* z;
+  const void* gz;
+  const void* u;
+  const void* gu;
+  void* out;
+  double c0, c1;
+  double* part;
+  size_t npts;
+  int K;
 };
 // out_i = W_i - (c0 + c1 l_i) X_i with (c0, c1) = coef[0..1] (device) or, if
 // coef is null, the values given; NORM: partials of ||out||^2.
@@ -338,6 +355,13 @@ struct FinArgs {
   const double* skip;
 };
 hipError_t finalize_batched(const FinArgs* args, int nprob, int nq, int post, int F, hipStream_t st);
+// The same over segments, no post-operation.
+struct FinSegArgs {
+  const double* part;
+  double* res;
+  SlotSegs s;
+};
+hipError_t finalize_segs_batched(const FinSegArgs* args, int nprob, hipStream_t st);
 
 // Batched axis pass (lap_axis_ex for every problem; line length n of each
 // problem's axis a power of two in 16..512, see batch_size_supported).

@@ -129,7 +129,7 @@ gpe_status laplacian(gpe_handle* h, const void* in, void* out);
 // kernels and the finalize into h->res (stream-ordered, no synchronisation);
 // after h->res has reached h->hres (fetch, or a lock-step round of a batch)
 // *_read checks and returns the values.  The plain forms do both.
-gpe_status finalize_enq(gpe_handle* h, int nq, int post, double* gram);
+gpe_status finalize_enq(gpe_handle* h, int nblk, int nq, int post, double* gram);
 gpe_status fetch(gpe_handle* h);   // synchronises: what the last finalize mirrored is in h->hres
 
 // Energy, gradient G (may be null), alpha_g/beta_g of G and ||X_i||^2 into gram.
@@ -158,6 +158,15 @@ struct RetractNorms {
 };
 gpe_status norms_enq(gpe_handle* h, const void* u, const void* xi, bool xi32);
 gpe_status norms_read(gpe_handle* h, bool has_xi, RetractNorms* rn);
+// Closing pass of a first-order step (RgbbArgs): the Riemannian gradient at z, its
+// norm, <s, v> and <v, v> of the differences s = z - u, v = grad(z) - grad(u), and
+// the retraction norms of (z, grad(z)).
+RgbbArgs rgbb_args(const gpe_handle* h, const void* z, const void* gz, const void* u, const void* gu, void* out,
+                   double ag, double bg);
+SlotSegs rgbb_segs(const gpe_handle* h);
+gpe_status rgbb_enq(gpe_handle* h, const void* z, const void* gz, const void* u, const void* gu, void* out, double ag,
+                    double bg);
+gpe_status rgbb_read(gpe_handle* h, RetractNorms* rn, double* gnorm, double* sv, double* vv);
 gpe_status retract_norms(gpe_handle* h, const void* u, const void* xi, bool xi32, RetractNorms* rn);
 // Coefficients (alpha, beta) of the projection of xi onto the tangent space at
 // u (Lemma 4.1 with the measured Gram system) from the norms of u and xi.

@@ -24,6 +24,8 @@ enum ReqKind {
   RQ_EVAL = 0,   // energy and gradient: a = X, c = G, gram; read with eval_read
   RQ_PGRAD,      // c = P_a b with multipliers (s0, s1), all c128; read with pgrad_read
   RQ_NORMS,      // retraction norms of a (c128) and b (b32, or null); read with norms_read
+  RQ_RGBB,       // closing pass of a first-order step: z = a, G(z) = b, u = e, grad(u) = f, grad(z) -> c,
+                 // multipliers (s0, s1); read with rgbb_read
   RQ_SCALE,      // c (c128) = sig_i (a_i + s0 b_i), a c128, b in b32 or null
   RQ_DOT,        // <a, b> over n elements (a32, b32); read with dot_read
   RQ_DIFF,       // c (c32) = a - b (both c128), n elements
@@ -44,6 +46,8 @@ struct Req {
   const void* b = nullptr;
   void* c = nullptr;
   void* d = nullptr;
+  const void* e = nullptr;
+  const void* f = nullptr;
   double s0 = 0.0, s1 = 0.0;
   double sig[7] = {0, 0, 0, 0, 0, 0, 0};
   double* gram = nullptr;

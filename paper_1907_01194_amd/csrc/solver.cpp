@@ -67,8 +67,6 @@ enum {
   B_GZ,      // gradient at the trial point (c128)
   B_GR,      // Riemannian gradient at u (c128)
   B_GRZ,     // Riemannian gradient at the trial point (c128)
-  B_T1,      // scratch (c128)
-  B_T2,      // scratch (c128)
   B_R,       // CG residual (work)
   B_P,       // CG direction (work)
   B_AP,      // Hess p (work)
@@ -110,6 +108,18 @@ Req rq_pgrad(const void* X, const void* G, void* gR, double ag, double bg) {
   r.a = X;
   r.b = G;
   r.c = gR;
+  r.s0 = ag;
+  r.s1 = bg;
+  return r;
+}
+Req rq_rgbb(const void* z, const void* gz, const void* u, const void* gu, void* out, double ag, double bg) {
+  Req r;
+  r.kind = RQ_RGBB;
+  r.a = z;
+  r.b = gz;
+  r.c = out;
+  r.e = u;
+  r.f = gu;
   r.s0 = ag;
   r.s1 = bg;
   return r;
@@ -315,12 +325,16 @@ SolveTask solve_task(Ctx& c, void* Xio, const gpe_solve_opts* o, gpe_solve_stats
   {
     double C = E, Q = 1.0;
     double step = o->rgbb_step0 / std::fmax(gn, 1e-300);
+    RetractNorms rn;   // of (u, gR); a step's closing pass leaves the next one's
+    bool have_rn = false;
     for (int k = 0; k < o->rgbb_maxit && gn > o->rgbb_tol; ++k) {
       if (o->time_limit > 0 && clk.sec() > o->time_limit) break;
-      RetractNorms rn;
-      c.push(rq_norms(u, gR, false));
-      ROUND;
-      CO_TRY(norms_read(h, true, &rn));
+      if (!have_rn) {
+        c.push(rq_norms(u, gR, false));
+        ROUND;
+        CO_TRY(norms_read(h, true, &rn));
+        have_rn = true;
+      }
       double t = step, Ez = 0, agz = 0, bgz = 0;
       bool have_z = false;
       for (int ls = 0; ls < o->ls_max; ++ls) {
@@ -340,19 +354,10 @@ SolveTask solve_task(Ctx& c, void* Xio, const gpe_solve_opts* o, gpe_solve_stats
         t *= o->rgbb_delta;
       }
       if (!have_z) break;                 // no trial step could be retracted
-      double gnz;
-      c.push(rq_pgrad(B[B_Z], B[B_GZ], B[B_GRZ], agz, bgz));
+      double gnz, sv, vv;
+      c.push(rq_rgbb(B[B_Z], B[B_GZ], u, gR, B[B_GRZ], agz, bgz));
       ROUND;
-      CO_TRY(pgrad_read(h, &gnz));
-      c.push(rq_diff(B[B_Z], u, B[B_T1], false, n));
-      c.push(rq_diff(B[B_GRZ], gR, B[B_T2], false, n));
-      c.push(rq_dot(B[B_T1], false, B[B_T2], false, n));
-      ROUND;
-      double sv, vv;
-      CO_TRY(dot_read(h, &sv));
-      c.push(rq_dot(B[B_T2], false, B[B_T2], false, n));
-      ROUND;
-      CO_TRY(dot_read(h, &vv));
+      CO_TRY(rgbb_read(h, &rn, &gnz, &sv, &vv));
       if (vv > 0) step = std::fabs(sv) / vv;
       step = std::fmin(std::fmax(step, 1e-20), 1e20);
       const double Qn = o->rgbb_varrho * Q + 1.0;
