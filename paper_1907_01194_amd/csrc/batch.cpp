@@ -8,6 +8,7 @@
 #include <cmath>
 #include <cstring>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "common.h"
@@ -72,7 +73,8 @@ gpe_status fin_records(gpe_batch* b, const std::vector<Item>& g, int nq, const s
                           : (size_t)(kind == STRIDE_COMP ? comp_blocks(h->npts) : h->nblk);
     for (int q = 0; q < nq; ++q)
       if (nb[i].nb[q] < 0 || (size_t)nb[i].nb[q] > stride) return fail(h0, GPE_EINVAL, "finalize: slot count");
-    (*recs)[i] = FinArgs{h->part, h->res, gram[i], stride, nb[i], cg ? h->res + CG_DONE : nullptr};
+    (*recs)[i] = FinArgs{h->part, h->res, gram[i], stride, nb[i], cg ? h->res + CG_DONE : nullptr,
+                         cg ? nullptr : h->hres};
   }
   return GPE_OK;
 }
@@ -243,7 +245,7 @@ gpe_status ex_rgbb(gpe_batch* b, std::vector<Item>& g) {
     const gpe_handle* h = g[i].c->h;
     const Req& r = *g[i].r;
     recs[i] = rgbb_args(h, r.a, r.b, r.e, r.f, r.c, r.s0, r.s1);
-    fr[i] = FinSegArgs{h->part, h->res, rgbb_segs(h)};
+    fr[i] = FinSegArgs{h->part, h->res, h->hres, rgbb_segs(h)};
     nb[i] = h->K * comp_blocks(h->npts);
   }
   GPE_TRY(ops(b, recs, nb));
@@ -628,22 +630,22 @@ gpe_status Lockstep::round(std::vector<Ctx*>& cs, bool sync) {
   // the most queues: a problem's own order is kept and launches are shared.
   std::vector<size_t> head(cs.size(), 0);
   bool cg = false;   // some operation left its results in res alone
+  std::vector<std::pair<unsigned, int>> heads;   // distinct head operations and how many queues wait at each
+  std::vector<Item> g;
   for (;;) {
-    unsigned best = 0;
-    int best_n = 0;
+    heads.clear();
     for (size_t i = 0; i < cs.size(); ++i) {
       if (head[i] >= cs[i]->q.size()) continue;
       const unsigned k = key_of(cs[i]->q[head[i]]);
-      int n = 0;
-      for (size_t j = 0; j < cs.size(); ++j)
-        if (head[j] < cs[j]->q.size() && key_of(cs[j]->q[head[j]]) == k) ++n;
-      if (n > best_n) {
-        best_n = n;
-        best = k;
-      }
+      auto it = std::find_if(heads.begin(), heads.end(), [k](const auto& h) { return h.first == k; });
+      if (it == heads.end()) heads.push_back({k, 1});
+      else ++it->second;
     }
-    if (best_n == 0) break;
-    std::vector<Item> g;
+    if (heads.empty()) break;
+    const unsigned best = std::max_element(heads.begin(), heads.end(), [](const auto& a, const auto& b) {
+                            return a.second < b.second;
+                          })->first;
+    g.clear();
     for (size_t i = 0; i < cs.size(); ++i)
       if (head[i] < cs[i]->q.size() && key_of(cs[i]->q[head[i]]) == best) g.push_back({cs[i], &cs[i]->q[head[i]++]});
     cg = cg || g[0].r->cg;
@@ -656,10 +658,12 @@ gpe_status Lockstep::round(std::vector<Ctx*>& cs, bool sync) {
   for (Ctx* c : cs) c->q.clear();
   if (!sync) return GPE_OK;   // the staging arena keeps its place: its records may not be consumed yet
   gpe_handle* h0 = cs[0]->h;
-  if (b_) {
+  // the reductions arrived in hres with their finalize; the state a device-resident
+  // CG keeps in res has to be copied
+  if (cg && b_) {
     GPE_HIP(h0, hipMemcpyAsync(b_->hres, b_->res, sizeof(double) * kResDoubles * b_->hs.size(),
                                hipMemcpyDeviceToHost, b_->st));
-  } else if (cg) {   // (a lone handle's other reductions arrive in hres by themselves)
+  } else if (cg) {
     for (Ctx* c : cs)
       GPE_HIP(c->h, hipMemcpyAsync(c->h->hres, c->h->res, sizeof(double) * kResDoubles, hipMemcpyDeviceToHost,
                                    c->h->st));

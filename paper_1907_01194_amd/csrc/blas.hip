@@ -206,13 +206,13 @@ __global__ void __launch_bounds__(kFinThreads)
 finalize_batched_kernel(const FinArgs* __restrict__ args, int nq, int post, int F) {
   const FinArgs& a = args[blockIdx.x];
   finalize_body([&](int q) { return a.part + (size_t)q * a.stride; }, [&](int q) { return a.nb.nb[q]; }, nq, a.res,
-                a.res, post, F, a.gram, nullptr, a.skip, nullptr);
+                a.res, post, F, a.gram, nullptr, a.skip, a.mirror);
 }
 
 __global__ void __launch_bounds__(kFinThreads) finalize_segs_batched_kernel(const FinSegArgs* __restrict__ args) {
   const FinSegArgs& a = args[blockIdx.x];
   finalize_body([&](int q) { return a.part + a.s.off[q]; }, [&](int q) { return a.s.nb[q]; }, a.s.nq, a.res, a.res,
-                POST_NONE, 1, nullptr, nullptr, nullptr, nullptr);
+                POST_NONE, 1, nullptr, nullptr, nullptr, a.mirror);
 }
 
 static bool counts_ok(const SlotCounts& nb, int nq, size_t stride) {

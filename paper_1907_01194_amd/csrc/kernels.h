@@ -353,12 +353,14 @@ struct FinArgs {
   size_t stride;
   SlotCounts nb;
   const double* skip;
+  double* mirror;   // see finalize (null: none)
 };
 hipError_t finalize_batched(const FinArgs* args, int nprob, int nq, int post, int F, hipStream_t st);
 // The same over segments, no post-operation.
 struct FinSegArgs {
   const double* part;
   double* res;
+  double* mirror;
   SlotSegs s;
 };
 hipError_t finalize_segs_batched(const FinSegArgs* args, int nprob, hipStream_t st);
