@@ -257,8 +257,9 @@ gpe_status gpe_newton_solve(gpe_handle* h, void* X_inout, const gpe_solve_opts* 
                             gpe_solve_stats* stats);
 
 /* Launch schedule chosen at creation: the fused x-pass kernel of the HVP
- * comes in up to 3 variants (rows of the grid per workgroup: half, default,
- * double); gpe_create times each on the handle's grid and keeps the fastest.
+ * comes in up to 3 variants (rows of the grid for one wavefront, for two, or one
+ * row with a thread per point); gpe_create times each on the handle's grid and
+ * keeps the fastest (grids below 2^18 points take the last untimed).
  * Writes the chosen variant and up to nvariants measured times in
  * microseconds (0 where a variant was not timed). */
 gpe_status gpe_schedule(const gpe_handle* h, int* xpass_variant, float* variant_us, int nvariants);

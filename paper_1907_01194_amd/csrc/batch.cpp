@@ -382,7 +382,7 @@ gpe_status hvp_batched(gpe_batch* b, std::vector<Item>& g, bool riem, bool cg, b
     if (!h->has_point) return fail(h, GPE_EINVAL, "batched HVP before the set point");
     const Req& r = *g[i].r;
     const bool w64 = sizeof(T) == 8;
-    xr[i] = XpassArgs<T>{w64 ? h->Xp : h->Xp32, r.a, w64 ? h->LX64 : h->LX32,
+    xr[i] = XpassArgs<T>{w64 ? h->Xp : h->Xp32, r.a, !riem ? nullptr : w64 ? h->LX64 : h->LX32,
                          w64 ? (const void*)h->V64 : (const void*)h->V32, r.c, twid<T>(h->ax[0]), h->part,
                          h->ax[0].lamc, h->npts, h->pstride, h->ax[0].n, hvp_params(h, riem, r.s0),
                          cg ? h->res + CG_DONE : nullptr};

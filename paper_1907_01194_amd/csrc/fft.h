@@ -588,7 +588,9 @@ template <typename T, int N, bool CONTIG> constexpr long ax_tiles(int K, size_t 
 // ---------------------------------------------------------------- fused x pass
 // Fused x pass of the Hessian-vector product: RPB x-rows, all K components.
 // Schedule variant VAR: rows per workgroup for about one wavefront (0), two
-// (1, the default) or four (2).  At n = 128, K = 7 a variant-0 workgroup is one
+// (1, the default) or four (2); XVAR_LATENCY: one row and a thread for each of
+// its points, for grids whose few workgroups are bound by a thread's chain of
+// FP64 operations (the threads beyond the lines' idle during the transform).  At n = 128, K = 7 a variant-0 workgroup is one
 // wavefront that owns one row of every component: 56 lanes hold 16 values each
 // for the transform, 64 lanes two points each for the pointwise terms.
 //
@@ -602,12 +604,15 @@ template <typename T, int N, bool CONTIG> constexpr long ax_tiles(int K, size_t 
 // spill 70 registers.  Measured (c128, c64):
 //   spin-3 128^3 247 -> 194 us, 140 -> 102;  spin-1 256 x 256 x 64 212 -> 165, 92 -> 82;
 //   spin-2 96^3 79 -> 60 us, 41 -> 36;  spin-2 256^2 12.6 -> 12.2 us, 10.2 -> 9.8.
+constexpr int XVAR_LATENCY = 3;
 template <int N, int K, int VAR = 1> struct XGeo {
   static constexpr int TPL = make_plan(N).T;
   static constexpr int WANT = VAR == 0 ? 64 : VAR == 1 ? 128 : 256;
-  static constexpr int RPB = WANT / (K * TPL) >= 1 ? WANT / (K * TPL) : 1;
+  static constexpr int RPB = VAR == XVAR_LATENCY ? (N >= 64 ? 1 : 64 / N)
+                                                 : (WANT / (K * TPL) >= 1 ? WANT / (K * TPL) : 1);
   static constexpr int LINES = RPB * K;
-  static constexpr int THREADS = ((LINES * TPL + 63) / 64) * 64;
+  static constexpr int WORK = VAR == XVAR_LATENCY && RPB * N > LINES * TPL ? RPB * N : LINES * TPL;
+  static constexpr int THREADS = ((WORK + 63) / 64) * 64;
   static constexpr int PPT = (RPB * N + THREADS - 1) / THREADS;   // points per thread
   static constexpr bool kWave = 64 % TPL == 0;
   // LDS: the padded twiddle table, then LINES padded lines
@@ -656,7 +661,13 @@ __device__ __forceinline__ void xpass_body(const c_t<T>* __restrict__ X, const c
       for (int i = 0; i < K; ++i) {
         z[i] = at(Z + r0 + i * npts, pt * (unsigned)sizeof(T2));
         x[i] = at(X + r0 + i * npts, pt * (unsigned)sizeof(T2));
-        y[i] = at(Y + r0 + i * npts, pt * (unsigned)sizeof(T2));
+      }
+      if (Y) {
+#pragma unroll
+        for (int i = 0; i < K; ++i) y[i] = at(Y + r0 + i * npts, pt * (unsigned)sizeof(T2));
+      } else {
+#pragma unroll
+        for (int i = 0; i < K; ++i) y[i] = mk<T2>(0, 0);
       }
       const T vj = at(V + r0, pt * (unsigned)sizeof(T));
       T s_xw = 0, s_lxw = 0, s_xz = 0, s_lxz = 0, s_zq = 0, s_zz = 0;

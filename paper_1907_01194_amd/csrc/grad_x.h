@@ -21,15 +21,15 @@ namespace gpe {
 // GRAD: G = L_x X + q (point: G = L_x X alone), the partial sums
 //   [0] pointwise energy + 1/2 <X, L_x X>, [1 + i] <X_i, q_i + (L_x X)_i>, [1 + K + i] ||X_i||^2,
 // and copies of X to xc (c128) and xc32 (c64) where given.  !GRAD: [0] only.
-template <int N, int F, bool GRAD>
-__global__ void __launch_bounds__((XGeo<N, 2 * F + 1>::THREADS), 2)
+template <int N, int F, bool GRAD, int VAR>
+__global__ void __launch_bounds__((XGeo<N, 2 * F + 1, VAR>::THREADS), 2)
 grad_xpass_kernel(const double2* __restrict__ X, const double* __restrict__ V, double2* __restrict__ G,
                   double2* __restrict__ xc, float2* __restrict__ xc32, const double2* __restrict__ twg, long nrows,
                   size_t npts, double lamc, PwParams p, bool point, double* __restrict__ part, size_t stride) {
   using T = double;
   using T2 = double2;
   constexpr int K = 2 * F + 1;
-  using GG = XGeo<N, K>;
+  using GG = XGeo<N, K, VAR>;
   using St = Stage<N, 0>;
   constexpr int TPL = GG::TPL, RPB = GG::RPB, LINES = GG::LINES, PPT = GG::PPT;
   constexpr int LSTR = GG::template lstr<T>();
@@ -128,10 +128,10 @@ grad_xpass_kernel(const double2* __restrict__ X, const double* __restrict__ V, d
   block_partials_any<NQ>(acc, part, stride, blockIdx.x);
 }
 
-template <int N, int F>
+template <int N, int F, int VAR>
 static void launch_gx(const LapAxis& ax, size_t npts, const void* X, const double* V, void* G, void* xc, void* xc32,
                       const PwParams& p, bool point, double* part, size_t stride, int* nb, hipStream_t st) {
-  using GG = XGeo<N, 2 * F + 1>;
+  using GG = XGeo<N, 2 * F + 1, VAR>;
   const long nrows = (long)(npts / N);
   const int grid = (int)((nrows + GG::RPB - 1) / GG::RPB);
   const size_t lds = sizeof(double2) * GG::template lds_elems<double>();
@@ -143,8 +143,8 @@ static void launch_gx(const LapAxis& ax, size_t npts, const void* X, const doubl
                        reinterpret_cast<double2*>(G), reinterpret_cast<double2*>(xc), reinterpret_cast<float2*>(xc32),
                        reinterpret_cast<const double2*>(ax.tw64), nrows, npts, ax.lamc, p, point, part, stride);
   };
-  if (G) run(&grad_xpass_kernel<N, F, true>);
-  else run(&grad_xpass_kernel<N, F, false>);
+  if (G) run(&grad_xpass_kernel<N, F, true, VAR>);
+  else run(&grad_xpass_kernel<N, F, false, VAR>);
   *nb = grid;
 }
 
@@ -153,7 +153,13 @@ hipError_t grad_xpass(const LapAxis& ax, size_t npts, const void* X, const doubl
                       const PwParams& p, bool point, double* part, size_t stride, int* nb, hipStream_t st) {
   switch (ax.n) {
 #define GPE_CASE(NN) \
-  case NN: launch_gx<NN, F>(ax, npts, X, V, G, xc, xc32, p, point, part, stride, nb, st); break;
+  case NN:                                                                                        \
+    if (NN >= 64 && NN <= 256 && npts < kLatencyPoints)                                           \
+      launch_gx<NN, F, (NN >= 64 && NN <= 256 ? XVAR_LATENCY : 1)>(ax, npts, X, V, G, xc, xc32, p, point, part, \
+                                                                  stride, nb, st);                 \
+    else                                                                                          \
+      launch_gx<NN, F, 1>(ax, npts, X, V, G, xc, xc32, p, point, part, stride, nb, st);           \
+    break;
     GPE_SIZES(GPE_CASE)
 #undef GPE_CASE
     default: return hipErrorInvalidValue;

@@ -212,7 +212,7 @@ static gpe_status hvp_t(gpe_handle* h, const void* Z, void* HZ, bool riem, const
   for (int q = 0; q < kMaxQ; ++q) nb.nb[q] = 0;
   int nbx = 0;
   GPE_KT(h, KK_HVP_XPASS,
-         hvp_xpass<T>(h->F, h->ax[0], h->npts, Xw, Z, Yw, Vw, HZ, p, h->part, h->pstride, &nbx, h->xvar, skip, h->st));
+         hvp_xpass<T>(h->F, h->ax[0], h->npts, Xw, Z, riem ? Yw : nullptr, Vw, HZ, p, h->part, h->pstride, &nbx, h->xvar, skip, h->st));
   for (int q = 0; q < 7; ++q) nb.nb[q] = nbx;
   double* coef = h->res + 32;
   // Projection coefficients (Lemma 4.1) from the x pass's partials: with few
@@ -259,10 +259,10 @@ static gpe_status tune_xpass_t(gpe_handle* h) {
   const int nv = xpass_variants(h->n[0]);
   if (nv <= 1 || h->npts < (1u << 15)) return GPE_OK;
   // Below 2^18 points a pass takes 10 us or so, which events around a launch (+- 5
-  // us) cannot rank; the smallest workgroups, the most of them, are the fastest
-  // there (spin-2 256^2, rocprof: 12.3, 12.2 and 15.0 us for variants 0, 1, 2).
-  if (h->npts < (1u << 18)) {
-    h->xvar = 0;
+  // us) cannot rank; the latency variant is the fastest there (spin-2
+  // 256^2, variants 0, 1, 2: 11.3, 11.0, 10.0 us in c128, 8.9, 9.2, 8.0 in c64).
+  if (h->npts < kLatencyPoints) {
+    h->xvar = 2;
     return GPE_OK;
   }
   // three distinct fields for X, Z, LX (aliasing them would hide memory traffic)

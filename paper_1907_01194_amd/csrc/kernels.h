@@ -51,6 +51,11 @@ struct AbSrc {
 // projection coefficients itself.
 constexpr int kAbLocalMax = 1024;
 
+// Grids below this many points take one x-row per workgroup and one point per
+// thread in the fused x passes (256^2, 2^16 points: 11.3 -> 10.0 us; from 2^18 on
+// every CU has several rows and the denser variants are timed instead).
+constexpr size_t kLatencyPoints = (size_t)1 << 18;
+
 // Physical constants of the pointwise terms, already combined with h:
 // zee[l] = b_l (storage order), c0 = 2 beta0 / h, ... (gradient factors)
 // and e0 = beta0 / (2h), ... (energy factors).
@@ -78,7 +83,7 @@ hipError_t grad_axis(const LapAxis& ax, bool sum_only, const void* in, const voi
 //   W = L_x Z + (pointwise Hessian terms of Sec. 3) + p.zc[i] Z_i,
 // with FP64 partial sums (one per workgroup, slots of stride `stride`):
 //   [0] sum_i <X_i, W_i>  [1] sum_i l_i <X_i, W_i>  (both through <(LX)_i, Z_i> = <X_i, (LZ)_i>,
-//   Y = L X), [2] sum <X_i,Z_i>, [3] sum l_i <X_i,Z_i>, [4] <Z, W - LZ>, [5] ||Z||^2,
+//   Y = L X; only their pointwise part with Y null, for a Euclidean product), [2] sum <X_i,Z_i>, [3] sum l_i <X_i,Z_i>, [4] <Z, W - LZ>, [5] ||Z||^2,
 //   [6] <Z, L_x Z> (Parseval).
 // Returns the number of workgroups (partials per slot) in *nblk_out.
 // var: schedule variant (rows per workgroup), 0 .. xpass_variants(n)-1; 1 is the default.

@@ -116,7 +116,8 @@ static void launch_xpass(const LapAxis& ax, size_t npts, const void* X, const vo
   *nb = grid;
 }
 
-// the line lengths that get all three schedule variants (the others use the default)
+// the line lengths that get all three schedule variants (the others use the default):
+// one or two wavefronts of rows, or the latency variant
 static constexpr bool tuned_size(int n) { return n == 64 || n == 96 || n == 128 || n == 256; }
 
 template <typename T, int N, int F>
@@ -125,7 +126,7 @@ static void launch_xpass_var(int var, const LapAxis& ax, size_t npts, const void
                              const double* skip, hipStream_t st) {
   if constexpr (tuned_size(N)) {
     if (var == 0) return launch_xpass<T, N, F, 0>(ax, npts, X, Z, Y, V, W, p, part, stride, nb, skip, st);
-    if (var == 2) return launch_xpass<T, N, F, 2>(ax, npts, X, Z, Y, V, W, p, part, stride, nb, skip, st);
+    if (var == 2) return launch_xpass<T, N, F, XVAR_LATENCY>(ax, npts, X, Z, Y, V, W, p, part, stride, nb, skip, st);
   }
   launch_xpass<T, N, F, 1>(ax, npts, X, Z, Y, V, W, p, part, stride, nb, skip, st);
 }
