@@ -103,10 +103,10 @@ template <int NQ> __device__ __forceinline__ void wave_sums(double (&v)[pow2_cei
 }
 
 // Block-reduce NQ per-thread doubles (any blockDim.x <= 1024, a multiple of the
-// wave size) and write the block's sums to part[q * stride + blk].
-template <int NQ>
-__device__ inline void block_partials_any(const double (&acc)[NQ], double* __restrict__ part, size_t stride,
-                                          size_t blk) {
+// wave size): thread q calls sink(q, sum q) for q < NQ.  block_partials_any: the
+// sums go to part[q * stride + blk].
+template <int NQ, typename Sink>
+__device__ inline void block_sums(const double (&acc)[NQ], Sink&& sink) {
   constexpr int P = pow2_ceil<NQ>();
   __shared__ double red[1024 / kWave][P];
   const int lane = threadIdx.x % kWave;
@@ -121,8 +121,13 @@ __device__ inline void block_partials_any(const double (&acc)[NQ], double* __res
   if (threadIdx.x < NQ) {
     double s = 0.0;
     for (int w = 0; w < nw; ++w) s += red[w][threadIdx.x];
-    part[(size_t)threadIdx.x * stride + blk] = s;
+    sink((int)threadIdx.x, s);
   }
+}
+template <int NQ>
+__device__ inline void block_partials_any(const double (&acc)[NQ], double* __restrict__ part, size_t stride,
+                                          size_t blk) {
+  block_sums(acc, [&](int q, double s) { part[(size_t)q * stride + blk] = s; });
 }
 
 // Workgroups of a reduction over npts grid points: four points per thread, but

@@ -19,6 +19,7 @@
 #pragma once
 
 #include "common.h"
+#include "finalize.h"
 #include "kernels.h"
 #include "spin.h"
 
@@ -620,12 +621,23 @@ template <int N, int K, int VAR = 1> struct XGeo {
   template <typename T> static constexpr size_t lds_elems() { return (size_t)lstr<T>() * (1 + LINES); }
 };
 
-template <typename T, int N, int F, int VAR>
+// A whole product in one workgroup (1D grids: one row is the grid): the sums, the
+// projection and the post-operations happen where W is still in registers and LDS.
+struct OneArgs {
+  double* gram = nullptr;     // component norms of the set point
+  double* res = nullptr;
+  double* mirror = nullptr;   // see finalize
+  int post = POST_NONE;       // after the projection's Gram solve
+  bool proj = false;
+};
+
+template <typename T, int N, int F, int VAR, bool ONE = false>
 __device__ __forceinline__ void xpass_body(const c_t<T>* __restrict__ X, const c_t<T>* __restrict__ Z,
                                            const c_t<T>* __restrict__ Y, const T* __restrict__ V,
                                            c_t<T>* __restrict__ W, const c_t<T>* __restrict__ twg, long nrows,
                                            size_t npts, T lamc, const PwParams& p, double* __restrict__ part,
-                                           size_t stride, long blk, const double* skip) {
+                                           size_t stride, long blk, const double* skip,
+                                           const OneArgs& one = OneArgs{}) {
   if (skip && *skip != 0.0) return;   // uniform over the workgroup
   using T2 = c_t<T>;
   constexpr int K = 2 * F + 1;
@@ -727,18 +739,41 @@ __device__ __forceinline__ void xpass_body(const c_t<T>* __restrict__ X, const c
   }
   __syncthreads();
 
-  // ---- W = L_x Z + q
+  // ---- ONE: sums, Gram solve and post-operations in this workgroup
+  __shared__ double sum[ONE ? 8 : 1], state[ONE ? 64 : 1];
+  if constexpr (ONE) {
+    if (t < 64) state[t] = one.res[t];
+    block_sums(acc, [&](int k, double s) { sum[k] = s; });
+    __syncthreads();
+    if (t == 0) {
+      if (one.proj) finalize_post(sum, 7, state, one.res, POST_HVP_AB, F, nullptr, one.gram);
+      if (one.post != POST_NONE) finalize_post(sum, 7, state, one.res, one.post, F, nullptr, one.gram);
+    }
+    __syncthreads();
+    if (one.mirror && t < 64) one.mirror[t] = state[t];
+  }
+
+  // ---- W = L_x Z + q [- (alpha_w + beta_w l) X]
 #pragma unroll
   for (int pp = 0; pp < PPT; ++pp) {
     const unsigned pt = t + pp * G::THREADS;
     if (t < G::THREADS && pt < np) {
 #pragma unroll
-      for (int i = 0; i < K; ++i)
-        at(W + r0 + i * npts, pt * (unsigned)sizeof(T2)) =
-            cadd(lds[(i * RPB + pt / N) * LSTR + lpad<T>(pt % N)], q[pp][i]);
+      for (int i = 0; i < K; ++i) {
+        T2 w = cadd(lds[(i * RPB + pt / N) * LSTR + lpad<T>(pt % N)], q[pp][i]);
+        if constexpr (ONE) {
+          if (one.proj) {
+            const T c = (T)(state[32] + state[33] * (double)(F - i));
+            const T2 xv = at(X + r0 + i * npts, pt * (unsigned)sizeof(T2));
+            w.x -= c * xv.x;
+            w.y -= c * xv.y;
+          }
+        }
+        at(W + r0 + i * npts, pt * (unsigned)sizeof(T2)) = w;
+      }
     }
   }
-  block_partials_any<7>(acc, part, stride, blk);
+  if constexpr (!ONE) block_partials_any<7>(acc, part, stride, blk);
 }
 
 }  // namespace gpe

@@ -96,6 +96,16 @@ static gpe_status grad_enq(gpe_handle* h, const void* X, void* G, double* gram, 
   const bool riem = kind == GRAD_RIEM, point = kind == GRAD_POINT;
   const bool mixed_point = point && h->prec == GPE_MIXED;
   norm = norm || riem;
+  if (h->dim == 1) {   // one row: one workgroup does it all
+    auto one = [&](auto f) {
+      return grad_one<f()>(h->ax[0], X, h->V64, G, point ? h->Xp : nullptr, mixed_point ? h->Xp32 : nullptr, h->pw,
+                           point, riem, norm, G ? gram : nullptr, h->res, h->hres, h->st);
+    };
+    GPE_KT(h, KK_PW_GRAD,
+           h->F == 1 ? one(std::integral_constant<int, 1>{}) : h->F == 2 ? one(std::integral_constant<int, 2>{})
+                                                                         : one(std::integral_constant<int, 3>{}));
+    return GPE_OK;
+  }
   int nbx = 0, tpc[3] = {0, 0, 0};
   auto gx = [&](auto f) {
     return grad_xpass<f()>(h->ax[0], h->npts, X, h->V64, G, point ? h->Xp : nullptr, mixed_point ? h->Xp32 : nullptr,
@@ -124,26 +134,14 @@ static gpe_status grad_enq(gpe_handle* h, const void* X, void* G, double* gram, 
          finalize_segs(h->part, s, h->part + (kMaxQ - 1) * ps, h->res, G ? POST_GRAD : POST_ENERGY, h->F,
                        G ? gram : nullptr, h->ticket, norm ? nullptr : h->hres, h->st));
   if (!norm) return GPE_OK;
-  const double* coef = h->res + 1 + 2 * K;
+  if (riem)
+    GPE_KT(h, KK_LAP_X + last,
+           grad_axis(h->ax[last], false, X, G, G, nullptr, h->F, h->npts, X, h->res + 1 + 2 * K, h->part, ps,
+                     first + last - 1, &tpc[last], h->st));
   SlotSegs sn;
   sn.nq = 1;
-  if (h->dim > 1) {
-    if (riem)
-      GPE_KT(h, KK_LAP_X + last,
-             grad_axis(h->ax[last], false, X, G, G, nullptr, h->F, h->npts, X, coef, h->part, ps, first + last - 1,
-                       &tpc[last], h->st));
-    sn.off[0] = (int)((first + last) * ps);   // the slot after the last axis' sums
-    sn.nb[0] = K * tpc[last];
-  } else {
-    if (riem)
-      GPE_KT(h, KK_PROJECT,
-             launch_single(ProjArgs<double, double, true>{X, G, G, coef, 0.0, 0.0, h->part, h->npts, h->F}, h->nblk,
-                           h->st));
-    else
-      GPE_KT(h, KK_VECTOR, (dot<double, double>(G, G, h->part, h->nblk, h->nel, h->st)));
-    sn.off[0] = 0;
-    sn.nb[0] = h->nblk;
-  }
+  sn.off[0] = (int)((first + last) * ps);   // the slot after the last axis' sums
+  sn.nb[0] = K * tpc[last];
   GPE_KT(h, KK_FINALIZE,
          finalize_segs(h->part, sn, h->res + kResNorm, h->res, POST_NONE, h->F, nullptr, h->ticket, h->hres, h->st));
   return GPE_OK;
@@ -208,6 +206,13 @@ static gpe_status hvp_t(gpe_handle* h, const void* Z, void* HZ, bool riem, const
   const void* Yw = sizeof(T) == 8 ? h->LX64 : h->LX32;
   const T* Vw = reinterpret_cast<const T*>(sizeof(T) == 8 ? (const void*)h->V64 : (const void*)h->V32);
   const double* skip = cg ? h->res + CG_DONE : nullptr;
+  const int post = cg ? POST_CG_KAPPA : !kappa ? POST_NONE : riem ? POST_HVP_KAPPA : POST_HVP_KAPPA_E;
+  if (h->dim == 1) {   // one row: one workgroup does it all
+    GPE_KT(h, KK_HVP_XPASS,
+           hvp_one<T>(h->F, h->ax[0], Xw, Z, riem ? Yw : nullptr, Vw, HZ, p, h->gram_pt, h->res,
+                      kappa && !cg ? h->hres : nullptr, post, riem, skip, h->st));
+    return GPE_OK;
+  }
   SlotCounts nb;
   for (int q = 0; q < kMaxQ; ++q) nb.nb[q] = 0;
   int nbx = 0;
@@ -218,33 +223,24 @@ static gpe_status hvp_t(gpe_handle* h, const void* Z, void* HZ, bool riem, const
   // Projection coefficients (Lemma 4.1) from the x pass's partials: with few
   // x-pass workgroups every workgroup of the last axis pass forms them itself;
   // in 3D otherwise one extra workgroup of the y pass does; else a finalize.
-  const bool ab_local = riem && h->dim >= 2 && nbx <= kAbLocalMax;
+  const bool ab_local = riem && nbx <= kAbLocalMax;
   const bool ab_ypass = riem && !ab_local && h->dim == 3;
   if (riem && !ab_local && !ab_ypass)
     GPE_KT(h, KK_FINALIZE,
            finalize(h->part, h->pstride, nb, 7, h->res, POST_HVP_AB, h->F, h->gram_pt, h->ticket, skip, nullptr,
                     h->st));
   int nq = 7;
-  if (h->dim == 1) {
-    // (after a CG stop this projection still runs, on an HZ that nothing reads any more)
-    if (riem)
-      GPE_KT(h, KK_PROJECT,
-             launch_single(ProjArgs<T, T, false>{Xw, HZ, HZ, coef, 0.0, 0.0, nullptr, h->npts, h->F}, h->nblk, h->st));
-  } else {
-    for (int a = 1; a < h->dim; ++a) {
-      const bool proj = riem && a == h->dim - 1;
-      AbSrc ab, fin;
-      if (proj && ab_local) ab = AbSrc{h->part, h->pstride, nbx, h->gram_pt, h->res};
-      if (a == 1 && ab_ypass) fin = AbSrc{h->part, h->pstride, nbx, h->gram_pt, h->res};
-      GPE_KT(h, KK_LAP_X + a,
-             lap_axis_ex<T>(h->ax[a], Z, HZ, HZ, h->F, h->npts, proj ? Xw : nullptr, coef, h->part, h->pstride,
-                            6 + a, &nb.nb[6 + a], skip, a == 1, ab.part ? &ab : nullptr, fin.part ? &fin : nullptr,
-                            h->st));
-      nq = 7 + a;
-    }
+  for (int a = 1; a < h->dim; ++a) {
+    const bool proj = riem && a == h->dim - 1;
+    AbSrc ab, fin;
+    if (proj && ab_local) ab = AbSrc{h->part, h->pstride, nbx, h->gram_pt, h->res};
+    if (a == 1 && ab_ypass) fin = AbSrc{h->part, h->pstride, nbx, h->gram_pt, h->res};
+    GPE_KT(h, KK_LAP_X + a,
+           lap_axis_ex<T>(h->ax[a], Z, HZ, HZ, h->F, h->npts, proj ? Xw : nullptr, coef, h->part, h->pstride, 6 + a,
+                          &nb.nb[6 + a], skip, a == 1, ab.part ? &ab : nullptr, fin.part ? &fin : nullptr, h->st));
+    nq = 7 + a;
   }
-  if (!cg && !kappa) return GPE_OK;
-  const int post = cg ? POST_CG_KAPPA : riem ? POST_HVP_KAPPA : POST_HVP_KAPPA_E;
+  if (post == POST_NONE) return GPE_OK;
   GPE_KT(h, KK_FINALIZE, finalize(h->part, h->pstride, nb, nq, h->res, post, h->F, h->gram_pt, h->ticket, skip,
                                   cg ? nullptr : h->hres, h->st));
   return GPE_OK;

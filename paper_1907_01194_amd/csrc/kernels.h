@@ -66,11 +66,19 @@ struct PwParams {
   double zc[7];  // HVP only: extra multiple of Z_i added to W_i
 };
 
+constexpr int kResNorm = 28;   // res slot of ||G||^2 of a gradient call
+
 // Fused x pass of the energy / gradient (FP64, grad_x.h).  G null: the energy
 // only.  Partial sums in slots 0 .. 2K (0 only for the energy), *nb per slot.
 template <int F>
 hipError_t grad_xpass(const LapAxis& ax, size_t npts, const void* X, const double* V, void* G, void* xc, void* xc32,
                       const PwParams& p, bool point, double* part, size_t stride, int* nb, hipStream_t st);
+// The same for a 1D grid, whole in one workgroup: res as POST_GRAD or POST_ENERGY
+// leaves it, proj: G projected, norm: ||G||^2 in res[kResNorm].
+template <int F>
+hipError_t grad_one(const LapAxis& ax, const void* X, const double* V, void* G, void* xc, void* xc32,
+                    const PwParams& p, bool point, bool proj, bool norm, double* gram, double* res, double* mirror,
+                    hipStream_t st);
 // Strided axis pass of the energy / gradient (FP64): sum_only forms the Parseval
 // sums <X_i, L_a X_i> alone (slot), else out = acc + L_a in [- projection] with
 // the sums in slot and ||out||^2 in slot + 1, written as c64 to out32 if given.
@@ -94,6 +102,13 @@ hipError_t hvp_xpass(int F, const LapAxis& ax, size_t npts, const void* X, const
                      const T* V, void* W, const PwParams& p, double* part, size_t stride, int* nblk_out, int var,
                      const double* skip, hipStream_t st);
 int xpass_variants(int n);
+
+// The whole product of a 1D grid in one workgroup: W, with the projection (proj;
+// coefficients to res[32..33] from gram), then the post-operation on the sums.
+template <typename T>
+hipError_t hvp_one(int F, const LapAxis& ax, const void* X, const void* Z, const void* Y, const T* V, void* W,
+                   const PwParams& p, double* gram, double* res, double* mirror, int post, bool proj,
+                   const double* skip, hipStream_t st);
 
 // Axis pass with Parseval partial <Z, L_a Z> into part[slot * stride + wg] and,
 // if coef != null, the projection epilogue out -= (coef[0] + coef[1] l) X

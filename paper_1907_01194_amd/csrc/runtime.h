@@ -72,7 +72,6 @@ struct gpe_handle {
 namespace gpe {
 
 constexpr int kResDoubles = 64;   // reduction results per handle (res, hres)
-constexpr int kResNorm = 28;      // slot of ||G||^2 of a gradient call
 
 // Status helpers: record a message on the handle and return the status.
 gpe_status fail(gpe_handle* h, gpe_status s, const std::string& msg);
