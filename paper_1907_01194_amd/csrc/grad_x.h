@@ -8,7 +8,7 @@
 // q at once and the other axes accumulate into it (8 fields), and every kinetic
 // sum <X_i, L_a X_i> comes from Parseval inside its pass, so an energy needs the
 // forward transforms only and writes nothing (3 fields).  Bound by HBM on large
-// grids (spin-2 96^3: 52 us for 2 fields and V with the gradient's sums, 24 us for
+// grids (spin-2 96^3: 46 us for 2 fields and V with the gradient's sums, 22 us for
 // the energy's one) and by latency on small ones (256^2: 12 us).  Measured, with
 // the results stored in pinned memory by the finalize instead of a copy:
 //   energy, spin-1 512^2 (4 launches -> 3) 56.5 -> 31.2 us;
@@ -59,16 +59,34 @@ grad_xpass_kernel(const double2* __restrict__ X, const double* __restrict__ V, d
   const unsigned np = (unsigned)(nrows - row0 < RPB ? nrows - row0 : RPB) * N;
 
   // ---- pointwise terms of this thread's points; the rows of X go to LDS
-  T2 q[GRAD ? PPT : 1][K];
+  // Where a workgroup has several rows, all of a thread's points are fetched before
+  // the first is used: LDS and registers hold the CU to 2-4 wavefronts per SIMD, too
+  // few to cover one point's loads at a time (spin-1 256 x 256 x 64: gradient 125.5 ->
+  // 115 us, energy 51.7 -> 48.4).  One row a workgroup is faster point by point (512^2:
+  // 15.5 us against 16.6).
+  constexpr bool AHEAD = RPB > 1;
+  T2 xs[AHEAD ? PPT : 1][K], q[GRAD ? PPT : 1][K];
+  T vs[AHEAD ? PPT : 1];
+  auto fetch = [&](int pp, T2(&x)[K], T& vj) {
+    const unsigned pt = t + pp * GG::THREADS;
+    if (pt < np) {
+#pragma unroll
+      for (int i = 0; i < K; ++i) x[i] = at(X + r0 + i * npts, pt * (unsigned)sizeof(T2));
+      vj = at(V + r0, pt * (unsigned)sizeof(T));
+    }
+  };
+  if constexpr (AHEAD) {
+#pragma unroll
+    for (int pp = 0; pp < PPT; ++pp) fetch(pp, xs[pp], vs[pp]);
+  }
 #pragma unroll
   for (int pp = 0; pp < PPT; ++pp) {
     const unsigned pt = t + pp * GG::THREADS;
     if (pt < np) {
       const unsigned ob = pt * (unsigned)sizeof(T2);
-      T2 x[K];
-#pragma unroll
-      for (int i = 0; i < K; ++i) x[i] = at(X + r0 + i * npts, ob);
-      const T vj = at(V + r0, pt * (unsigned)sizeof(T));
+      if constexpr (!AHEAD) fetch(pp, xs[0], vs[0]);
+      const T2(&x)[K] = xs[AHEAD ? pp : 0];
+      const T vj = vs[AHEAD ? pp : 0];
 #pragma unroll
       for (int i = 0; i < K; ++i) {
         lds[(i * RPB + pt / N) * LSTR + lpad<T>(pt % N)] = x[i];
@@ -189,6 +207,9 @@ static void launch_gx(const LapAxis& ax, size_t npts, const void* X, const doubl
   *nb = grid;
 }
 
+// 256 threads' rows a workgroup from kLatencyPoints on, against 128: gradient and
+// energy of spin-2 96^3 46.7, 24.0 -> 46.4, 22.8 us, of spin-1 256 x 256 x 64 126.6,
+// 58.5 -> 125.5, 51.7 (fewer partial sums, and one twiddle table for twice the rows).
 template <int F>
 hipError_t grad_xpass(const LapAxis& ax, size_t npts, const void* X, const double* V, void* G, void* xc, void* xc32,
                       const PwParams& p, bool point, double* part, size_t stride, int* nb, hipStream_t st) {
@@ -196,10 +217,10 @@ hipError_t grad_xpass(const LapAxis& ax, size_t npts, const void* X, const doubl
 #define GPE_CASE(NN) \
   case NN:                                                                                        \
     if (NN >= 64 && NN <= 256 && npts < kLatencyPoints)                                           \
-      launch_gx<NN, F, (NN >= 64 && NN <= 256 ? XVAR_LATENCY : 1)>(ax, npts, X, V, G, xc, xc32, p, point, part, \
+      launch_gx<NN, F, (NN >= 64 && NN <= 256 ? XVAR_LATENCY : 2)>(ax, npts, X, V, G, xc, xc32, p, point, part, \
                                                                   stride, nb, st);                 \
     else                                                                                          \
-      launch_gx<NN, F, 1>(ax, npts, X, V, G, xc, xc32, p, point, part, stride, nb, st);           \
+      launch_gx<NN, F, 2>(ax, npts, X, V, G, xc, xc32, p, point, part, stride, nb, st);           \
     break;
     GPE_SIZES(GPE_CASE)
 #undef GPE_CASE

@@ -68,6 +68,30 @@ def test_energy_and_gradients_every_line_length(n):
         gp.close()
 
 
+@pytest.mark.parametrize("F,grid", [(1, (256, 32, 32)), (2, (96, 64, 48)), (3, (64, 64, 64)), (1, (512, 512)),
+                                    (2, (192, 32, 48))])
+def test_gradient_dense_rows(F, grid):
+    """Grids from 2^18 points on, several x rows a workgroup and a last one that
+    is only partly filled (256: 5 rows of 1024; 512: one row): energy and
+    Riemannian gradient against the oracle at the tolerances above."""
+    import torch
+    from paper_1907_01194_amd.binding import Problem
+    from gpu_util import dev, host, assert_field
+    print("dense rows", F, grid, flush=True)
+    spec = small_spec(F, grid, p=0.1, q=0.05)
+    prob = oracle_problem(spec)
+    u = oracle.retraction.psi(prob, W.noisy_envelope_state(spec, 3, (0.2,) * len(grid)), 1)
+    ref, E_or = oracle.rgrad(prob, u)[0], oracle.energy(prob, u)
+    gp = Problem(spec, "fp64")
+    X = dev(u)
+    assert abs(gp.energy(X) - E_or) <= 1e-10 * abs(E_or)
+    G, E, gn = gp.grad(X, riemannian=True)
+    assert abs(E - E_or) <= 1e-10 * abs(E_or)
+    assert_field(host(G), ref, 1e-11, "gradient")
+    assert abs(gn - np.linalg.norm(ref)) <= 1e-11 * gn
+    gp.close()
+
+
 @pytest.mark.parametrize("n", [s for s in SIZES if 2 * s in SIZES])
 def test_prolong_every_line_length(n):
     """Fourier prolongation of every coarse length, as a contiguous and as a
