@@ -11,9 +11,9 @@
 // grids (spin-2 96^3: 46 us for 2 fields and V with the gradient's sums, 22 us for
 // the energy's one) and by latency on small ones (256^2: 12 us).  Measured, with
 // the results stored in pinned memory by the finalize instead of a copy:
-//   energy, spin-1 512^2 (4 launches -> 3) 56.5 -> 31.2 us;
-//   Riemannian gradient, spin-2 256^2 (7 launches, 2 synchronisations -> 5, 1) 75.9 -> 48.0 us;
-//   energy, gradient, set point and product, spin-2 96^3 (autograd) 984 -> 636 us.
+//   energy, spin-1 512^2 (4 launches -> 2) 56.5 -> 28.6 us;
+//   Riemannian gradient, spin-2 256^2 (7 launches, 2 synchronisations -> 4, 1) 75.9 -> 39.9 us;
+//   energy, gradient, set point and product, spin-2 96^3 (autograd) 984 -> 620 us.
 #include "fft.h"
 
 namespace gpe {
@@ -31,12 +31,31 @@ struct GradOne {
   bool proj = false, norm = false;
 };
 
-template <int N, int F, bool GRAD, int VAR, bool ONE = false>
-__global__ void __launch_bounds__((XGeo<N, 2 * F + 1, VAR>::THREADS), 2)
+// SUMS: the workgroups from nbx on take the tiles of the strided axes' Parseval
+// sums.  They read X alone, like the x pass, and a launch of their own waits for
+// it for nothing: on small grids one latency instead of two or three (spin-1 48^3,
+// energy 26.5 -> 20.8 us; 512^2 31.2 -> 28.6), on large ones their transforms fill
+// the x pass' waits (spin-2 96^3, energy 69.9 -> 56.3, Riemannian gradient 151 ->
+// 144).  Axes of the x axis' length only (one kernel per length, not per pair).
+template <int N, int F, int VAR> constexpr int sums_threads() {
+  constexpr int a = XGeo<N, 2 * F + 1, VAR>::THREADS, b = AxGeo<double, N, false>::THREADS;
+  return a > b ? a : b;
+}
+template <int N, int F, bool GRAD, int VAR, bool ONE = false, bool SUMS = false>
+__global__ void __launch_bounds__((SUMS ? sums_threads<N, F, VAR>() : XGeo<N, 2 * F + 1, VAR>::THREADS), 2)
 grad_xpass_kernel(const double2* __restrict__ X, const double* __restrict__ V, double2* __restrict__ G,
                   double2* __restrict__ xc, float2* __restrict__ xc32, const double2* __restrict__ twg, long nrows,
                   size_t npts, double lamc, PwParams p, bool point, double* __restrict__ part, size_t stride,
-                  GradOne one) {
+                  GradOne one, SumAxes sums, int nbx) {
+  if constexpr (SUMS) {
+    if ((int)blockIdx.x >= nbx) {   // uniform over the workgroup
+      const int tiles = (2 * F + 1) * sums.tpc, b = (int)blockIdx.x - nbx, k = b < tiles ? 0 : 1;
+      lap_body<double, N, false, 1, LAP_SUM>(X, nullptr, nullptr, twg, sums.inner[k], sums.lamc[k], F, npts, nullptr,
+                                             nullptr, part, stride, sums.slot[k], (long)(b - k * tiles), nullptr,
+                                             AbSrc{});
+      return;
+    }
+  }
   using T = double;
   using T2 = double2;
   constexpr int K = 2 * F + 1;
@@ -56,7 +75,7 @@ grad_xpass_kernel(const double2* __restrict__ X, const double* __restrict__ V, d
   for (int i = 0; i < NQ; ++i) acc[i] = 0.0;
   const long row0 = (long)blockIdx.x * RPB;
   const size_t r0 = (size_t)row0 * N;
-  const unsigned np = (unsigned)(nrows - row0 < RPB ? nrows - row0 : RPB) * N;
+  const unsigned np = SUMS && t >= GG::THREADS ? 0 : (unsigned)(nrows - row0 < RPB ? nrows - row0 : RPB) * N;
 
   // ---- pointwise terms of this thread's points; the rows of X go to LDS
   // Where a workgroup has several rows, all of a thread's points are fetched before
@@ -186,44 +205,59 @@ grad_xpass_kernel(const double2* __restrict__ X, const double* __restrict__ V, d
   }
 }
 
-template <int N, int F, int VAR>
+template <int N, int F, int VAR, bool RIDE>
 static void launch_gx(const LapAxis& ax, size_t npts, const void* X, const double* V, void* G, void* xc, void* xc32,
-                      const PwParams& p, bool point, double* part, size_t stride, int* nb, hipStream_t st) {
+                      const PwParams& p, bool point, double* part, size_t stride, int* nb, SumAxes* sums, hipStream_t st) {
   using GG = XGeo<N, 2 * F + 1, VAR>;
+  using AG = AxGeo<double, N, false>;
   const long nrows = (long)(npts / N);
   const int grid = (int)((nrows + GG::RPB - 1) / GG::RPB);
-  const size_t lds = sizeof(double2) * GG::template lds_elems<double>();
+  const int tiles = RIDE ? (int)ax_tiles<double, N, false>(2 * F + 1, npts) : 0;
+  sums->tpc = tiles / (2 * F + 1);
+  size_t elems = GG::template lds_elems<double>();
+  if (RIDE && elems < (size_t)padded_len<double>(N) + AG::TILE) elems = (size_t)padded_len<double>(N) + AG::TILE;
+  const size_t lds = sizeof(double2) * elems;
   auto run = [&](auto* kernel) {
     if (lds > 65536)
       (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)lds);
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(GG::THREADS), lds, st, reinterpret_cast<const double2*>(X), V,
+    hipLaunchKernelGGL(kernel, dim3(grid + sums->n * tiles), dim3(RIDE ? sums_threads<N, F, VAR>() : GG::THREADS),
+                       lds, st, reinterpret_cast<const double2*>(X), V,
                        reinterpret_cast<double2*>(G), reinterpret_cast<double2*>(xc), reinterpret_cast<float2*>(xc32),
                        reinterpret_cast<const double2*>(ax.tw64), nrows, npts, ax.lamc, p, point, part, stride,
-                       GradOne{});
+                       GradOne{}, *sums, grid);
   };
-  if (G) run(&grad_xpass_kernel<N, F, true, VAR>);
-  else run(&grad_xpass_kernel<N, F, false, VAR>);
+  if (G) run(&grad_xpass_kernel<N, F, true, VAR, false, RIDE>);
+  else run(&grad_xpass_kernel<N, F, false, VAR, false, RIDE>);
   *nb = grid;
 }
 
-// 256 threads' rows a workgroup from kLatencyPoints on, against 128: gradient and
+// From kLatencyPoints on 256 threads' rows a workgroup, against 128: gradient and
 // energy of spin-2 96^3 46.7, 24.0 -> 46.4, 22.8 us, of spin-1 256 x 256 x 64 126.6,
 // 58.5 -> 125.5, 51.7 (fewer partial sums, and one twiddle table for twice the rows).
+// With other axes' sums in the launch 128, the threads of most of their tiles (the
+// rest of a workgroup would idle): energy of spin-2 96^3 72.6 -> 56.3 us, of spin-3
+// 128^3 172 -> 140 (in launches of their own 69.9 and 154.5).
 template <int F>
 hipError_t grad_xpass(const LapAxis& ax, size_t npts, const void* X, const double* V, void* G, void* xc, void* xc32,
-                      const PwParams& p, bool point, double* part, size_t stride, int* nb, hipStream_t st) {
+                      const PwParams& p, bool point, double* part, size_t stride, int* nb, SumAxes* sums,
+                      hipStream_t st) {
   switch (ax.n) {
-#define GPE_CASE(NN) \
-  case NN:                                                                                        \
-    if (NN >= 64 && NN <= 256 && npts < kLatencyPoints)                                           \
-      launch_gx<NN, F, (NN >= 64 && NN <= 256 ? XVAR_LATENCY : 2)>(ax, npts, X, V, G, xc, xc32, p, point, part, \
-                                                                  stride, nb, st);                 \
-    else                                                                                          \
-      launch_gx<NN, F, 2>(ax, npts, X, V, G, xc, xc32, p, point, part, stride, nb, st);           \
-    break;
+#define GPE_GX(NN, VAR, RIDE) \
+  launch_gx<NN, F, VAR, RIDE>(ax, npts, X, V, G, xc, xc32, p, point, part, stride, nb, sums, st)
+#define GPE_CASE(NN)                                               \
+  case NN: {                                                       \
+    constexpr bool mid = NN >= 64 && NN <= 256;                    \
+    const bool small = mid && npts < kLatencyPoints;               \
+    if (small && sums->n) GPE_GX(NN, (mid ? XVAR_LATENCY : 1), true);   \
+    else if (small) GPE_GX(NN, (mid ? XVAR_LATENCY : 2), false);   \
+    else if (sums->n) GPE_GX(NN, 1, true);                         \
+    else GPE_GX(NN, 2, false);                                     \
+    break;                                                         \
+  }
     GPE_SIZES(GPE_CASE)
 #undef GPE_CASE
+#undef GPE_GX
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -239,7 +273,8 @@ static void launch_one(const LapAxis& ax, const void* X, const double* V, void* 
                                 (int)lds);
     hipLaunchKernelGGL(kernel, dim3(1), dim3(GG::THREADS), lds, st, reinterpret_cast<const double2*>(X), V,
                        reinterpret_cast<double2*>(G), reinterpret_cast<double2*>(xc), reinterpret_cast<float2*>(xc32),
-                       reinterpret_cast<const double2*>(ax.tw64), 1, (size_t)N, ax.lamc, p, point, nullptr, 0, one);
+                       reinterpret_cast<const double2*>(ax.tw64), 1, (size_t)N, ax.lamc, p, point, nullptr, 0, one,
+                       SumAxes{}, 1);
   };
   if (G) run(&grad_xpass_kernel<N, F, true, XVAR_LATENCY, true>);
   else run(&grad_xpass_kernel<N, F, false, XVAR_LATENCY, true>);
@@ -262,6 +297,6 @@ hipError_t grad_one(const LapAxis& ax, const void* X, const double* V, void* G, 
 template hipError_t grad_one<GPE_GRAD_F>(const LapAxis&, const void*, const double*, void*, void*, void*,
                                          const PwParams&, bool, bool, bool, double*, double*, double*, hipStream_t);
 template hipError_t grad_xpass<GPE_GRAD_F>(const LapAxis&, size_t, const void*, const double*, void*, void*, void*,
-                                           const PwParams&, bool, double*, size_t, int*, hipStream_t);
+                                           const PwParams&, bool, double*, size_t, int*, SumAxes*, hipStream_t);
 
 }  // namespace gpe

@@ -107,18 +107,35 @@ static gpe_status grad_enq(gpe_handle* h, const void* X, void* G, double* gram, 
     return GPE_OK;
   }
   int nbx = 0, tpc[3] = {0, 0, 0};
+  const int first = G ? 1 + 2 * K : 1;   // slot of the first kinetic sum kept apart
+  // axes of which only the sums are wanted, in the x pass' launch where they can be
+  auto sum_only = [&](int a) { return !G || (riem && a == last); };
+  auto rides = [&](int a) { return sum_only(a) && h->ax[a].n == h->ax[0].n; };
+  // (their slots lie past the axis passes', which leave norms in the slot after their own)
+  auto kin_slot = [&](int a) { return rides(a) ? first + last + a : first + a - 1; };
+  SumAxes sums;
+  for (int a = 1; a <= last; ++a)
+    if (rides(a)) {
+      sums.inner[sums.n] = h->ax[a].inner;
+      sums.lamc[sums.n] = h->ax[a].lamc;
+      sums.slot[sums.n++] = kin_slot(a);
+    }
   auto gx = [&](auto f) {
     return grad_xpass<f()>(h->ax[0], h->npts, X, h->V64, G, point ? h->Xp : nullptr, mixed_point ? h->Xp32 : nullptr,
-                           h->pw, point, h->part, h->pstride, &nbx, h->st);
+                           h->pw, point, h->part, h->pstride, &nbx, &sums, h->st);
   };
   GPE_KT(h, KK_PW_GRAD,
          h->F == 1 ? gx(std::integral_constant<int, 1>{}) : h->F == 2 ? gx(std::integral_constant<int, 2>{})
                                                                       : gx(std::integral_constant<int, 3>{}));
-  const int first = G ? 1 + 2 * K : 1;   // slot of the first kinetic sum kept apart
-  for (int a = 1; a <= last; ++a)
+  for (int a = 1; a <= last; ++a) {
+    if (rides(a)) {
+      tpc[a] = sums.tpc;
+      continue;
+    }
     GPE_KT(h, KK_LAP_X + a,
-           grad_axis(h->ax[a], !G || (riem && a == last), X, G, G, mixed_point && a == last ? h->LX32 : nullptr, h->F,
+           grad_axis(h->ax[a], sum_only(a), X, G, G, mixed_point && a == last ? h->LX32 : nullptr, h->F,
                      h->npts, nullptr, nullptr, h->part, h->pstride, first + a - 1, &tpc[a], h->st));
+  }
   const size_t ps = h->pstride;
   SlotSegs s;
   auto add = [&](size_t off, int n) {
@@ -127,8 +144,8 @@ static gpe_status grad_enq(gpe_handle* h, const void* X, void* G, double* gram, 
   };
   for (int q = 0; q < first; ++q) add(q * ps, nbx);
   for (int a = 1; a <= last; ++a) {
-    if (!G) add((first + a - 1) * ps, K * tpc[a]);
-    for (int i = 0; G && i < K; ++i) add((first + a - 1) * ps + (size_t)i * tpc[a], tpc[a]);
+    if (!G) add(kin_slot(a) * ps, K * tpc[a]);
+    for (int i = 0; G && i < K; ++i) add(kin_slot(a) * ps + (size_t)i * tpc[a], tpc[a]);
   }
   GPE_KT(h, KK_FINALIZE,
          finalize_segs(h->part, s, h->part + (kMaxQ - 1) * ps, h->res, G ? POST_GRAD : POST_ENERGY, h->F,

@@ -68,11 +68,22 @@ struct PwParams {
 
 constexpr int kResNorm = 28;   // res slot of ||G||^2 of a gradient call
 
+// Strided axes whose Parseval sums <X_i, L_a X_i> alone are formed in the x pass'
+// launch (axes of the x axis' length); a component's sums are tpc partials of the slot.
+struct SumAxes {
+  int n = 0;
+  int inner[2] = {1, 1};
+  int slot[2] = {0, 0};
+  int tpc = 0;   // set by grad_xpass
+  double lamc[2] = {0, 0};
+};
+
 // Fused x pass of the energy / gradient (FP64, grad_x.h).  G null: the energy
 // only.  Partial sums in slots 0 .. 2K (0 only for the energy), *nb per slot.
 template <int F>
 hipError_t grad_xpass(const LapAxis& ax, size_t npts, const void* X, const double* V, void* G, void* xc, void* xc32,
-                      const PwParams& p, bool point, double* part, size_t stride, int* nb, hipStream_t st);
+                      const PwParams& p, bool point, double* part, size_t stride, int* nb, SumAxes* sums,
+                      hipStream_t st);
 // The same for a 1D grid, whole in one workgroup: res as POST_GRAD or POST_ENERGY
 // leaves it, proj: G projected, norm: ||G||^2 in res[kResNorm].
 template <int F>

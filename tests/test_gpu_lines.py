@@ -92,6 +92,31 @@ def test_gradient_dense_rows(F, grid):
     gp.close()
 
 
+@pytest.mark.parametrize("n", SIZES)
+def test_equal_axes(n):
+    """Axes of the x axis' length, whose sums share the x pass' launch: energy and
+    Riemannian gradient of square, of cubic and of mixed grids (y or z alone of
+    x's length) against the oracle at the tolerances above."""
+    import torch
+    from paper_1907_01194_amd.binding import Problem
+    from gpu_util import dev, host, assert_field
+    grids = [(1, (n, n)), (2, (n, 4, n)), (3, (n, n, 6))] + ([(1, (n, n, n))] if n <= 64 else [])
+    for F, grid in grids:
+        print("equal axes", F, grid, flush=True)
+        spec = small_spec(F, grid, p=0.1, q=0.05)
+        prob = oracle_problem(spec)
+        u = oracle.retraction.psi(prob, W.noisy_envelope_state(spec, n, (0.2,) * len(grid)), 1)
+        ref, E_or = oracle.rgrad(prob, u)[0], oracle.energy(prob, u)
+        gp = Problem(spec, "fp64")
+        X = dev(u)
+        assert abs(gp.energy(X) - E_or) <= 1e-10 * abs(E_or)
+        G, E, gn = gp.grad(X, riemannian=True)
+        assert abs(E - E_or) <= 1e-10 * abs(E_or)
+        assert_field(host(G), ref, 1e-11, "gradient")
+        assert abs(gn - np.linalg.norm(ref)) <= 1e-11 * gn
+        gp.close()
+
+
 @pytest.mark.parametrize("n", [s for s in SIZES if 2 * s in SIZES])
 def test_prolong_every_line_length(n):
     """Fourier prolongation of every coarse length, as a contiguous and as a
