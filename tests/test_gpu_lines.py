@@ -42,6 +42,33 @@ def test_every_line_length(n, precision):
         gp.close()
 
 
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("F,grid", [(1, (192, 192)), (3, (192, 96)), (2, (192, 16, 24)), (2, (192, 512)),
+                                    (1, (192, 48, 64)), (2, (192, 64, 48)), (1, (192, 48, 48))])
+def test_untuned_length_schedules(F, grid, precision):
+    """The x pass of length 192 on either side of the lines between its one-row,
+    128- and 256-thread schedules (2^17 and 2^19 points), the last workgroup
+    partly filled (5 or 3 rows of 3072): the product against the oracle at the
+    tolerances above."""
+    import torch
+    from paper_1907_01194_amd.binding import Problem
+    from gpu_util import dev, host, assert_field
+    print("schedules", F, grid, precision, flush=True)
+    tol = 1e-11 if precision == "fp64" else 1e-5
+    spec = small_spec(F, grid)
+    prob = oracle_problem(spec)
+    u = oracle.retraction.psi(prob, W.noisy_envelope_state(spec, 5, (0.2,) * len(grid)), 1)
+    xi = oracle.project(prob, u, W.random_direction(spec, 6))
+    gp = Problem(spec, precision)
+    gp.set_point(dev(u))
+    HR, kappa = gp.hvp_dot(dev(xi, gp.work_dtype), 0.2)
+    ref = oracle.rhess(prob, u, xi, sigma=0.2)
+    assert_field(host(HR), ref, tol, "rhess")
+    k_or = oracle.inner(xi, ref)
+    assert abs(kappa - k_or) <= tol * abs(k_or)
+    gp.close()
+
+
 @pytest.mark.parametrize("n", SIZES)
 def test_energy_and_gradients_every_line_length(n):
     """The energy (forward transforms and Parseval sums only), the Euclidean and
