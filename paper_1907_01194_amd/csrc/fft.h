@@ -19,6 +19,8 @@
 #pragma once
 
 #include "common.h"
+#include <type_traits>
+
 #include "finalize.h"
 #include "kernels.h"
 #include "spin.h"
@@ -386,21 +388,43 @@ __device__ __forceinline__ void line_apply(LineRegs<T, N>& v, c_t<T>* lds, const
   }
 }
 
+constexpr int ab_batch(int n) { return n >= 96 ? 16 : 8; }
+
 // Projection coefficients of the HVP (Lemma 4.1 with the measured Gram
 // system): sums slots 0 and 1 of the x pass's partials (ab.n per slot,
 // ab.stride apart) in a fixed order over the workgroup, solves the 2x2 Gram
 // system with the set point's component norms ab.gram and returns the
 // coefficients in c[0..1] (every thread); res: also stored in ab.res[32..33].
-__device__ inline void ab_coeffs(const AbSrc& ab, int F, bool store, double* c) {
+template <int U> __device__ inline void ab_coeffs(const AbSrc& ab, int F, bool store, double* c) {
   __shared__ double red2[2][1024 / kWave];
   __shared__ double cf[2];
   const int t = threadIdx.x;
   double s0 = 0.0, s1 = 0.0;
-#pragma unroll 8
-  for (int b = t; b < ab.n; b += blockDim.x) {
-    s0 += ab.part[b];
-    s1 += ab.part[ab.stride + b];
-  }
+  // One workgroup beside a pass that fills HBM waits long for each batch of loads,
+  // and outlasted the pass with 8 per slot (spin-3 128^3, 16384 partials: y pass 126 ->
+  // 121 us, product 490 -> 482, c64 245 -> 235).  U: 16 where the line's own registers
+  // are there for them, 8 below (16 costs the c64 pass of length 48 wavefronts, 11.5 ->
+  // 12.3 us).  The rest in batches of 4 (clamped addresses: no load waits for a branch).
+  const int bd = blockDim.x, n = ab.n;
+  int b = t;
+  auto batch = [&](auto u_) {
+    constexpr int B = decltype(u_)::value;
+    double p0[B], p1[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const int i = b + u * bd < n ? b + u * bd : n - 1;
+      p0[u] = ab.part[i];
+      p1[u] = ab.part[ab.stride + i];
+    }
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      s0 += b + u * bd < n ? p0[u] : 0.0;
+      s1 += b + u * bd < n ? p1[u] : 0.0;
+    }
+    b += B * bd;
+  };
+  while (b + (U - 1) * bd < n) batch(std::integral_constant<int, U>{});
+  while (b < n) batch(std::integral_constant<int, 4>{});
   s0 = wave_sum(s0);
   s1 = wave_sum(s1);
   if (t % kWave == 0) {
@@ -531,7 +555,7 @@ __device__ __forceinline__ void lap_body(const c_t<T>* __restrict__ in, const c_
   double c0 = 0.0, c1 = 0.0;
   if (X && ab.part) {   // uniform: the coefficients from the x pass's partials
     double cf[2];
-    ab_coeffs(ab, F, blk == 0, cf);
+    ab_coeffs<ab_batch(N)>(ab, F, blk == 0, cf);
     c0 = cf[0];
     c1 = cf[1];
   } else if (X) {
@@ -591,9 +615,10 @@ template <typename T, int N, bool CONTIG> constexpr long ax_tiles(int K, size_t 
 // Schedule variant VAR: rows per workgroup for about one wavefront (0), two
 // (1, the default) or four (2); XVAR_LATENCY: one row and a thread for each of
 // its points, for grids whose few workgroups are bound by a thread's chain of
-// FP64 operations (the threads beyond the lines' idle during the transform).  At n = 128, K = 7 a variant-0 workgroup is one
-// wavefront that owns one row of every component: 56 lanes hold 16 values each
-// for the transform, 64 lanes two points each for the pointwise terms.
+// FP64 operations (the threads beyond the lines' idle during the transform).  At
+// n = 128, K = 7 a variant-0 workgroup is one wavefront that owns one row of every
+// component: 56 lanes hold 16 values each for the transform, 64 lanes two points
+// each for the pointwise terms.
 //
 // Bound by its 29 streams of HBM traffic (4 fields and V; 5.0 TB/s of the copy
 // rate's 5.7 for this pattern) in c128 and by those and VALU issue in c64.  The
@@ -604,7 +629,9 @@ template <typename T, int N, bool CONTIG> constexpr long ax_tiles(int K, size_t 
 // with spills).  At least 2 (c128) and 4 (c64) wavefronts per SIMD: 3 in c128
 // spill 70 registers.  Measured (c128, c64):
 //   spin-3 128^3 247 -> 194 us, 140 -> 102;  spin-1 256 x 256 x 64 212 -> 165, 92 -> 82;
-//   spin-2 96^3 79 -> 60 us, 41 -> 36;  spin-2 256^2 12.6 -> 12.2 us, 10.2 -> 9.8.
+//   spin-2 96^3 79 -> 55 us, 41 -> 32;  spin-2 256^2 (one row) 12.6 -> 10.3, 10.2 -> 8.0.
+// Operands of the next point fetched ahead gain nothing (spin-1 256 x 256 x 64 167 ->
+// 166, 88 -> 87) and spill in c64 from K = 5 on (96^3 32 -> 43).
 constexpr int XVAR_LATENCY = 3;
 template <int N, int K, int VAR = 1> struct XGeo {
   static constexpr int TPL = make_plan(N).T;

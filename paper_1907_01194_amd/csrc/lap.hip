@@ -33,7 +33,7 @@ lap_axis_kernel(const c_t<T>* __restrict__ in, const c_t<T>* acc, c_t<T>* out,
     if (b == 0) {
       if (skip && *skip != 0.0) return;
       double cf[2];
-      ab_coeffs(fin, F, true, cf);
+      ab_coeffs<ab_batch(N)>(fin, F, true, cf);
       return;
     }
     --b;
@@ -116,7 +116,7 @@ static void launch_xpass(const LapAxis& ax, size_t npts, const void* X, const vo
   *nb = grid;
 }
 
-// the line lengths that get all three schedule variants (the others use the default):
+// the line lengths that get all three schedule variants (the others go by the grid's size):
 // one or two wavefronts of rows, or the latency variant
 static constexpr bool tuned_size(int n) { return n == 64 || n == 96 || n == 128 || n == 256; }
 
