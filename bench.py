@@ -43,53 +43,53 @@ VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 # VALU instructions (SQ_INSTS_VALU, per wavefront; x64 lanes), by precision and
 # schedule variant; valid only while the kernel sources hash to `src_hash`.
 MEASURED = {
-    "src_hash": "b9479596af174dd3",
+    "src_hash": "a976946e9c511bd2",
     "traffic": {
         "fp64": {
             "0": {
-                "hvp_xpass": 960321477,
-                "lap_axis_y": 705329830,
-                "lap_axis_z": 939946766
+                "hvp_xpass": 960761303,
+                "lap_axis_y": 705386450,
+                "lap_axis_z": 940000236
             },
             "1": {
-                "hvp_xpass": 958474865,
-                "lap_axis_y": 705329830,
-                "lap_axis_z": 939946766
+                "hvp_xpass": 958755287,
+                "lap_axis_y": 705386450,
+                "lap_axis_z": 940000236
             },
             "2": {
-                "hvp_xpass": 957689317,
-                "lap_axis_y": 705329830,
-                "lap_axis_z": 939946766
+                "hvp_xpass": 960298469,
+                "lap_axis_y": 705386450,
+                "lap_axis_z": 940000236
             }
         },
         "mixed": {
             "0": {
-                "hvp_xpass": 479323960,
-                "lap_axis_y": 352821879,
-                "lap_axis_z": 469991312
+                "hvp_xpass": 479481566,
+                "lap_axis_y": 352743393,
+                "lap_axis_z": 470070766
             },
             "1": {
-                "hvp_xpass": 478860473,
-                "lap_axis_y": 352821879,
-                "lap_axis_z": 469991312
+                "hvp_xpass": 478967520,
+                "lap_axis_y": 352743393,
+                "lap_axis_z": 470070766
             },
             "2": {
-                "hvp_xpass": 478603403,
-                "lap_axis_y": 352821879,
-                "lap_axis_z": 469991312
+                "hvp_xpass": 479326952,
+                "lap_axis_y": 352743393,
+                "lap_axis_z": 470070766
             }
         }
     },
     "valu": {
         "fp64": {
-            "0": 67518464,
-            "1": 67493888,
-            "2": 64040960
+            "0": 57212900,
+            "1": 56877100,
+            "2": 59408400
         },
         "mixed": {
-            "0": 67600384,
-            "1": 67371008,
-            "2": 64229376
+            "0": 58818600,
+            "1": 58245100,
+            "2": 60620800
         }
     }
 }
