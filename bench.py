@@ -34,9 +34,10 @@ import numpy as np
 
 HBM_PEAK_GBS = 8000.0   # MI355X HBM3E, published
 
-# VALU lane-operation peak of MI355X without packed FP32: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz
-# (the published 78.6 TFLOP/s FP64 / non-packed FP32 vector rate, an FMA counting as 2 flops).
-VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
+# VALU lane-operation peaks of MI355X: 256 CUs x 2.4 GHz x 64 (FP64) or 128 (FP32) lanes, the published
+# 78.6 and 157.3 TFLOP/s vector rates with an FMA counting as 2 flops.  (The c64 x pass, without
+# packed instructions, has measured 41 TOP/s: more than the FP64 rate.)
+VALU_PEAK_TOPS = {"fp64": 256 * 64 * 2.4e9 / 1e12, "mixed": 256 * 128 * 2.4e9 / 1e12}
 
 # Per-launch HBM bytes of the HVP's kernels from rocprofv3 counter runs recorded
 # in profiles/ (FETCH_SIZE + WRITE_SIZE, copy-kernel calibrated) and the x pass's
@@ -285,8 +286,9 @@ def roofline(spec, prec, ms, kt, variant, steps):
     if valu and dom == "hvp_xpass":
         ops = valu * 64
         tops = ops / per_launch_s / 1e12
-        kern["valu"] = {"bound": "alu", "achieved": round(tops, 2), "peak": round(VALU_PEAK_TOPS, 2),
-                        "unit": "TOP/s (VALU lane operations, non-packed)", "frac": round(tops / VALU_PEAK_TOPS, 4),
+        peak = VALU_PEAK_TOPS[prec]
+        kern["valu"] = {"bound": "alu", "achieved": round(tops, 2), "peak": round(peak, 2),
+                        "unit": "TOP/s (VALU lane operations)", "frac": round(tops / peak, 4),
                         "lane_ops_per_launch": ops}
     return {"bound": "hbm", "achieved": round(hvp_gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(hvp_gbs / HBM_PEAK_GBS, 4), "traffic": traffic,
