@@ -867,9 +867,9 @@ gpe_status gpe_grad(gpe_handle* h, const void* X, void* G, int riemannian, doubl
   GPE_TRY(fetch(h));
   GPE_TRY(eval_read(h, true, &e, &ag, &bg));
   if (E) *E = e;
-  if (gnorm) {
+  if (riemannian || gnorm) {   // (formed for every Riemannian gradient, and checked with or without a taker)
     GPE_TRY(finite(h, h->hres + kResNorm, 1, "the gradient norm"));
-    *gnorm = std::sqrt(h->hres[kResNorm]);
+    if (gnorm) *gnorm = std::sqrt(h->hres[kResNorm]);
   }
   return GPE_OK;
 }
