@@ -185,7 +185,10 @@ gpe_status gpe_grad(gpe_handle* h, const void* X, void* G, int riemannian, doubl
 /* Fix the point X for subsequent gpe_hvp calls: copies X into the handle,
  * computes grad E(X) in FP64 and the multipliers (alpha_g, beta_g) of its
  * projection (Lemma 4.2), and in a GPE_MIXED handle a c64 copy of X.
- * X: device c128 field; the caller may modify it afterwards. */
+ * X: device c128 field; the caller may modify it afterwards.
+ * Errors: GPE_EDEGEN, GPE_ENUMERIC for a point without a projection or with
+ * NaN or Inf.  After an error the handle has no set point: products return
+ * GPE_EINVAL until a point is accepted. */
 gpe_status gpe_set_point(gpe_handle* h, const void* X);
 
 /* Hessian-vector product at the set point u (Sec. 3 HVP formula; Lemma 4.2).

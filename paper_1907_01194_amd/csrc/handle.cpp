@@ -876,6 +876,9 @@ gpe_status gpe_grad(gpe_handle* h, const void* X, void* G, int riemannian, doubl
 
 gpe_status gpe_set_point(gpe_handle* h, const void* X) {
   if (!h || !X) return fail(h, GPE_EINVAL, "NULL argument");
+  // the kernels replace X_p, its Gram system and L X_p before the point can be
+  // rejected: until it is accepted there is none
+  h->has_point = false;
   // the multipliers and L X_p, which the HVP needs for <X_i, (LZ)_i> = <(LX)_i, Z_i>
   GPE_TRY(grad_enq(h, X, h->prec == GPE_MIXED ? h->T64 : h->LX64, h->gram_pt, GRAD_POINT, false));
   GPE_TRY(fetch(h));
