@@ -288,12 +288,25 @@ static void trace_row(const gpe_solve_opts* o, gpe_solve_stats* st, double t, do
   st->trace_len++;
 }
 
+// However a run ends, the handle's products return to its own precision.  A run
+// that ends normally in the polish has set them up; after an error the c64 set
+// point is of an earlier iterate, so there is none.
+struct PolishEnd {
+  gpe_handle* h;
+  ~PolishEnd() {
+    if (!h->polish) return;
+    h->polish = false;
+    h->has_point = false;
+  }
+};
+
 SolveTask solve_task(Ctx& c, void* Xio, const gpe_solve_opts* o, gpe_solve_stats* st) {
   gpe_handle* h = c.h;
   Clock clk;
   CO_TRY(ensure_bufs(h));
   auto& B = h->solver_bufs;
   h->polish = false;
+  const PolishEnd polish_end{h};
   bool w32 = work32(h);
   st->polish_at = -1;
   const size_t n = h->nel;

@@ -70,3 +70,46 @@ def test_failed_set_point_leaves_no_point(F, grid, precision):
         assert_field(host(gp.hvp(Z)), oracle.hvp(prob, u, xi), tol, "hvp")
         assert_field(host(gp.hvp(Z, riemannian=True, sigma=0.2)), oracle.rhess(prob, u, xi, sigma=0.2), tol, "rhess")
     gp.close()
+
+
+@pytest.mark.parametrize("lockstep", [False, True])
+def test_failed_polish_returns_to_work_precision(lockstep):
+    """A mixed solve that fails in its FP64 polish: the handle's products take c64
+    directions again, once a point is set (none is left behind).  One value of
+    V = 1e200 where X is 1e-50 gives ||grad|| = 2e150 and a curvature that
+    overflows (GPE_ENUMERIC) in the polish's first CG iteration; away from that
+    point the c64 Euclidean product is the oracle's, for a direction that is 0
+    there in every component."""
+    import torch
+    from paper_1907_01194_amd.binding import Batch, GpeError, Problem
+    from gpu_util import dev, host, relnorm
+    print("failed polish", lockstep, flush=True)
+    spec = small_spec(2, (16, 16))
+    prob = oracle_problem(spec)
+    u = oracle.retraction.psi(prob, W.noisy_envelope_state(spec, 4, (0.2, 0.2)), 1)
+    z = W.random_direction(spec, 5)
+    z[:, 9, 7] = 0
+    spec.V = spec.V.copy()
+    spec.V[9, 7] = 1e200
+    start = u.copy()
+    start[:, 9, 7] = 1e-50
+    batch = Batch([spec, spec], "mixed") if lockstep else None
+    gp = batch.problems[0] if lockstep else Problem(spec, "mixed")
+    opts = dict(rgbb_maxit=0, maxit=2, polish_tol=1e300)
+    with pytest.raises(GpeError) as e:
+        if lockstep:
+            batch.newton_solve([dev(start), dev(start)], **opts)
+        else:
+            gp.newton_solve(dev(start), **opts)
+    assert e.value.status == 4
+    Z = dev(z, torch.complex64)
+    with pytest.raises(GpeError) as e:
+        gp.hvp(Z)
+    assert e.value.status == 1
+    u[:, 9, 7] = 0
+    gp.set_point(dev(u))
+    got, ref = host(gp.hvp(Z)), oracle.hvp(prob, u, z)   # (prob: V as it was)
+    away = np.ones(spec.shape, bool)
+    away[9, 7] = False
+    assert relnorm(got[:, away], ref[:, away]) <= 1e-5
+    (batch or gp).close()
