@@ -486,10 +486,13 @@ gpe_status cg_init_enq(gpe_handle* h, double tol, double eps, int maxit) {
 
 // Small fields: the CG's closing step applies the residual and cap tests from
 // the update's partials itself (every one of its workgroups sums them), and
-// the update needs no finalize launch.
-bool cg_local_step(const gpe_handle* h) {
-  return h->nblk <= 256 && (size_t)h->nblk * (size_t)elementwise_blocks(h->nel) <= (size_t)1 << 20;
-}
+// the update needs no finalize launch.  Up to 256 partials (2^18 points) each
+// thread of a workgroup loads at most one of them, so the sum costs the same
+// there whatever the grid, however many workgroups repeat it.  A CG iteration
+// with and without the finalize's launch, in c128 and c64: spin-3 256^2 141.8 ->
+// 139.0 us, 135.2 -> 131.4;  512 x 384 244.5 -> 241.3, 185.2 -> 180.5;  64^3 271.0 -> 269.1,
+// 213.1 -> 210.9;  spin-2 512^2 185.4 -> 182.0, 140.0 -> 139.0.
+bool cg_local_step(const gpe_handle* h) { return h->nblk <= kRedThreads; }
 
 template <typename T>
 static gpe_status cg_step_t(gpe_handle* h, const void* p, const void* q, void* z, void* r) {
