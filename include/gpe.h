@@ -260,15 +260,17 @@ gpe_status gpe_newton_solve(gpe_handle* h, void* X_inout, const gpe_solve_opts* 
                             gpe_solve_stats* stats);
 
 /* Launch schedule chosen at creation: the fused x-pass kernel of the HVP
- * comes in up to 3 variants (rows of the grid for one wavefront, for two, or one
- * row with a thread per point); gpe_create times each on the handle's grid and
- * keeps the fastest (grids below 2^18 points take the last untimed).
- * Writes the chosen variant and up to nvariants measured times in
+ * comes in up to 3 variants: rows of the grid for one wavefront a workgroup (0),
+ * for two (1), and (2) one row with a thread per point on grids of fewer than
+ * 2^19 points, rows for four wavefronts on larger ones.  gpe_create times each
+ * on the handle's grid and keeps the fastest; grids of up to 2^17 points take
+ * variant 2 untimed.  (A 1D grid runs whole in one workgroup, whatever the
+ * variant.)  Writes the chosen variant and up to nvariants measured times in
  * microseconds (0 where a variant was not timed). */
 gpe_status gpe_schedule(const gpe_handle* h, int* xpass_variant, float* variant_us, int nvariants);
 
 /* Force the fused x pass's schedule variant (0 .. count-1; count from
- * gpe_schedule_count, 3 for n_x in {64, 96, 128, 256}, else 1) instead of the
+ * gpe_schedule_count, 3 for n_x in {64, 96, 128, 192, 256}, else 1) instead of the
  * autotuned one, e.g. to compare every variant's results.  All variants
  * compute the same products (they differ in rows per workgroup only).
  * Errors: GPE_EINVAL for a variant out of range (the schedule is unchanged). */
@@ -349,7 +351,8 @@ gpe_status gpe_batch_newton_solve(gpe_batch* b, void* const* X_inout, const gpe_
                                   gpe_solve_stats* stats);
 
 /* Chosen schedule variant of the batched x pass and the measured
- * microseconds per variant (0 if not timed; a batch of one is not timed). */
+ * microseconds per variant (0 if not timed; a batch of one is not timed).  The
+ * batch's variants are rows for one, two and four wavefronts (0, 1, 2) on every grid. */
 gpe_status gpe_batch_schedule(const gpe_batch* b, int* xpass_variant, float* variant_us, int nvariants);
 
 /* Message of the last failure on the batch; for NULL, of the last failed

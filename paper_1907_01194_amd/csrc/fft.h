@@ -612,8 +612,8 @@ template <typename T, int N, bool CONTIG> constexpr long ax_tiles(int K, size_t 
 
 // ---------------------------------------------------------------- fused x pass
 // Fused x pass of the Hessian-vector product: RPB x-rows, all K components.
-// Schedule variant VAR: rows per workgroup for about one wavefront (0), two
-// (1, the default) or four (2); XVAR_LATENCY: one row and a thread for each of
+// Geometry VAR: rows per workgroup for about one wavefront (0), two (1, the
+// default) or four (2); XVAR_LATENCY: one row and a thread for each of
 // its points, for grids whose few workgroups are bound by a thread's chain of
 // FP64 operations (the threads beyond the lines' idle during the transform).  At
 // n = 128, K = 7 a variant-0 workgroup is one wavefront that owns one row of every

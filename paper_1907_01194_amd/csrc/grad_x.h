@@ -247,7 +247,7 @@ hipError_t grad_xpass(const LapAxis& ax, size_t npts, const void* X, const doubl
   launch_gx<NN, F, VAR, RIDE>(ax, npts, X, V, G, xc, xc32, p, point, part, stride, nb, sums, st)
 #define GPE_CASE(NN)                                               \
   case NN: {                                                       \
-    constexpr bool mid = NN >= 64 && NN <= 256;                    \
+    constexpr bool mid = mid_length(NN);                           \
     const bool small = mid && npts < kLatencyPoints;               \
     if (small && sums->n) GPE_GX(NN, (mid ? XVAR_LATENCY : 1), true);   \
     else if (small) GPE_GX(NN, (mid ? XVAR_LATENCY : 2), false);   \

@@ -270,11 +270,8 @@ static gpe_status hvp_t(gpe_handle* h, const void* Z, void* HZ, bool riem, const
 template <typename T>
 static gpe_status tune_xpass_t(gpe_handle* h) {
   const int nv = xpass_variants(h->n[0]);
-  if (nv <= 1 || h->npts < (1u << 15)) return GPE_OK;
-  // Below 2^18 points a pass takes 10 us or so, which events around a launch (+- 5
-  // us) cannot rank; the latency variant is the fastest there (spin-2
-  // 256^2, variants 0, 1, 2: 11.3, 11.0, 10.0 us in c128, 8.9, 9.2, 8.0 in c64).
-  if (h->npts < kLatencyPoints) {
+  if (nv <= 1 || h->dim == 1) return GPE_OK;   // (a 1D grid runs whole in one workgroup)
+  if (h->npts <= kUntimedPoints) {
     h->xvar = 2;
     return GPE_OK;
   }

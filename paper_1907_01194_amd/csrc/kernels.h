@@ -51,10 +51,30 @@ struct AbSrc {
 // projection coefficients itself.
 constexpr int kAbLocalMax = 1024;
 
-// Grids below this many points take one x-row per workgroup and one point per
-// thread in the fused x passes (256^2, 2^16 points: 11.3 -> 10.0 us; from 2^18 on
-// every CU has several rows and the denser variants are timed instead).
+// x lengths whose fused x passes come in several schedules (rows a workgroup, XGeo).
+// Longer ones have one row a workgroup in each of them; shorter ones take two
+// wavefronts' rows.
+constexpr bool mid_length(int n) { return n >= 64 && n <= 256; }
+// Gradients and energies of a mid x length take one x row a workgroup, a thread for
+// each of its points, below this many grid points (256^2: 11.3 -> 10.0 us): from here
+// on every CU has several rows.
 constexpr size_t kLatencyPoints = (size_t)1 << 18;
+// The product's x pass: schedule 2 is that one row a workgroup below kDensePoints, and
+// four wavefronts' rows from there on; up to kUntimedPoints it is taken as it is, above
+// the three are timed on the handle's own grid (schedules 0, 1, one row, four
+// wavefronts' rows in us; 64, 96, 128, 192 and 256 points by 16 rows to 2^20 points in
+// every spin and precision):
+//   64^2 spin 1 c64 5.3, 6.2, 5.0, 6.7;     128^2 spin 1 c64 8.1, 9.1, 6.6, 10.0;
+//   96 x 16 spin 3 c128 11.7, 11.0, 8.2, 11.9;  256^2 spin 2 c128 11.1, 11.2, 10.1, 14.3;
+//   256 x 512 (2^17) spin 1 c64 9.6, 9.8, 7.8, 11.2, spin 2 c128 16.7, 16.6, 16.4, 16.1;
+//   192 x 32 x 32 (0.75 2^18) spin 3 c128 24.2, 24.1, 27.6, 26.1, spin 1 c64 11.3, 11.1, 9.8, 12.3;
+//   256 x 32 x 32 (2^18) spin 1 c64 13.4, 14.8, 12.6, 14.6, c128 16.0, 18.0, 18.5, 16.4;
+//   128 x 64 x 64 (2^19) spin 1 c128 22.7, 23.3, 30.1, 23.4;
+//   192 x 48 x 96 (1.7 2^19) spin 1 c64 two wavefronts 23.7, four 21.6.
+// One row is never behind schedule 1 up to 2^17 points (nor more than 0.8 us behind the best),
+// and never more than 2 % ahead of the rest from 2^19 on.
+constexpr size_t kUntimedPoints = (size_t)1 << 17;
+constexpr size_t kDensePoints = (size_t)1 << 19;
 
 // Physical constants of the pointwise terms, already combined with h:
 // zee[l] = b_l (storage order), c0 = 2 beta0 / h, ... (gradient factors)
@@ -105,7 +125,7 @@ hipError_t grad_axis(const LapAxis& ax, bool sum_only, const void* in, const voi
 //   Y = L X; only their pointwise part with Y null, for a Euclidean product), [2] sum <X_i,Z_i>, [3] sum l_i <X_i,Z_i>, [4] <Z, W - LZ>, [5] ||Z||^2,
 //   [6] <Z, L_x Z> (Parseval).
 // Returns the number of workgroups (partials per slot) in *nblk_out.
-// var: schedule variant (rows per workgroup), 0 .. xpass_variants(n)-1; 1 is the default.
+// var: schedule (rows per workgroup; see kDensePoints), 0 .. xpass_variants(n)-1; 1 is the default.
 // skip (all the launches below that take one): a device flag; when it is
 // nonzero at launch time every workgroup returns at once (null: never).
 template <typename T>
@@ -419,7 +439,8 @@ hipError_t lap_batched(const LapArgs<T>* args, const Span& sp, int F, int slot, 
 int lap_batch_blocks(int n, int inner, size_t npts, int K, bool c64);
 bool batch_size_supported(int n);
 
-// Batched fused x pass (hvp_xpass for every problem with schedule variant var).
+// Batched fused x pass (hvp_xpass for every problem): rows for one (var 0), two (1) or
+// four (2) wavefronts, whatever the grids.
 template <typename T> struct XpassArgs {
   const void* X;
   const void* Z;

@@ -116,45 +116,20 @@ static void launch_xpass(const LapAxis& ax, size_t npts, const void* X, const vo
   *nb = grid;
 }
 
-// the line lengths that get all three schedule variants (the others go by the grid's size):
-// one or two wavefronts of rows, or the latency variant
-static constexpr bool tuned_size(int n) { return n == 64 || n == 96 || n == 128 || n == 256; }
-
-// An untuned length with work for its rows' threads to gain by another variant.
-// 256 threads' rows leave fewer threads without a line in the transform than 128
-// do by an eighth and more (192, K = 3: 240 of 256 against 96 of 128; K = 5 alike),
-// where c64 is bound by issue and the grid fills the chip either way: 192 x 48 x 96
-// spin-1 23.7 -> 21.6 us, 192 x 96 x 64 spin-2 45.3 -> 43.8; 192 x 48 x 32 has too
-// few rows (12.9 -> 14.1), c128 is bound by HBM (37.1 -> 38.7).
-template <int N, int K> static constexpr bool denser_fills() {
-  using A = XGeo<N, K, 1>;
-  using B = XGeo<N, K, 2>;
-  return B::LINES * B::TPL * A::THREADS * 8 > A::LINES * A::TPL * B::THREADS * 9;
-}
-constexpr size_t kDensePoints = 2 * kLatencyPoints;
-// One row a workgroup on grids of few rows of a middle length: 192^2 spin-1 8.0 ->
-// 6.7 us, c64 7.6 -> 6.3, 192 x 96 spin-3 11.6 -> 9.3; at 192 x 48 x 24 slower
-// (20.8 -> 22.6).
-constexpr size_t kFewRowsPoints = kLatencyPoints / 2;
-
 template <typename T, int N, int F>
 static void launch_xpass_var(int var, const LapAxis& ax, size_t npts, const void* X, const void* Z, const void* Y,
                              const T* V, void* W, const PwParams& p, double* part, size_t stride, int* nb,
                              const double* skip, hipStream_t st) {
-  if constexpr (tuned_size(N)) {
+  if constexpr (mid_length(N)) {   // the other lengths have schedule 1 only
     if (var == 0) return launch_xpass<T, N, F, 0>(ax, npts, X, Z, Y, V, W, p, part, stride, nb, skip, st);
-    if (var == 2) return launch_xpass<T, N, F, XVAR_LATENCY>(ax, npts, X, Z, Y, V, W, p, part, stride, nb, skip, st);
-  }
-  if constexpr (!tuned_size(N) && N > 64 && N < 256)
-    if (npts < kFewRowsPoints)
+    if (var == 2 && npts < kDensePoints)
       return launch_xpass<T, N, F, XVAR_LATENCY>(ax, npts, X, Z, Y, V, W, p, part, stride, nb, skip, st);
-  if constexpr (!tuned_size(N) && sizeof(T) == 4 && denser_fills<N, 2 * F + 1>())
-    if (npts >= kDensePoints)
-      return launch_xpass<T, N, F, 2>(ax, npts, X, Z, Y, V, W, p, part, stride, nb, skip, st);
+    if (var == 2) return launch_xpass<T, N, F, 2>(ax, npts, X, Z, Y, V, W, p, part, stride, nb, skip, st);
+  }
   launch_xpass<T, N, F, 1>(ax, npts, X, Z, Y, V, W, p, part, stride, nb, skip, st);
 }
 
-int xpass_variants(int n) { return tuned_size(n) ? 3 : 1; }
+int xpass_variants(int n) { return mid_length(n) ? 3 : 1; }
 
 template <typename T>
 hipError_t hvp_xpass(int F, const LapAxis& ax, size_t npts, const void* X, const void* Z, const void* Y,
