@@ -229,7 +229,8 @@ template <typename T> __host__ __device__ constexpr bool digit_split(int Ns, int
 // LDS index of element a of a butterfly whose first element is `base`.
 // LS = 0: the line is contiguous from lbase in the padded layout; LS > 0: its
 // elements sit LS apart from lbase (lines side by side).
-template <typename T, int R, int M, int LS> __device__ __forceinline__ int lds_at(int lbase, int base, int a) {
+template <typename T, int R, int M, int LS>
+__host__ __device__ __forceinline__ int lds_at(int lbase, int base, int a) {
   if constexpr (LS > 0) return lbase + (base + a * M) * LS;
   else if constexpr (write_split<T>(M, R)) return lbase + lpad<T>(base) + (M == 1 ? a : lpad<T>(a * M));
   else if constexpr (digit_split<T>(M, R)) return lbase + lpad<T>(base) + lpad<T>(a * M);
