@@ -84,21 +84,19 @@ int lap_batch_blocks(int n, int inner, size_t npts, int K, bool c64) {
 }
 
 template <typename T, bool CONTIG>
-static void launch_lb(const LapArgs<T>* args, const Span& sp, int F, int slot, hipStream_t st) {
+static hipError_t launch_lb(const LapArgs<T>* args, const Span& sp, int F, int slot, hipStream_t st) {
   constexpr size_t lds = lap_batch_lds<T, CONTIG>();
-  if (lds > 65536)
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&lap_batched_kernel<T, CONTIG>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  const hipError_t e = allow_lds(&lap_batched_kernel<T, CONTIG>, lds);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((lap_batched_kernel<T, CONTIG>), dim3(sp.nblocks), dim3(kLapBatchThreads), lds, st, args,
                      sp.blk0, sp.nprob, F, slot);
+  return hipGetLastError();
 }
 
 template <typename T>
 hipError_t lap_batched(const LapArgs<T>* args, const Span& sp, int F, int slot, bool contig, hipStream_t st) {
   if (sp.nprob < 1 || sp.nblocks < 1) return hipErrorInvalidValue;
-  if (contig) launch_lb<T, true>(args, sp, F, slot, st);
-  else launch_lb<T, false>(args, sp, F, slot, st);
-  return hipGetLastError();
+  return contig ? launch_lb<T, true>(args, sp, F, slot, st) : launch_lb<T, false>(args, sp, F, slot, st);
 }
 
 // ---------------------------------------------------------------- fused x pass
@@ -163,9 +161,8 @@ template <typename T, int F, int VAR>
 static hipError_t launch_xb(const XpassArgs<T>* args, const Span& sp, hipStream_t st) {
   using G = XB<2 * F + 1, VAR>;
   const size_t lds = sizeof(c_t<T>) * G::template lds_elems<T>();
-  if (lds > 65536)
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&xpass_batched_kernel<T, F, VAR>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  const hipError_t e = allow_lds(&xpass_batched_kernel<T, F, VAR>, lds);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((xpass_batched_kernel<T, F, VAR>), dim3(sp.nblocks), dim3(G::THREADS), lds, st, args, sp.blk0,
                      sp.nprob);
   return hipGetLastError();

@@ -130,6 +130,13 @@ __device__ inline void block_partials_any(const double (&acc)[NQ], double* __res
   block_sums(acc, [&](int q, double s) { part[(size_t)q * stride + blk] = s; });
 }
 
+// Let a kernel take `lds` bytes of dynamic LDS (up to 64 KB need no asking).
+template <typename Kernel> inline hipError_t allow_lds(Kernel* kernel, size_t lds) {
+  if (lds <= 65536) return hipSuccess;
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)lds);
+}
+
 // Workgroups of a reduction over npts grid points: four points per thread, but
 // no fewer than one per thread up to 256 workgroups (a small field's reduction is
 // bound by each thread's chain of loads: the CG update of a 256^2 spin-2 field

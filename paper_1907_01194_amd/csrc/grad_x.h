@@ -206,7 +206,7 @@ grad_xpass_kernel(const double2* __restrict__ X, const double* __restrict__ V, d
 }
 
 template <int N, int F, int VAR, bool RIDE>
-static void launch_gx(const LapAxis& ax, size_t npts, const void* X, const double* V, void* G, void* xc, void* xc32,
+static hipError_t launch_gx(const LapAxis& ax, size_t npts, const void* X, const double* V, void* G, void* xc, void* xc32,
                       const PwParams& p, bool point, double* part, size_t stride, int* nb, SumAxes* sums, hipStream_t st) {
   using GG = XGeo<N, 2 * F + 1, VAR>;
   using AG = AxGeo<double, N, false>;
@@ -218,18 +218,17 @@ static void launch_gx(const LapAxis& ax, size_t npts, const void* X, const doubl
   if (RIDE && elems < (size_t)padded_len<double>(N) + AG::TILE) elems = (size_t)padded_len<double>(N) + AG::TILE;
   const size_t lds = sizeof(double2) * elems;
   auto run = [&](auto* kernel) {
-    if (lds > 65536)
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds);
+    const hipError_t e = allow_lds(kernel, lds);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kernel, dim3(grid + sums->n * tiles), dim3(RIDE ? sums_threads<N, F, VAR>() : GG::THREADS),
                        lds, st, reinterpret_cast<const double2*>(X), V,
                        reinterpret_cast<double2*>(G), reinterpret_cast<double2*>(xc), reinterpret_cast<float2*>(xc32),
                        reinterpret_cast<const double2*>(ax.tw64), nrows, npts, ax.lamc, p, point, part, stride,
                        GradOne{}, *sums, grid);
+    return hipGetLastError();
   };
-  if (G) run(&grad_xpass_kernel<N, F, true, VAR, false, RIDE>);
-  else run(&grad_xpass_kernel<N, F, false, VAR, false, RIDE>);
   *nb = grid;
+  return G ? run(&grad_xpass_kernel<N, F, true, VAR, false, RIDE>) : run(&grad_xpass_kernel<N, F, false, VAR, false, RIDE>);
 }
 
 // From kLatencyPoints on 256 threads' rows a workgroup, against 128: gradient and
@@ -244,40 +243,37 @@ hipError_t grad_xpass(const LapAxis& ax, size_t npts, const void* X, const doubl
                       hipStream_t st) {
   switch (ax.n) {
 #define GPE_GX(NN, VAR, RIDE) \
-  launch_gx<NN, F, VAR, RIDE>(ax, npts, X, V, G, xc, xc32, p, point, part, stride, nb, sums, st)
+  return launch_gx<NN, F, VAR, RIDE>(ax, npts, X, V, G, xc, xc32, p, point, part, stride, nb, sums, st)
 #define GPE_CASE(NN)                                               \
   case NN: {                                                       \
     constexpr bool mid = mid_length(NN);                           \
     const bool small = mid && npts < kLatencyPoints;               \
     if (small && sums->n) GPE_GX(NN, (mid ? XVAR_LATENCY : 1), true);   \
-    else if (small) GPE_GX(NN, (mid ? XVAR_LATENCY : 2), false);   \
-    else if (sums->n) GPE_GX(NN, 1, true);                         \
-    else GPE_GX(NN, 2, false);                                     \
-    break;                                                         \
+    if (small) GPE_GX(NN, (mid ? XVAR_LATENCY : 2), false);        \
+    if (sums->n) GPE_GX(NN, 1, true);                              \
+    GPE_GX(NN, 2, false);                                          \
   }
     GPE_SIZES(GPE_CASE)
 #undef GPE_CASE
 #undef GPE_GX
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 template <int N, int F>
-static void launch_one(const LapAxis& ax, const void* X, const double* V, void* G, void* xc, void* xc32,
+static hipError_t launch_one(const LapAxis& ax, const void* X, const double* V, void* G, void* xc, void* xc32,
                        const PwParams& p, bool point, const GradOne& one, hipStream_t st) {
   using GG = XGeo<N, 2 * F + 1, XVAR_LATENCY>;
   const size_t lds = sizeof(double2) * GG::template lds_elems<double>();
   auto run = [&](auto* kernel) {
-    if (lds > 65536)
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds);
+    const hipError_t e = allow_lds(kernel, lds);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kernel, dim3(1), dim3(GG::THREADS), lds, st, reinterpret_cast<const double2*>(X), V,
                        reinterpret_cast<double2*>(G), reinterpret_cast<double2*>(xc), reinterpret_cast<float2*>(xc32),
                        reinterpret_cast<const double2*>(ax.tw64), 1, (size_t)N, ax.lamc, p, point, nullptr, 0, one,
                        SumAxes{}, 1);
+    return hipGetLastError();
   };
-  if (G) run(&grad_xpass_kernel<N, F, true, XVAR_LATENCY, true>);
-  else run(&grad_xpass_kernel<N, F, false, XVAR_LATENCY, true>);
+  return G ? run(&grad_xpass_kernel<N, F, true, XVAR_LATENCY, true>) : run(&grad_xpass_kernel<N, F, false, XVAR_LATENCY, true>);
 }
 
 template <int F>
@@ -287,12 +283,11 @@ hipError_t grad_one(const LapAxis& ax, const void* X, const double* V, void* G, 
   const GradOne one{gram, res, mirror, proj, norm};
   switch (ax.n) {
 #define GPE_CASE(NN) \
-  case NN: launch_one<NN, F>(ax, X, V, G, xc, xc32, p, point, one, st); break;
+  case NN: return launch_one<NN, F>(ax, X, V, G, xc, xc32, p, point, one, st);
     GPE_SIZES(GPE_CASE)
 #undef GPE_CASE
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 template hipError_t grad_one<GPE_GRAD_F>(const LapAxis&, const void*, const double*, void*, void*, void*,
                                          const PwParams&, bool, bool, bool, double*, double*, double*, hipStream_t);

@@ -17,19 +17,19 @@ hvp_one_kernel(const c_t<T>* __restrict__ X, const c_t<T>* __restrict__ Z, const
 }
 
 template <typename T, int N, int F>
-static void launch(const LapAxis& ax, const void* X, const void* Z, const void* Y, const T* V, void* W,
+static hipError_t launch(const LapAxis& ax, const void* X, const void* Z, const void* Y, const T* V, void* W,
                    const PwParams& p, double* gram, double* res, double* mirror, int post, bool proj,
                    const double* skip, hipStream_t st) {
   using T2 = c_t<T>;
   using G = XGeo<N, 2 * F + 1, XVAR_LATENCY>;
   const size_t lds = sizeof(T2) * G::template lds_elems<T>();
-  if (lds > 65536)
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&hvp_one_kernel<T, N, F>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  const hipError_t e = allow_lds(&hvp_one_kernel<T, N, F>, lds);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((hvp_one_kernel<T, N, F>), dim3(1), dim3(G::THREADS), lds, st, reinterpret_cast<const T2*>(X),
                      reinterpret_cast<const T2*>(Z), reinterpret_cast<const T2*>(Y), V, reinterpret_cast<T2*>(W),
                      reinterpret_cast<const T2*>(sizeof(T) == 8 ? ax.tw64 : ax.tw32), (T)ax.lamc, p, skip,
                      OneArgs{gram, res, mirror, post, proj});
+  return hipGetLastError();
 }
 
 template <typename T>
@@ -38,14 +38,13 @@ hipError_t hvp_one(int F, const LapAxis& ax, const void* X, const void* Z, const
                    const double* skip, hipStream_t st) {
   switch (ax.n * 4 + F) {
 #define GPE_CASE(NN)                                                                                                   \
-  case NN * 4 + 1: launch<T, NN, 1>(ax, X, Z, Y, V, W, p, gram, res, mirror, post, proj, skip, st); break;            \
-  case NN * 4 + 2: launch<T, NN, 2>(ax, X, Z, Y, V, W, p, gram, res, mirror, post, proj, skip, st); break;            \
-  case NN * 4 + 3: launch<T, NN, 3>(ax, X, Z, Y, V, W, p, gram, res, mirror, post, proj, skip, st); break;
+  case NN * 4 + 1: return launch<T, NN, 1>(ax, X, Z, Y, V, W, p, gram, res, mirror, post, proj, skip, st); \
+  case NN * 4 + 2: return launch<T, NN, 2>(ax, X, Z, Y, V, W, p, gram, res, mirror, post, proj, skip, st); \
+  case NN * 4 + 3: return launch<T, NN, 3>(ax, X, Z, Y, V, W, p, gram, res, mirror, post, proj, skip, st);
     GPE_SIZES(GPE_CASE)
 #undef GPE_CASE
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 template hipError_t hvp_one<double>(int, const LapAxis&, const void*, const void*, const void*, const double*, void*,
                                     const PwParams&, double*, double*, double*, int, bool, const double*, hipStream_t);

@@ -96,7 +96,7 @@ hipError_t lap_axis(const LapAxis& ax, const void* in, const void* acc, void* ou
 }
 
 template <typename T, int N, int F, int VAR>
-static void launch_xpass(const LapAxis& ax, size_t npts, const void* X, const void* Z, const void* Y, const T* V,
+static hipError_t launch_xpass(const LapAxis& ax, size_t npts, const void* X, const void* Z, const void* Y, const T* V,
                          void* W, const PwParams& p, double* part, size_t stride, int* nb, const double* skip,
                          hipStream_t st) {
   using T2 = c_t<T>;
@@ -106,18 +106,18 @@ static void launch_xpass(const LapAxis& ax, size_t npts, const void* X, const vo
   const int grid = (int)((nrows + G::RPB - 1) / G::RPB);
   const size_t lds = sizeof(T2) * G::template lds_elems<T>();
   const T2* tw = reinterpret_cast<const T2*>(sizeof(T) == 8 ? ax.tw64 : ax.tw32);
-  if (lds > 65536)
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&hvp_xpass_kernel<T, N, F, VAR>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  const hipError_t e = allow_lds(&hvp_xpass_kernel<T, N, F, VAR>, lds);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((hvp_xpass_kernel<T, N, F, VAR>), dim3(grid), dim3(G::THREADS), lds, st,
                      reinterpret_cast<const T2*>(X), reinterpret_cast<const T2*>(Z),
                      reinterpret_cast<const T2*>(Y), V, reinterpret_cast<T2*>(W), tw, nrows, npts, (T)ax.lamc, p,
                      part, stride, skip);
   *nb = grid;
+  return hipGetLastError();
 }
 
 template <typename T, int N, int F>
-static void launch_xpass_var(int var, const LapAxis& ax, size_t npts, const void* X, const void* Z, const void* Y,
+static hipError_t launch_xpass_var(int var, const LapAxis& ax, size_t npts, const void* X, const void* Z, const void* Y,
                              const T* V, void* W, const PwParams& p, double* part, size_t stride, int* nb,
                              const double* skip, hipStream_t st) {
   if constexpr (mid_length(N)) {   // the other lengths have schedule 1 only
@@ -126,7 +126,7 @@ static void launch_xpass_var(int var, const LapAxis& ax, size_t npts, const void
       return launch_xpass<T, N, F, XVAR_LATENCY>(ax, npts, X, Z, Y, V, W, p, part, stride, nb, skip, st);
     if (var == 2) return launch_xpass<T, N, F, 2>(ax, npts, X, Z, Y, V, W, p, part, stride, nb, skip, st);
   }
-  launch_xpass<T, N, F, 1>(ax, npts, X, Z, Y, V, W, p, part, stride, nb, skip, st);
+  return launch_xpass<T, N, F, 1>(ax, npts, X, Z, Y, V, W, p, part, stride, nb, skip, st);
 }
 
 int xpass_variants(int n) { return mid_length(n) ? 3 : 1; }
@@ -137,17 +137,13 @@ hipError_t hvp_xpass(int F, const LapAxis& ax, size_t npts, const void* X, const
                      const double* skip, hipStream_t st) {
   switch (ax.n * 4 + F) {
 #define GPE_CASE(NN)                                                                                          \
-  case NN * 4 + 1: launch_xpass_var<T, NN, 1>(var, ax, npts, X, Z, Y, V, W, p, part, stride, nb, skip, st); \
-    break;                                                                                                    \
-  case NN * 4 + 2: launch_xpass_var<T, NN, 2>(var, ax, npts, X, Z, Y, V, W, p, part, stride, nb, skip, st); \
-    break;                                                                                                    \
-  case NN * 4 + 3: launch_xpass_var<T, NN, 3>(var, ax, npts, X, Z, Y, V, W, p, part, stride, nb, skip, st); \
-    break;
+  case NN * 4 + 1: return launch_xpass_var<T, NN, 1>(var, ax, npts, X, Z, Y, V, W, p, part, stride, nb, skip, st); \
+  case NN * 4 + 2: return launch_xpass_var<T, NN, 2>(var, ax, npts, X, Z, Y, V, W, p, part, stride, nb, skip, st); \
+  case NN * 4 + 3: return launch_xpass_var<T, NN, 3>(var, ax, npts, X, Z, Y, V, W, p, part, stride, nb, skip, st);
     GPE_SIZES(GPE_CASE)
 #undef GPE_CASE
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 size_t lap_max_blocks(const LapAxis& ax, int K) {
