@@ -238,9 +238,9 @@ static gpe_status hvp_t(gpe_handle* h, const void* Z, void* HZ, bool riem, const
   for (int q = 0; q < 7; ++q) nb.nb[q] = nbx;
   double* coef = h->res + 32;
   // Projection coefficients (Lemma 4.1) from the x pass's partials: with few
-  // x-pass workgroups every workgroup of the last axis pass forms them itself;
-  // in 3D otherwise one extra workgroup of the y pass does; else a finalize.
-  const bool ab_local = riem && nbx <= kAbLocalMax;
+  // rows every workgroup of the last axis pass forms them itself; in 3D
+  // otherwise one extra workgroup of the y pass does; else a finalize.
+  const bool ab_local = riem && h->npts / (size_t)h->n[0] <= (size_t)kAbLocalMax;
   const bool ab_ypass = riem && !ab_local && h->dim == 3;
   if (riem && !ab_local && !ab_ypass)
     GPE_KT(h, KK_FINALIZE,

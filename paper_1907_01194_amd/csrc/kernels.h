@@ -47,8 +47,12 @@ struct AbSrc {
   const double* gram = nullptr;
   double* res = nullptr;
 };
-// Largest x-pass workgroup count for which the last axis pass forms the
-// projection coefficients itself.
+// Most x rows (of a lone product; of a batch: x-pass workgroups) for which the last
+// axis pass forms the projection coefficients itself.  By rows, so that it does not
+// hang on the schedule, which is ranked by the x pass alone: beyond it, with few
+// enough workgroups to stay local, 3D products lose in the last pass what the
+// schedule gains (128 x 48 x 24, schedule 1, local and in the y pass: spin-3 c128
+// 48.0 and 43.3 us, spin-1 30.4 and 27.6, c64 22.2 and 20.9; 48^3 spin 1 24.0 and 22.8).
 constexpr int kAbLocalMax = 1024;
 
 // x lengths whose fused x passes come in several schedules (rows a workgroup, XGeo).
