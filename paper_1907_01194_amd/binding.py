@@ -402,10 +402,11 @@ class Batch:
         """HZ_i = Hess(Z_i) for every problem at its set point; returns (HZs, kappas).
         kappa=False: no kappas (None) and no synchronisation."""
         m = len(self.problems)
-        Zs = [Z for _, Z in zip(self.problems, Zs)]   # (gone through twice below: Zs may be an iterator)
+        if not isinstance(Zs, (list, tuple)):   # (an iterator: Zs is gone through twice below)
+            Zs = [Z for _, Z in zip(self.problems, Zs)]
         zp = (c_void_p * m)(*[p._w(Z).value for p, Z in zip(self.problems, Zs)])
         # (a checked Z has the result's shape, type and device: half the cost of building each from its parts)
-        outs = outs if outs is not None else [self.torch.empty_like(Z) for Z in Zs]
+        outs = outs if outs is not None else [self.torch.empty_like(Z) for _, Z in zip(self.problems, Zs)]
         hp = (c_void_p * m)(*[p._w(H).value for p, H in zip(self.problems, outs)])
         sg = (c_double * m)(*([0.0] * m if sigma is None else [float(x) for x in sigma]))
         kap = (c_double * m)() if kappa else None
