@@ -61,8 +61,8 @@ typedef enum { GPE_R1_PROJECTIVE = 1, GPE_R2_ORTHOGONAL = 2, GPE_R3_CLOSED = 3 }
 /* Problem statement (Sec. 2 energy with mass and magnetization constraints,
  * Sec. 3 discretisation).  F in {1,2,3}; dim in {1,2,3}; each used n[a] is
  * one of 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256, 384, 512, i.e.
- * 2^k or 3*2^k (Sec. 3 asks for an even n; the line transforms take radix
- * 8/4/2 stages and at most one radix-3 stage); unused axes are ignored;
+ * 2^k or 3*2^k (Sec. 3 asks for an even n; the line transforms take up to
+ * three stages of radix 3 to 16); unused axes are ignored;
  * lo[a] < hi[a]; beta = (beta0, beta1, beta2, beta3) (beta2 used for F >= 2,
  * beta3 for F = 3); Zeeman shifts p, q give b_l = -p l + q l^2; |M| < F.
  * A negative M is handled by the symmetry M <-> -M, phi_l <-> phi_-l (Sec. 4),
@@ -302,8 +302,8 @@ const char* gpe_version(void);
  * problem in lock step: at each of its steps the device work of all problems
  * that are at the same step is one launch per kernel stage (the fused HVP x
  * pass, the axis passes, the finalize, the CG updates, the energy and
- * gradient, the retraction), and the scalars of all problems come back in one
- * copy with one synchronisation.  Each problem runs the iteration
+ * gradient, the retraction), and the scalars of all problems come back with
+ * one synchronisation.  Each problem runs the iteration
  * gpe_newton_solve runs (the same readings, tolerances and counters); the
  * batched kernels may sum partial results in another order, so iteration
  * counts and the last digits of a problem's iterates can differ from a lone

@@ -211,11 +211,11 @@ template <typename T> __host__ __device__ constexpr int pad_run() { return 1 << 
 template <typename T> __host__ __device__ constexpr int lpad(int j) { return j + (j >> pad_shift<T>()); }
 // LDS elements a padded line (or twiddle table) of length N occupies
 template <typename T> __host__ __device__ constexpr int padded_len(int N) { return N + (N >> pad_shift<T>()) + 1; }
-// Index shortcuts of a padded stage: elements b + r B may be taken as
-// lpad(b) + lpad(r B) when B is a multiple of the pad run; elements
-// base + r Ns (base = (b / Ns) Ns R + b % Ns) as lpad(base) + lpad(r Ns) when
-// Ns is, or as lpad(base) + r when Ns = 1 and R divides the pad run (base + r
-// then never carries into the pad count).
+// Index shortcuts of a padded stage: b + r B may be taken as lpad(b) + lpad(r B)
+// when B is a multiple of the pad run; the elements base + r Ns of a butterfly
+// (base = (b / Ns) Ns R + b % Ns) as lpad(base) + lpad(r Ns) when Ns is, or as
+// lpad(base) + r when Ns = 1 and R divides the pad run (base + r then never
+// carries into the pad count).
 template <typename T> __host__ __device__ constexpr bool read_split(int B) { return B % pad_run<T>() == 0; }
 template <typename T> __host__ __device__ constexpr bool write_split(int Ns, int R) {
   return read_split<T>(Ns) || (Ns == 1 && pad_run<T>() % R == 0);

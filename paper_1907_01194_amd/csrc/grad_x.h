@@ -80,9 +80,11 @@ grad_xpass_kernel(const double2* __restrict__ X, const double* __restrict__ V, d
   // ---- pointwise terms of this thread's points; the rows of X go to LDS
   // Where a workgroup has several rows, all of a thread's points are fetched before
   // the first is used: LDS and registers hold the CU to 2-4 wavefronts per SIMD, too
-  // few to cover one point's loads at a time (spin-1 256 x 256 x 64: gradient 125.5 ->
-  // 115 us, energy 51.7 -> 48.4).  One row a workgroup is faster point by point (512^2:
-  // 15.5 us against 16.6).
+  // few to cover one point's loads at a time.  256 x 256 x 64, gradient of spin 1, 2, 3:
+  // 116 -> 106 us, 186 -> 179, 265 -> 251, although 256 points of spin 1, 2 and 3 spill 6,
+  // 12 and 10 registers (spin 3 also point by point); spin-3 128^3 energy 128 -> 121.
+  // Grids whose workgroups are few lose a little: 256 x 64 x 32 spin 2 30.5 -> 31.8 us.
+  // One row a workgroup is faster point by point (512^2: 15.5 us against 16.6).
   constexpr bool AHEAD = RPB > 1;
   T2 xs[AHEAD ? PPT : 1][K], q[GRAD ? PPT : 1][K];
   T vs[AHEAD ? PPT : 1];

@@ -60,8 +60,8 @@ constexpr int kAbLocalMax = 1024;
 // wavefronts' rows.
 constexpr bool mid_length(int n) { return n >= 64 && n <= 256; }
 // Gradients and energies of a mid x length take one x row a workgroup, a thread for
-// each of its points, below this many grid points (256^2: 11.3 -> 10.0 us): from here
-// on every CU has several rows.
+// each of its points, below this many grid points (gradient of spin-2 256^2: 10.4 -> 9.8
+// us): from here on every CU has several rows.
 constexpr size_t kLatencyPoints = (size_t)1 << 18;
 // The product's x pass: schedule 2 is that one row a workgroup below kDensePoints, and
 // four wavefronts' rows from there on; up to kUntimedPoints it is taken as it is, above
@@ -126,8 +126,8 @@ hipError_t grad_axis(const LapAxis& ax, bool sum_only, const void* in, const voi
 //   W = L_x Z + (pointwise Hessian terms of Sec. 3) + p.zc[i] Z_i,
 // with FP64 partial sums (one per workgroup, slots of stride `stride`):
 //   [0] sum_i <X_i, W_i>  [1] sum_i l_i <X_i, W_i>  (both through <(LX)_i, Z_i> = <X_i, (LZ)_i>,
-//   Y = L X; only their pointwise part with Y null, for a Euclidean product), [2] sum <X_i,Z_i>, [3] sum l_i <X_i,Z_i>, [4] <Z, W - LZ>, [5] ||Z||^2,
-//   [6] <Z, L_x Z> (Parseval).
+//   Y = L X; only their pointwise part with Y null, for a Euclidean product), [2] sum <X_i,Z_i>,
+//   [3] sum l_i <X_i,Z_i>, [4] <Z, W - LZ>, [5] ||Z||^2, [6] <Z, L_x Z> (Parseval).
 // Returns the number of workgroups (partials per slot) in *nblk_out.
 // var: schedule (rows per workgroup; see kDensePoints), 0 .. xpass_variants(n)-1; 1 is the default.
 // skip (all the launches below that take one): a device flag; when it is

@@ -38,7 +38,7 @@ struct gpe_handle {
   double* hres = nullptr;      // pinned host mirror of res
   bool res_shared = false;     // res / hres are slices of a batch's arrays (not owned)
   int nblk = 1;
-  int xvar = 1;                // schedule variant of the fused x pass (autotuned)
+  int xvar = 1;                // schedule of the product's x pass (tune_xpass)
   float xvar_us[3] = {0, 0, 0};  // measured microseconds per variant (0: not measured)
   gpe::PwParams pw;
 
@@ -125,9 +125,9 @@ template <typename T>
 gpe_status laplacian(gpe_handle* h, const void* in, void* out);
 
 // Operations that end in a reduction come in two halves: *_enq launches the
-// kernels and the finalize into h->res (stream-ordered, no synchronisation);
-// after h->res has reached h->hres (fetch, or a lock-step round of a batch)
-// *_read checks and returns the values.  The plain forms do both.
+// kernels and the finalize into h->res, mirrored in h->hres (stream-ordered,
+// no synchronisation); after a synchronisation (fetch, or a lock-step round)
+// *_read checks and returns the values from h->hres.  The plain forms do both.
 gpe_status finalize_enq(gpe_handle* h, int nblk, int nq, int post, double* gram);
 gpe_status fetch(gpe_handle* h);   // synchronises: what the last finalize mirrored is in h->hres
 

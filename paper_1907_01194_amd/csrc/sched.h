@@ -6,8 +6,9 @@
 // of each step that needs a scalar back (Round).  The scheduler resumes every
 // problem's coroutine until each has suspended, runs all queued operations
 // (one batched launch per operation and stage for all problems that queued
-// the same operation, single launches for a lone problem), copies every
-// problem's reduction results to the host once and synchronises once, then
+// the same operation, single launches for a lone problem) and synchronises
+// once (the finalize of a reduction stores its results in pinned memory; the
+// state of a device-resident CG is copied, once for all problems), then
 // resumes them all again.  A single solve is the one-problem case.
 #pragma once
 
@@ -130,8 +131,8 @@ class Lockstep {
  public:
   // batch: the batch the problems belong to (null for a lone handle).
   explicit Lockstep(::gpe_batch* batch) : b_(batch) {}
-  // Execute every queued request; with sync, bring all results to the host
-  // and synchronise, else leave the launches queued on the stream.
+  // Execute every queued request; with sync, copy the state of a device-resident
+  // CG if there was one and synchronise, else leave the launches queued.
   gpe_status round(std::vector<Ctx*>& cs, bool sync = true);
   // Resume the drivers round after round until every one has returned.
   gpe_status run(std::vector<Ctx*>& cs);
