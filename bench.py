@@ -44,40 +44,40 @@ VALU_PEAK_TOPS = {"fp64": 256 * 64 * 2.4e9 / 1e12, "mixed": 256 * 128 * 2.4e9 / 
 # VALU instructions (SQ_INSTS_VALU, per wavefront; x64 lanes), by precision and
 # schedule variant; valid only while the kernel sources hash to `src_hash`.
 MEASURED = {
-    "src_hash": "a976946e9c511bd2",
+    "src_hash": "9c90f54301f9d0d1",
     "traffic": {
         "fp64": {
             "0": {
-                "hvp_xpass": 960761303,
-                "lap_axis_y": 705386450,
-                "lap_axis_z": 940000236
+                "hvp_xpass": 960737751,
+                "lap_axis_y": 705255390,
+                "lap_axis_z": 940001259
             },
             "1": {
-                "hvp_xpass": 958755287,
-                "lap_axis_y": 705386450,
-                "lap_axis_z": 940000236
+                "hvp_xpass": 958755288,
+                "lap_axis_y": 705255390,
+                "lap_axis_z": 940001259
             },
             "2": {
-                "hvp_xpass": 960298469,
-                "lap_axis_y": 705386450,
-                "lap_axis_z": 940000236
+                "hvp_xpass": 957742550,
+                "lap_axis_y": 705255390,
+                "lap_axis_z": 940001259
             }
         },
         "mixed": {
             "0": {
-                "hvp_xpass": 479481566,
-                "lap_axis_y": 352743393,
-                "lap_axis_z": 470070766
+                "hvp_xpass": 479486687,
+                "lap_axis_y": 352744417,
+                "lap_axis_z": 470069742
             },
             "1": {
-                "hvp_xpass": 478967520,
-                "lap_axis_y": 352743393,
-                "lap_axis_z": 470070766
+                "hvp_xpass": 478990046,
+                "lap_axis_y": 352744417,
+                "lap_axis_z": 470069742
             },
             "2": {
-                "hvp_xpass": 479326952,
-                "lap_axis_y": 352743393,
-                "lap_axis_z": 470070766
+                "hvp_xpass": 478758621,
+                "lap_axis_y": 352744417,
+                "lap_axis_z": 470069742
             }
         }
     },
@@ -85,12 +85,12 @@ MEASURED = {
         "fp64": {
             "0": 57212900,
             "1": 56877100,
-            "2": 59408400
+            "2": 56946700
         },
         "mixed": {
             "0": 58818600,
             "1": 58245100,
-            "2": 60620800
+            "2": 58298400
         }
     }
 }
